@@ -119,6 +119,14 @@ pe_status pe_system_info(pe_system sys, int32_t *n_vars, int32_t *n_polys, int64
  *   precision PE_DD (complex double-double) or PE_FP64 (complex double).
  *   stream    hipStream_t.
  *
+ * The derivatives are formed as df_p/dx_i = (1/x_i) sum_s a_{s,i} V_s from
+ * the monomials' values V_s where x_i and the products stay within a range
+ * that keeps this as accurate as the forward and backward products of
+ * Section 3.2; the other (polynomial, point) pairs (a coordinate of zero, very
+ * large or small magnitudes, non-finite points) and systems with exponents
+ * above 31 take those products.  The results of the former do not depend on
+ * the schedule; pe_set_schedule and the autotuner choose that of the latter.
+ *
  * Every output entry is written, including the exact zeros of the Jacobian
  * where a polynomial does not depend on a variable.  Results are
  * deterministic: the order of every summation is fixed by the system and
@@ -197,8 +205,8 @@ pe_status pe_eval_jac_paper_layout(pe_system sys, int64_t n_points, pe_cvec poin
                                    void *stream);
 
 /*
- * pe_set_schedule -- pin the launch schedule used by pe_eval_jac for this
- * system: `lanes` lanes cooperate on one monomial (1, 2, 4, 8, 16 or 32),
+ * pe_set_schedule -- pin the launch schedule of pe_eval_jac's forward and
+ * backward products (see there) for this system: `lanes` lanes cooperate on one monomial (1, 2, 4, 8, 16 or 32),
  * `chunk_vars` variables per lane (2, 4 or 8), `threads` per workgroup
  * (64..1024, a multiple of 64) and `groups` workgroups per polynomial for a
  * point.  Passing 0 for these four restores their automatic selection.

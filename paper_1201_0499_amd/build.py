@@ -27,7 +27,8 @@ COMMON = ["-O3", "-std=c++17", "-fPIC", "-ffp-contract=off", "-fno-fast-math", "
 DEVICE = [f"--offload-arch={ARCH}", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
           ]
 
-SOURCES = ["eval.hip", "newton.hip", "track.hip", "ablation.hip", "api.cpp", "schedule.cpp",
+SOURCES = ["eval.hip", "newton.hip", "track.hip", "ablation.hip", "quotient.hip", "small.hip", "api.cpp",
+           "schedule.cpp", "quotient_tables.cpp",
            "newton_api.cpp", "batch_api.cpp", "track_api.cpp", "ablation_api.cpp"]
 
 

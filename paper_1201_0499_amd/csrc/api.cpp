@@ -27,6 +27,7 @@
 #include "eval.hpp"
 #include "internal.hpp"
 #include "newton.hpp"
+#include "quotient_args.hpp"
 #include "schedule.hpp"
 
 namespace pe {
@@ -295,6 +296,8 @@ void System::fill_args(const Schedule &sc, EvalArgs &a) const
     a.any_fold = sc.any_fold;
     a.T = 1;
     a.nbuf = 1;
+    a.repair = 0;
+    a.merge = 1;
     a.word = (const uint32_t *)sc.word.ptr;
     a.dest = (const uint16_t *)sc.dest.ptr;
     a.vdest = (const uint16_t *)sc.vdest.ptr;
@@ -305,9 +308,142 @@ void System::fill_args(const Schedule &sc, EvalArgs &a) const
     a.group_info = (const int4 *)sc.group_info.ptr;
 }
 
+// Tables of the quotient kernels, packed and uploaded once per chunk size.
+pe_status System::quot_for(int words, bool find_only, Quot **out)
+{
+    *out = nullptr;
+    if (!quot_ok) return PE_OK;
+    const int CH = quot_chunk(n_vars, max_exp, quot_pad, quot_max_m, words);
+    if (CH == 0) return PE_OK;
+    for (auto &q : quots)
+        if (q->CH == CH) {
+            *out = q.get();
+            return PE_OK;
+        }
+    if (find_only) return PE_OK;
+    QuotTables t;
+    t.CH = CH;
+    t.pad = quot_pad;
+    CsrView v{n_vars, n_polys, n_monos, poly_start.data(), mono_start.data(), pos.data(), exp.data()};
+    if (!build_quot_tables(v, t).empty()) {
+        quot_ok = false;  // outside the packing: the general kernel serves
+        return PE_OK;
+    }
+    std::vector<double> c(t.mono.size() * 4);
+    for (size_t i = 0; i < t.mono.size(); ++i)
+        std::copy_n(coef_host.data() + 4 * (size_t)t.mono[i], 4, c.data() + 4 * i);
+    std::unique_ptr<Quot> q(new Quot());
+    q->CH = CH;
+    q->n_blk = t.n_blk;
+    q->multi = t.multi;
+    hipError_t e = q->coef.upload(c.data(), c.size() * sizeof(double));
+#define PE_UP(buf)                                                          \
+    if (e == hipSuccess) e = q->buf.upload(t.buf.data(), t.buf.size() * sizeof(t.buf[0]));
+    PE_UP(words)
+    PE_UP(slice)
+    PE_UP(chunk)
+    PE_UP(poly)
+    PE_UP(block)
+    PE_UP(runs)
+    PE_UP(out)
+#undef PE_UP
+    if (e != hipSuccess) return hip_fail(e, "uploading the quotient tables");
+    *out = q.get();
+    quots.push_back(std::move(q));
+    return PE_OK;
+}
+
+void System::fill_quot(const Quot &q, QuotArgs &a) const
+{
+    a = QuotArgs{};
+    a.n_vars = n_vars;
+    a.n_polys = n_polys;
+    a.D = max_exp;
+    a.pad = quot_pad;
+    a.CH = q.CH;
+    a.n_blk = q.n_blk;
+    a.multi = q.multi;
+    a.PP = 1;
+    a.nbuf = 1;
+    const int b = quot_point_exp(max_exp) - 1;
+    a.x_lo = (uint32_t)(1023 - b) << 20;
+    a.x_span = (uint32_t)(2 * b + 1) << 20;
+    a.words = (const uint2 *)q.words.ptr;
+    a.coef = (const double *)q.coef.ptr;
+    a.slice = (const int2 *)q.slice.ptr;
+    a.chunk = (const int4 *)q.chunk.ptr;
+    a.poly = (const int4 *)q.poly.ptr;
+    a.block = (const int2 *)q.block.ptr;
+    a.runs = (const uint16_t *)q.runs.ptr;
+    a.out = (const uint16_t *)q.out.ptr;
+    a.sys_coef = (const double *)coef.ptr;
+}
+
+// Lanes per monomial and per run on nt threads: as many as fit one round.
+void quot_lanes(QuotArgs &a, int m, int nt)
+{
+    const int ranks = a.n_blk * kRankBlock;
+    a.log2L = m * 4 <= nt ? 2 : (m * 2 <= nt ? 1 : 0);
+    a.log2S = ranks * 4 <= nt ? 2 : (ranks * 2 <= nt ? 1 : 0);
+}
+
+hipError_t System::run_quot(const Quot &q, int prec, int cc, int maxt, EvalArgs a, unsigned threads,
+                            size_t lds, hipStream_t hs) const
+{
+    const int words = prec == 0 ? 2 : (prec == 1 ? 4 : 8);
+    const bool jac = a.J[0] != nullptr;
+    QuotArgs qa;
+    fill_quot(q, qa);
+    qa.n_points = a.n_points;
+    for (int p = 0; p < 8; ++p) {
+        qa.x[p] = a.x[p];
+        qa.f[p] = a.f[p];
+        qa.J[p] = a.J[p];
+    }
+    qa.mask = a.mask;
+    // the general kernel takes whole polynomials
+    a.repair = 1;
+    a.merge = a.G;
+    a.G = 1;
+    a.n_groups = n_polys;
+    const int64_t P = a.n_points, units = P * n_polys;
+    const int m = (int)std::max<int64_t>(1, std::min<int64_t>(quot_max_m, q.CH));
+    const auto lds_for = [&](int T, int nbuf) {
+        return quot_lds_bytes(n_vars, max_exp, quot_pad, q.CH, q.multi, nbuf, T * words);
+    };
+    if (units <= kSmallUnits && a.T == 1 && a.nbuf == 1) {
+        quot_lanes(qa, m, (int)threads);
+        return launch_small(prec, cc, maxt, a, qa, dim3((unsigned)n_polys, (unsigned)P, 1), threads,
+                            std::max(lds, lds_for(1, 1) + 16), hs);
+    }
+    const int cap = prec == 2 ? 512 : 1024;  // threads a CU's registers hold (and a workgroup's limit)
+    const int T = prec == 0 && P >= kPointsF64 && lds_for(kPointsF64, 1) <= (size_t)kMaxLds ? kPointsF64 : 1;
+    if (lds_for(T, 2) <= (size_t)kMaxLds) qa.nbuf = 2;
+    const size_t qlds = lds_for(T, qa.nbuf);
+    const int per_cu = (int)std::max<size_t>(1, kMaxLds / qlds);
+    // the smallest workgroups that fill the CU's registers, no larger than
+    // one round of lanes can use
+    int nt = 64;
+    while (nt < cap && nt * per_cu < cap) nt *= 2;
+    const int most = (std::max(m, jac ? q.n_blk * kRankBlock : 1) * kParts + 63) / 64 * 64;
+    nt = std::min(nt, most);
+    quot_lanes(qa, m, nt);
+    // several polynomials per workgroup share one power table, while the
+    // workgroups still make eight rounds of the chip
+    const int64_t resident = 256 * std::max(1, std::min(per_cu, cap / nt));
+    const int64_t tiles = (P + T - 1) / T;
+    qa.PP = (int)std::max<int64_t>(1, std::min<int64_t>(8, tiles * n_polys / (resident * 8)));
+    const dim3 grid((unsigned)((n_polys + qa.PP - 1) / qa.PP), (unsigned)std::min<int64_t>(tiles, 65535), 1);
+    hipError_t e = launch_quot(prec, T, qa, grid, (unsigned)nt, qlds, hs);
+    if (e != hipSuccess) return e;
+    // few workgroups, so that looking for work costs little when there is none
+    const int64_t gy = std::min<int64_t>((P + a.T - 1) / a.T, std::max<int64_t>(1, 2048 / n_polys));
+    return launch_eval(prec, cc, maxt, a, dim3((unsigned)n_polys, (unsigned)gy, 1), dim3(threads), lds, hs);
+}
+
 pe_status System::eval_locked(int64_t n_points, const double *const x[4], double *const f[4],
                               double *const J[4], bool dd, hipStream_t hs, const int32_t *mask,
-                              bool no_alloc)
+                              bool no_alloc, bool quotients)
 {
     Schedule *sc = nullptr;
     pe_status st = no_alloc ? find_schedule(n_points, &sc) : schedule_for(n_points, &sc);
@@ -364,6 +500,14 @@ pe_status System::eval_locked(int64_t n_points, const double *const x[4], double
         if (!no_alloc) a.partial = (double *)partial.ptr;
     }
     const int maxt = sc->nt <= 256 ? 256 : (sc->nt <= 512 ? 512 : 1024);
+    Quot *quot = nullptr;
+    if (quotients) st = quot_for(words, no_alloc, &quot);
+    if (st != PE_OK) return st;
+    if (quot) {
+        hipError_t e = run_quot(*quot, dd ? 1 : 0, sc->cc, maxt, a, (unsigned)sc->nt, lds, hs);
+        if (e != hipSuccess) return hip_fail(e, "launching the evaluation by quotients");
+        return PE_OK;
+    }
     const int64_t gy = std::min<int64_t>((n_points + T - 1) / T, 65535);
     dim3 grid((unsigned)a.n_groups, (unsigned)gy, 1);
     dim3 block((unsigned)sc->nt, 1, 1);
@@ -384,6 +528,8 @@ hipError_t library_init()
     std::call_once(g_init_once, [] {
         g_init_err = eval_kernels_init();
         if (g_init_err == hipSuccess) g_init_err = newton_kernels_init();
+        if (g_init_err == hipSuccess) g_init_err = quot_kernels_init();
+        if (g_init_err == hipSuccess) g_init_err = small_kernels_init();
     });
     return g_init_err;
 }
@@ -472,12 +618,21 @@ pe_status pe_create_system(int32_t n_vars, int32_t n_polys, int64_t n_monos,
         c[4 * s + 2] = coef.im_hi[s];
         c[4 * s + 3] = coef.im_lo[s];
     }
+    // the quotient kernels need coefficients in their products' range (or zero)
+    S->quot_ok = true;
+    for (int64_t s = 0; s < n_monos && S->quot_ok; ++s) {
+        const double big = std::max(std::fabs(c[4 * s + 0]), std::fabs(c[4 * s + 2]));
+        S->quot_ok = big == 0.0 ? c[4 * s + 1] == 0.0 && c[4 * s + 3] == 0.0
+                                : std::abs(std::ilogb(big)) < kProductExp;
+    }
+    quot_shape(CsrView{n_vars, n_polys, n_monos, poly_start, mono_start, pos, exp}, S->quot_pad, S->quot_max_m);
     if (hipGetDevice(&S->device) != hipSuccess) return fail(PE_EDEVICE, "hipGetDevice failed");
     // the device address of the static scratch, looked up once per device
     he = static_scratch_setup();
     if (he != hipSuccess) return hip_fail(he, "locating the static scratch");
     he = S->coef.upload(c.data(), c.size() * sizeof(double));
     if (he != hipSuccess) return hip_fail(he, "uploading coefficients");
+    if (S->quot_ok) S->coef_host = std::move(c);
     if (nnz >= ((int64_t)1 << 31)) return fail(PE_EUNSUPPORTED, "more than 2^31 support entries");
     {
         std::vector<int32_t> ms32((size_t)n_monos + 1);
@@ -567,6 +722,8 @@ pe_status pe_get_schedule(pe_system sys, int64_t n_points, int32_t *lanes, int32
         if (st != PE_OK) return st;
         int T = 1, nbuf = 1;
         S->launch_shape(*sc, n_points, true, T, nbuf);
+        Quot *quot = nullptr;  // packed with them
+        if ((st = S->quot_for(4, false, &quot)) != PE_OK) return st;
         if (tile_points) *tile_points = T;
         if (stage_buffers) *stage_buffers = nbuf;
     }
@@ -701,6 +858,14 @@ pe_status pe_eval_jac_qd(pe_system sys, int64_t n_points, const double *const *p
             if (e != hipSuccess) return hip_fail(e, "allocating partial sums");
         }
         a.partial = (double *)S->partial.ptr;
+    }
+    Quot *quot = nullptr;
+    st = S->quot_for(8, false, &quot);
+    if (st != PE_OK) return st;
+    if (quot) {
+        hipError_t e = S->run_quot(*quot, 2, cc, nt, a, (unsigned)nt, lds, hs);
+        if (e != hipSuccess) return hip_fail(e, "launching the quad-double evaluation by quotients");
+        return PE_OK;
     }
     const int64_t gy = std::min<int64_t>(n_points, 65535);
     dim3 grid((unsigned)a.n_groups, (unsigned)gy, 1);

@@ -55,6 +55,14 @@ struct Batch {
     size_t lds_dd = 0, lds_64 = 0;
     int grid = 0;
     DevBuf desc, tasks;
+    // the quotient kernel's launch for each precision (0 = FP64, 1 = double-
+    // double): descriptors, workgroup size, LDS and grid; threads 0 if no
+    // system of the batch is within those kernels
+    struct QuotLaunch {
+        DevBuf desc;
+        int threads = 0, grid = 0;
+        size_t lds = 0;
+    } quot[2];
     std::mutex mu;
 };
 
@@ -62,6 +70,60 @@ static int lanes_for(int k, const BatchConfig &c)
 {
     int L = next_pow2(std::max(1, (std::max(1, k) + c.cc - 1) / c.cc)) * c.lanes_mult;
     return std::min(L, 32);
+}
+
+// Descriptors and launch shape of the quotient kernel in one precision, for
+// the batch's systems and tasks.
+static pe_status build_quot(Batch &B, const std::vector<BatchDesc> &descs, int dd)
+{
+    Batch::QuotLaunch &ql = B.quot[dd];
+    const int words = dd ? 4 : 2, ns = (int)B.sys.size();
+    std::vector<QuotBatchDesc> qd((size_t)ns);
+    size_t lds1 = 0, lds2 = 0;
+    int most = 0;
+    ql.threads = 0;
+    for (int i = 0; i < ns; ++i) {
+        System &S = *B.sys[(size_t)i];
+        qd[(size_t)i].a = QuotArgs{};
+        qd[(size_t)i].a.n_polys = S.n_polys;
+        qd[(size_t)i].x_off = descs[(size_t)i].x_off;
+        qd[(size_t)i].f_off = descs[(size_t)i].f_off;
+        qd[(size_t)i].J_off = descs[(size_t)i].J_off;
+        Quot *q = nullptr;
+        {
+            std::lock_guard<std::mutex> lock(S.mu);
+            pe_status st = S.quot_for(words, false, &q);
+            if (st != PE_OK) return st;
+        }
+        if (!q) continue;
+        S.fill_quot(*q, qd[(size_t)i].a);
+        const auto lds = [&](int nbuf) {
+            return quot_lds_bytes(S.n_vars, S.max_exp, S.quot_pad, q->CH, q->multi, nbuf, words);
+        };
+        lds1 = std::max(lds1, lds(1));
+        lds2 = std::max(lds2, lds(2));
+        most = std::max(most, (int)std::max<int64_t>(std::min<int64_t>(S.quot_max_m, q->CH),
+                                                     q->n_blk * kRankBlock));
+    }
+    if (lds1 == 0) return PE_OK;
+    // two buffers of values unless they cost residency
+    const int nbuf = (size_t)kMaxLds / lds2 >= std::min<size_t>(4, kMaxLds / lds1) ? 2 : 1;
+    ql.lds = nbuf == 2 ? lds2 : lds1;
+    const int per_cu = (int)std::max<size_t>(1, kMaxLds / ql.lds);
+    int nt = 64;
+    while (nt < 1024 && nt * per_cu < 1024) nt *= 2;
+    nt = std::max(64, std::min(nt, (most * kParts + 63) / 64 * 64));
+    for (int i = 0; i < ns; ++i) {
+        QuotArgs &a = qd[(size_t)i].a;
+        if (a.CH == 0) continue;
+        a.nbuf = nbuf;
+        quot_lanes(a, (int)std::max<int64_t>(1, std::min<int64_t>(B.sys[(size_t)i]->quot_max_m, a.CH)), nt);
+    }
+    const hipError_t e = ql.desc.upload(qd.data(), qd.size() * sizeof(QuotBatchDesc));
+    if (e != hipSuccess) return hip_fail(e, "uploading batch tables");
+    ql.threads = nt;
+    ql.grid = 256 * std::max(1, std::min(per_cu, 1024 / nt));
+    return PE_OK;
 }
 
 // (Re)build descriptors and tasks for `pps` points per system.
@@ -128,6 +190,11 @@ static pe_status build_batch(Batch &B, const std::vector<int64_t> &pps, hipStrea
     hipError_t e = B.desc.upload(descs.data(), descs.size() * sizeof(BatchDesc));
     if (e == hipSuccess) e = B.tasks.upload(tv.data(), tv.size() * sizeof(BatchTask));
     if (e != hipSuccess) return hip_fail(e, "uploading batch tables");
+    for (int dd = 0; dd < 2; ++dd) {
+        pe_status st = build_quot(B, descs, dd);
+        if (st != PE_OK) return st;
+        B.quot[dd].grid = (int)std::min<int64_t>((int64_t)tv.size(), B.quot[dd].grid);
+    }
     B.n_tasks = (int64_t)tv.size();
     B.lds_dd = lds_max;
     B.lds_64 = lds_max / 2;
@@ -147,7 +214,8 @@ static pe_status build_batch(Batch &B, const std::vector<int64_t> &pps, hipStrea
 }
 
 static pe_status launch_batch_eval(Batch &B, const std::vector<int64_t> &pps, pe_cvec points,
-                                   pe_cvec out_f, pe_cvec out_J, bool dd, hipStream_t hs)
+                                   pe_cvec out_f, pe_cvec out_J, bool dd, hipStream_t hs,
+                                   bool quotients = true)
 {
     if (!B.built || !(B.built_cfg == B.cfg) || B.built_pps != pps) {
         pe_status st = build_batch(B, pps, hs);
@@ -166,6 +234,23 @@ static pe_status launch_batch_eval(Batch &B, const std::vector<int64_t> &pps, pe
         a.x[q] = x[q];
         a.f[q] = f[q];
         a.J[q] = jac ? J[q] : nullptr;
+    }
+    a.repair = 0;
+    const Batch::QuotLaunch &ql = B.quot[dd ? 1 : 0];
+    if (quotients && ql.threads) {
+        QuotBatchArgs qa{};
+        qa.desc = (const QuotBatchDesc *)ql.desc.ptr;
+        qa.tasks = a.tasks;
+        qa.n_tasks = a.n_tasks;
+        for (int q = 0; q < 4; ++q) {
+            qa.x[q] = a.x[q];
+            qa.f[q] = a.f[q];
+            qa.J[q] = a.J[q];
+        }
+        const hipError_t qe = launch_quot_batch(dd ? 1 : 0, qa, (unsigned)ql.grid, (unsigned)ql.threads,
+                                                ql.lds, hs);
+        if (qe != hipSuccess) return hip_fail(qe, "launching the batch kernel");
+        a.repair = 1;  // the general kernel serves what the quotients refused
     }
     const int maxt = B.cfg.nt <= 256 ? 256 : (B.cfg.nt <= 512 ? 512 : 1024);
     hipError_t e = launch_batch(dd ? 1 : 0, B.cfg.cc, maxt, a, dim3((unsigned)B.grid),
@@ -396,7 +481,7 @@ pe_status pe_autotune_batch(pe_batch b, const int64_t *points_per_system, pe_cve
         B->cfg = c;
         float ms = 0.f;
         pe_status st = time_calls(hs, 2, [&](hipStream_t ts) {
-            return launch_batch_eval(*B, pps, points, out_f, out_J, dd, ts);
+            return launch_batch_eval(*B, pps, points, out_f, out_J, dd, ts, false);
         }, ms);
         if (st == PE_EUNSUPPORTED) continue;  // e.g. LDS too large for this schedule
         if (st != PE_OK) return st;
@@ -454,7 +539,7 @@ pe_status pe_autotune_system(pe_system sys, int64_t n_points, pe_cvec points, pe
         }
         auto call = [&](hipStream_t ts) {
             std::lock_guard<std::mutex> lock(S->mu);
-            return S->eval_locked(n_points, x, f, J, dd, ts, nullptr);
+            return S->eval_locked(n_points, x, f, J, dd, ts, nullptr, false, false);
         };
         // calls per timed graph: about 20 ms of work, 1 to 10 calls
         float ms = 0.f;

@@ -243,6 +243,29 @@ struct LdsVec<Arith64> {
     }
 };
 
+// Workgroups are handed to the 8 XCDs of the chip in turn (workgroup i to
+// XCD i mod 8), and each XCD has its own L2.  This maps the workgroup index
+// to the share it works on so that each XCD takes a contiguous range of
+// shares: the polynomials whose output entries share cache lines (J is
+// polynomial-minor) then write them through one L2.  A bijection of
+// [0, count) for any count; the results do not depend on it.
+__device__ __forceinline__ int xcd_order(int i, int count)
+{
+    constexpr int kXcds = 8;
+    const int xcd = i % kXcds, slot = i / kXcds;
+    const int q = count / kXcds, r = count % kXcds;
+    return xcd * q + min(xcd, r) + slot;
+}
+
+// The leading word of a value that a quotient kernel leaves to the general
+// kernel: a NaN that no computed value of that kernel can be (those are
+// finite).
+__device__ __forceinline__ double refused() { return __longlong_as_double(0x7FF8A55E55EDD1F7ll); }
+__device__ __forceinline__ bool is_refused(double v)
+{
+    return __double_as_longlong(v) == 0x7FF8A55E55EDD1F7ll;
+}
+
 template <class A>
 struct Io;
 

@@ -32,6 +32,10 @@ struct EvalArgs {
     int32_t any_fold;     // 1 if some polynomial's constant last monomial is folded
     int32_t T;            // points per workgroup tile (1..32)
     int32_t nbuf;         // staging buffers: 1, or 2 (one barrier per item)
+    int32_t repair;       // 1: only the (polynomial, point) pairs that a quotient
+                          //   kernel left (f's leading word is refused()); needs G = 1
+    int32_t merge;        // shares of the tables' split that one workgroup takes
+                          //   together (1, or all of a polynomial's)
     // packed tables (schedule order = system order)
     const uint32_t *word;          // [M][KP]
     const uint16_t *dest;          // [M][KP] staging slot of each derivative term
@@ -76,6 +80,7 @@ struct BatchArgs {
     const double *x[4];
     double *f[4];
     double *J[4];
+    int32_t repair;  // 1: only polynomials that a quotient kernel left
 };
 
 hipError_t launch_batch(int prec, int cc, int maxt, const BatchArgs &args, dim3 grid, dim3 block,

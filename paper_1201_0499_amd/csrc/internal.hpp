@@ -10,6 +10,7 @@
 
 #include "polyeval.h"
 #include "eval.hpp"
+#include "quotient_args.hpp"
 
 namespace pe {
 
@@ -44,6 +45,20 @@ struct Schedule {
     size_t lds_bytes(int words, int T = 1, int nbuf = 1) const;
 };
 
+// Calls of at most this many (polynomial, point) pairs run in one launch
+// (small.hip): two workgroups per CU.
+constexpr int64_t kSmallUnits = 512;
+
+// Packed tables of one system for the quotient kernels (quotient.hpp).
+struct Quot {
+    int CH = 0, n_blk = 0;
+    bool multi = false;
+    DevBuf words, coef, slice, chunk, poly, block, runs, out;
+};
+
+// lanes per monomial (of at most m in a chunk) and per run for nt threads
+void quot_lanes(QuotArgs &a, int m, int nt);
+
 struct System {
     int32_t n_vars = 0, n_polys = 0;
     int64_t n_monos = 0;
@@ -52,6 +67,13 @@ struct System {
     std::vector<int64_t> poly_start, mono_start;
     std::vector<int32_t> pos, exp;
     DevBuf coef;  // [M][4]
+    // for the quotient kernels: coefficients (host), whether their range and
+    // the exponents allow these kernels at all, and the most monomials of a
+    // polynomial without its folded constant
+    std::vector<double> coef_host;
+    bool quot_ok = false, quot_pad = true;
+    int64_t quot_max_m = 0;
+    std::vector<std::unique_ptr<Quot>> quots;
     // schedule selection: pinned values (0 = automatic)
     int pin_L = 0, pin_cc = 0, pin_nt = 0, pin_G = 0;
     // points per tile and staging buffers (0 = automatic)
@@ -85,12 +107,24 @@ struct System {
     pe_status schedule_with(int L, int cc, int nt, int G, Schedule **out);
     // launch arguments of a schedule (points, outputs and mask unset)
     void fill_args(const Schedule &sc, EvalArgs &a) const;
+    // the quotient tables for values of `words` doubles: *out is nullptr if
+    // the system is outside those kernels (or, with find_only, not packed yet)
+    pe_status quot_for(int words, bool find_only, Quot **out);
+    // launch arguments of the quotient kernels (points, outputs, mask and
+    // launch shape unset)
+    void fill_quot(const Quot &q, QuotArgs &a) const;
+    // evaluation by quotients (prec 0 = FP64, 1 = double-double, 2 =
+    // quad-double) of the points, outputs and mask of `a`, whose general
+    // kernel with maxt, threads and lds bytes serves what they refuse
+    hipError_t run_quot(const Quot &q, int prec, int cc, int maxt, EvalArgs a, unsigned threads, size_t lds,
+                        hipStream_t hs) const;
     // evaluation with the lock held; J[0] == nullptr skips the Jacobian,
     // mask (optional) skips points whose entry is not -1.  no_alloc: use
-    // only existing schedule tables and the static scratch, allocate nothing
+    // only existing schedule tables and the static scratch, allocate nothing;
+    // quotients = false: the general kernel alone (the autotuner times it)
     pe_status eval_locked(int64_t n_points, const double *const x[4], double *const f[4],
                           double *const J[4], bool dd, hipStream_t stream, const int32_t *mask,
-                          bool no_alloc = false);
+                          bool no_alloc = false, bool quotients = true);
 };
 
 // Newton's method from n_starts starts (the body of pe_newton, called with

@@ -1,0 +1,100 @@
+// Evaluation with the Jacobian by quotients: tables, launch arguments and
+// launch wrappers (kernels in quotient.hip, packing in quotient_tables.cpp).
+//
+// With V_s = c_s x^{a_s} the value of monomial s (Section 2, equation (1)),
+//
+//     f_p = sum_s V_s,     df_p/dx_i = (1 / x_i) sum_s a_{s,i} V_s,
+//
+// so a monomial of k variables costs k products for its value and one scaled
+// addition per variable, where the forward and backward products of
+// Section 3.2 with their common factor cost about 5k products.  The quotient
+// exists only for x_i != 0, and the products must stay away from overflow
+// and underflow; see the rules below.  Whatever they refuse goes to the
+// general kernel (eval.hip), which has no such restriction.
+#pragma once
+
+#include <stdint.h>
+
+#include <string>
+#include <vector>
+
+#include "schedule.hpp"
+
+namespace pe {
+
+// Factors x_i^{a_i} of a monomial are multiplied in quads.  The canonical
+// order of a monomial's product (and so every bit of it) does not depend on
+// how many lanes take part: its quads fall into kParts contiguous ranges,
+// each range is multiplied from the left, then (r0 r1)(r2 r3).  A run of
+// terms is added in kParts interleaved partial sums, combined the same way.
+constexpr int kQuad = 4;
+constexpr int kParts = 4;
+// Outputs of a chunk are summed in blocks of kRankBlock ranks (by run
+// length), padded to the longest run of the block.
+constexpr int kRankBlock = 16;
+// An entry of a run: position of the monomial's value in the chunk in the
+// low kEntryBits bits, the exponent above them; padding has exponent 0.
+constexpr int kEntryBits = 11;
+constexpr int kMaxQuotExp = (1 << (16 - kEntryBits)) - 1;
+constexpr int kMaxQuotChunk = 1024;  // monomials per chunk, at most (<= 2^kEntryBits)
+
+// Range rules.  Partial products of a monomial (quads of factors apart) must
+// have a binary exponent within +-kProductExp, which the kernel checks; a
+// quad of factors is bounded beforehand, by the points: every |x_i| (larger
+// part) within 2^+-b, b from quot_point_exp.  With coefficients within
+// 2^+-kProductExp (or zero) no product, nor an error term of quad-double
+// arithmetic, overflows or becomes subnormal.
+constexpr int kProductExp = 300;
+constexpr int kQuadExp = 400;
+
+// Largest binary exponent of a coordinate (either sign) for maximal exponent
+// d: kQuad factors of at most 2^(d (b + 1/2)) each stay within 2^kQuadExp.
+inline int quot_point_exp(int d)
+{
+    const int b = (2 * kQuadExp / kQuad - d) / (2 * d);
+    return b < 0 ? 0 : (b > 60 ? 60 : b);
+}
+
+// Packed tables of one system for chunks of CH monomials.  Monomials of a
+// polynomial are ordered by their number of variables, most first (stable),
+// so that the 64 monomials of a slice need about the same number of quads;
+// one constant monomial per polynomial is folded into the value output.
+struct QuotTables {
+    int CH = 0;            // monomials per chunk (a multiple of 64)
+    int n_blk = 0;         // rank blocks per chunk
+    bool pad = true;       // the power table has an entry 1 for incomplete quads (set by
+                           //   the caller; may be false if every monomial but the
+                           //   folded ones has the same number of variables, a
+                           //   multiple of kQuad)
+    bool multi = false;    // some polynomial has more than one chunk
+    int n_chunks = 0;
+    std::vector<uint16_t> words;     // per slice [quads][monomials][kQuad]: power-table
+                                     //   entry (a-1) n + variable, or d n: the entry 1
+    std::vector<int32_t> mono;       // [monomials in table order]: index in the system
+    std::vector<int32_t> slice;      // [slices][2]: first quad in words, quads
+    std::vector<int32_t> chunk;      // [chunks][4]: first monomial (table order),
+                                     //   monomials, first slice, first rank block
+    std::vector<int32_t> poly;       // [n_polys][4]: first chunk, end chunk, 1 + index
+                                     //   of the folded constant (0: none), 0
+    std::vector<int32_t> block;      // [chunks][n_blk][2]: first row, rows
+    std::vector<uint16_t> runs;      // [rows][kRankBlock][kParts] entries
+    std::vector<uint16_t> out;       // [chunks][n_blk * kRankBlock]: output of a rank
+                                     //   (0xFFFF past the last)
+};
+
+// Monomials per chunk for values of `words` doubles: what one workgroup's
+// LDS holds, at most kMaxQuotChunk; 0 if the power table leaves no room or
+// the system is outside the packing (exponents, variables).
+int quot_chunk(int n_vars, int max_exp, bool pad, int64_t max_m, int words);
+
+// LDS bytes of a workgroup with nbuf buffers of chunk values.
+size_t quot_lds_bytes(int n_vars, int max_exp, bool pad, int CH, bool multi, int nbuf, int words);
+
+// Whether the power table needs the entry 1 (see QuotTables::pad), and the
+// most monomials of a polynomial without its folded constant.
+void quot_shape(const CsrView &S, bool &pad, int64_t &max_m);
+
+// Fill t for chunks of t.CH monomials; empty string on success.
+std::string build_quot_tables(const CsrView &S, QuotTables &t);
+
+}  // namespace pe

@@ -1,0 +1,536 @@
+// Device code of the quotient evaluation (quotient.hip describes it), shared
+// by its kernels and by the single-launch kernel of small.hip.
+//
+// The arithmetic A is a policy of dd.hpp / qd.hpp for one point, or
+// PointsF64<T>: T points side by side in FP64, which share every index,
+// address and exponent of the tables.
+#pragma once
+
+#include <algorithm>
+
+#include "dd.hpp"
+#include "device.hpp"
+#include "packing.hpp"
+#include "quotient_args.hpp"
+
+namespace pe {
+
+// ---------------------------------------------------------------------------
+// T points in FP64
+// ---------------------------------------------------------------------------
+
+template <int T>
+struct PointsF64 {
+    struct C {
+        Arith64::C v[T];
+    };
+    template <class F>
+    __device__ __forceinline__ static C each(const F &f)
+    {
+        C r;
+#pragma unroll
+        for (int t = 0; t < T; ++t) r.v[t] = f(t);
+        return r;
+    }
+    __device__ __forceinline__ static C zero()
+    {
+        return each([](int) { return Arith64::zero(); });
+    }
+    __device__ __forceinline__ static C one()
+    {
+        return each([](int) { return Arith64::one(); });
+    }
+    __device__ __forceinline__ static C mul(const C &a, const C &b)
+    {
+        return each([&](int t) { return Arith64::mul(a.v[t], b.v[t]); });
+    }
+    __device__ __forceinline__ static C sum(const C &a, const C &b)
+    {
+        return each([&](int t) { return Arith64::sum(a.v[t], b.v[t]); });
+    }
+};
+
+// entries of T values of 16 bytes, so that one address serves all points
+template <int T>
+struct LdsVec<PointsF64<T>> {
+    using C = typename PointsF64<T>::C;
+    double2 *p;
+    __device__ __forceinline__ C get(int i) const
+    {
+        const double2 *q = p + T * i;
+        return PointsF64<T>::each([&](int t) { return Arith64::C{q[t].x, q[t].y}; });
+    }
+    __device__ __forceinline__ void put(int i, const C &c) const
+    {
+#pragma unroll
+        for (int t = 0; t < T; ++t) p[T * i + t] = make_double2(c.v[t].re, c.v[t].im);
+    }
+    __device__ __forceinline__ static LdsVec at(double2 *raw, int count, double2 *&next)
+    {
+        next = raw + T * (size_t)count;
+        return {raw};
+    }
+};
+
+// What differs between one point and several: loads, stores, range checks,
+// lane exchanges and sums over the wave.
+template <class A>
+struct Pts {
+    using C = typename A::C;
+    using One = A;
+    static constexpr int T = 1;
+    __device__ __forceinline__ static const typename A::C &at(const C &c, int) { return c; }
+    __device__ __forceinline__ static typename A::C &at(C &c, int) { return c; }
+    __device__ __forceinline__ static C all(const typename A::C &v) { return v; }
+    template <int M>
+    __device__ __forceinline__ static C sum_over(const C &v)
+    {
+        return sum_xor<A, M>(v);
+    }
+    __device__ __forceinline__ static C other(const C &v, int d) { return shfl_xor_c(v, d); }
+};
+
+template <int N>
+struct Pts<PointsF64<N>> {
+    using A = PointsF64<N>;
+    using C = typename A::C;
+    using One = Arith64;
+    static constexpr int T = N;
+    __device__ __forceinline__ static const Arith64::C &at(const C &c, int t) { return c.v[t]; }
+    __device__ __forceinline__ static Arith64::C &at(C &c, int t) { return c.v[t]; }
+    __device__ __forceinline__ static C all(const Arith64::C &v)
+    {
+        return A::each([&](int) { return v; });
+    }
+    template <int M>
+    __device__ __forceinline__ static C sum_over(const C &v)
+    {
+        return A::each([&](int t) { return sum_xor<Arith64, M>(v.v[t]); });
+    }
+    __device__ __forceinline__ static C other(const C &v, int d)
+    {
+        return A::each([&](int t) { return shfl_xor_c(v.v[t], d); });
+    }
+};
+
+// ---------------------------------------------------------------------------
+// sums of a * V with a small integer a
+// ---------------------------------------------------------------------------
+
+template <class A>
+struct RunAcc;
+
+template <>
+struct RunAcc<Arith64> {
+    Arith64::C s;
+    __device__ __forceinline__ void clear() { s = Arith64::zero(); }
+    __device__ __forceinline__ void add(const Arith64::C &v, double a)
+    {
+        s.re = fma(a, v.re, s.re);
+        s.im = fma(a, v.im, s.im);
+    }
+    __device__ __forceinline__ Arith64::C get() const { return s; }
+};
+
+template <int T>
+struct RunAcc<PointsF64<T>> {
+    using C = typename PointsF64<T>::C;
+    RunAcc<Arith64> s[T];
+    __device__ __forceinline__ void clear()
+    {
+#pragma unroll
+        for (int t = 0; t < T; ++t) s[t].clear();
+    }
+    __device__ __forceinline__ void add(const C &v, double a)
+    {
+#pragma unroll
+        for (int t = 0; t < T; ++t) s[t].add(v.v[t], a);
+    }
+    __device__ __forceinline__ C get() const
+    {
+        return PointsF64<T>::each([&](int t) { return s[t].get(); });
+    }
+};
+
+template <>
+struct RunAcc<ArithDD> {
+    DWAcc re, im;
+    __device__ __forceinline__ void clear()
+    {
+        re = {0.0, 0.0};
+        im = {0.0, 0.0};
+    }
+    // s + a v: a v.hi exactly as p + e, p into s by TwoSum, everything else
+    // (of relative order u) into the FP64 compensation
+    __device__ __forceinline__ static void one(DWAcc &s, const dd &v, double a)
+    {
+        const dd p = two_prod(a, v.hi);
+        const dd t = two_sum(s.s, p.hi);
+        s.s = t.hi;
+        s.c = s.c + (t.lo + fma(a, v.lo, p.lo));
+    }
+    __device__ __forceinline__ void add(const ArithDD::C &v, double a)
+    {
+        one(re, v.re, a);
+        one(im, v.im, a);
+    }
+    __device__ __forceinline__ ArithDD::C get() const { return {dw_acc_get(re), dw_acc_get(im)}; }
+};
+
+template <>
+struct RunAcc<ArithQD> {
+    ArithQD::C s;
+    __device__ __forceinline__ void clear() { s = ArithQD::zero(); }
+    __device__ __forceinline__ void add(const ArithQD::C &v, double a)
+    {
+        s = ArithQD::add(s, ArithQD::scale(v, a));
+    }
+    __device__ __forceinline__ ArithQD::C get() const { return s; }
+};
+
+// 1 / x
+__device__ __forceinline__ Arith64::C quot_inv(const Arith64::C &x) { return Arith64::inv(x); }
+__device__ __forceinline__ ArithDD::C quot_inv(const ArithDD::C &x) { return ArithDD::inv(x); }
+// from the double-double reciprocal y, with e = 1 - x y of order 2^-103:
+// y + y (e + e^2), the rest e^3
+__device__ __forceinline__ ArithQD::C quot_inv(const ArithQD::C &x)
+{
+    const ArithDD::C d = ArithDD::inv({{x.re.x0, x.re.x1}, {x.im.x0, x.im.x1}});
+    const ArithQD::C y{{d.re.hi, d.re.lo, 0.0, 0.0}, {d.im.hi, d.im.lo, 0.0, 0.0}};
+    const ArithQD::C e = ArithQD::add(ArithQD::one(), ArithQD::neg(ArithQD::mul(x, y)));
+    return ArithQD::add(y, ArithQD::mul(y, ArithQD::add(e, ArithQD::mul(e, e))));
+}
+
+__device__ __forceinline__ double lead_re(const Arith64::C &v) { return v.re; }
+__device__ __forceinline__ double lead_im(const Arith64::C &v) { return v.im; }
+__device__ __forceinline__ double lead_re(const ArithDD::C &v) { return v.re.hi; }
+__device__ __forceinline__ double lead_im(const ArithDD::C &v) { return v.im.hi; }
+__device__ __forceinline__ double lead_re(const ArithQD::C &v) { return v.re.x0; }
+__device__ __forceinline__ double lead_im(const ArithQD::C &v) { return v.im.x0; }
+
+__device__ __forceinline__ void make_nan(Arith64::C &v) { v.re = refused(); }
+__device__ __forceinline__ void make_nan(ArithDD::C &v) { v.re.hi = refused(); }
+__device__ __forceinline__ void make_nan(ArithQD::C &v) { v.re.x0 = refused(); }
+
+// Distance of a value's exponent field (the larger part's high word without
+// sign) above lo; span or more, as unsigned, means out of range.  Zero,
+// infinities and NaN are always out.
+template <class C>
+__device__ __forceinline__ uint32_t range_pos(const C &v, uint32_t lo)
+{
+    const uint32_t r = (uint32_t)__double2hiint(lead_re(v)) & 0x7FFFFFFFu;
+    const uint32_t i = (uint32_t)__double2hiint(lead_im(v)) & 0x7FFFFFFFu;
+    return max(r, i) - lo;
+}
+
+constexpr uint32_t kProdLo = (uint32_t)(1023 - kProductExp) << 20;
+constexpr uint32_t kProdSpan = (uint32_t)(2 * kProductExp) << 20;
+
+// Farthest that a lane's products were from the range, per point.
+template <class A>
+struct Worst {
+    uint32_t w[Pts<A>::T] = {};
+    __device__ __forceinline__ void see(const typename A::C &v)
+    {
+#pragma unroll
+        for (int t = 0; t < Pts<A>::T; ++t) w[t] = max(w[t], range_pos(Pts<A>::at(v, t), kProdLo));
+    }
+    __device__ __forceinline__ void mark(typename A::C &v) const
+    {
+#pragma unroll
+        for (int t = 0; t < Pts<A>::T; ++t)
+            if (w[t] >= kProdSpan) make_nan(Pts<A>::at(v, t));
+    }
+};
+
+// x + 0: turns a negative zero into zero (an output without terms is +0)
+__device__ __forceinline__ Arith64::C plus_zero(const Arith64::C &v) { return {v.re + 0.0, v.im + 0.0}; }
+__device__ __forceinline__ ArithDD::C plus_zero(const ArithDD::C &v)
+{
+    return {{v.re.hi + 0.0, v.re.lo + 0.0}, {v.im.hi + 0.0, v.im.lo + 0.0}};
+}
+__device__ __forceinline__ ArithQD::C plus_zero(const ArithQD::C &v)
+{
+    return {{v.re.x0 + 0.0, v.re.x1 + 0.0, v.re.x2 + 0.0, v.re.x3 + 0.0},
+            {v.im.x0 + 0.0, v.im.x1 + 0.0, v.im.x2 + 0.0, v.im.x3 + 0.0}};
+}
+
+// LDS of a workgroup (entries of one value, or of one for each point)
+template <class A>
+struct QuotLds {
+    LdsVec<A> u;    // [D][n]: x^1 .. x^D; then, if the tables need it, the entry 1
+    LdsVec<A> y;    // [n]: 1 / x
+    LdsVec<A> V;    // [nbuf][CH]: monomial values
+    LdsVec<A> acc;  // [n+1] sums over chunks (multi): J entries, then f
+};
+
+template <class A>
+__device__ __forceinline__ QuotLds<A> quot_lds(double2 *raw, const QuotArgs &a, double2 *&next)
+{
+    QuotLds<A> l;
+    double2 *p = raw;
+    l.u = LdsVec<A>::at(p, a.D * a.n_vars + a.pad, p);
+    l.y = LdsVec<A>::at(p, a.n_vars, p);
+    l.V = LdsVec<A>::at(p, a.nbuf * a.CH, p);
+    l.acc = LdsVec<A>::at(p, a.multi ? a.n_vars + 1 : 0, p);
+    next = p;
+    return l;
+}
+
+// The power table and the reciprocals of points pt .. pt+npt-1 (callers add
+// the barrier).  A coordinate out of range becomes NaN in the table: the
+// values of the polynomials that contain it then are NaN too.
+template <class A>
+__device__ __forceinline__ void quot_table(const QuotArgs &a, const QuotLds<A> &lds, int64_t pt, int npt,
+                                           bool jac)
+{
+    using C = typename A::C;
+    using P = Pts<A>;
+    using One = typename P::One;
+    const int n = a.n_vars, NT = (int)blockDim.x;
+    for (int i = (int)threadIdx.x; i < n; i += NT) {
+        C x, y;
+#pragma unroll
+        for (int t = 0; t < P::T; ++t) {
+            typename One::C v = Io<One>::load(a.x, (pt + min(t, npt - 1)) * n + i);
+            P::at(y, t) = quot_inv(v);
+            if (range_pos(v, a.x_lo) >= a.x_span) {
+                make_nan(v);
+                P::at(y, t) = One::one();
+            }
+            P::at(x, t) = v;
+        }
+        lds.u.put(i, x);
+        C xr = x;
+        for (int r = 1; r < a.D; ++r) {
+            xr = A::mul(xr, x);
+            lds.u.put(r * n + i, xr);
+        }
+        if (jac) lds.y.put(i, y);
+    }
+    if (a.pad && threadIdx.x == 0) lds.u.put(a.D * n, A::one());
+}
+
+// Values of the monomials of chunk ck into V at entry vo.
+template <class A>
+__device__ __forceinline__ void chunk_values(const QuotArgs &a, const int4 &ck, const QuotLds<A> &lds, int vo)
+{
+    using C = typename A::C;
+    using P = Pts<A>;
+    using One = typename P::One;
+    const int log2L = a.log2L, sub = (int)threadIdx.x & ((1 << log2L) - 1);
+    const int items = ck.y << log2L;
+    // whole waves take part (lane exchanges), so the trip count is uniform
+    for (int w0 = (int)threadIdx.x & ~63; w0 < items; w0 += (int)blockDim.x) {
+        const int s = (w0 + ((int)threadIdx.x & 63)) >> log2L;
+        const bool on = s < ck.y;
+        const int sl = __builtin_amdgcn_readfirstlane(s >> 6);
+        const int2 sh = a.slice[ck.z + sl];
+        const int cnt = min(64, ck.y - 64 * sl);
+        const uint2 *wp = a.words + (int64_t)sh.x + (on ? s - 64 * sl : 0);
+        const int Q = sh.y, qs = (Q + kParts - 1) / kParts;
+        const typename One::C coef = Io<One>::coef(a.coef, (int64_t)ck.x + (on ? s : 0));
+        Worst<A> worst;
+        auto quad = [&](const uint2 &w) {
+            const C u0 = lds.u.get((int)(w.x & 0xFFFFu)), u1 = lds.u.get((int)(w.x >> 16));
+            const C u2 = lds.u.get((int)(w.y & 0xFFFFu)), u3 = lds.u.get((int)(w.y >> 16));
+            return A::mul(A::mul(u0, u1), A::mul(u2, u3));
+        };
+        // product of range r (quads r qs .. ), which has at least one quad
+        auto range = [&](int r) {
+            const int j0 = r * qs, j1 = min(Q, j0 + qs);
+            C p = quad(wp[(int64_t)j0 * cnt]);
+            worst.see(p);
+            for (int j = j0 + 1; j < j1; ++j) {
+                p = A::mul(p, quad(wp[(int64_t)j * cnt]));
+                worst.see(p);
+            }
+            return p;
+        };
+        C prod = A::one();
+        if (log2L == 0) {
+            for (int h = 0; h < 2 && 2 * h * qs < Q; ++h) {
+                C t = range(2 * h);
+                if ((2 * h + 1) * qs < Q) {
+                    t = A::mul(t, range(2 * h + 1));
+                    worst.see(t);
+                }
+                prod = h == 0 ? t : A::mul(prod, t);
+            }
+            worst.see(prod);
+        } else {
+            // ranges 2 sub, 2 sub + 1 of two lanes, or range sub of four; a
+            // lower lane's product is the left factor, and only what reaches
+            // the group's first lane counts
+            const int r0 = log2L == 1 ? 2 * sub : sub;
+            if (r0 * qs < Q) {
+                prod = range(r0);
+                if (log2L == 1 && (r0 + 1) * qs < Q) {
+                    prod = A::mul(prod, range(r0 + 1));
+                    worst.see(prod);
+                }
+            }
+            for (int d = 1; d < (1 << log2L); d <<= 1) {
+                worst.mark(prod);  // so that the other lane learns of it
+                prod = A::mul(prod, P::other(prod, d));
+                worst.see(prod);
+            }
+        }
+        prod = A::mul(prod, P::all(coef));
+        worst.mark(prod);
+        if (on && sub == 0) lds.V.put(vo + s, prod);
+    }
+}
+
+// Sum of a run by one lane's NP of its kParts partial sums, combined with
+// the other lanes of the run.  e: the lane's entries of the run's first row.
+template <class A, int NP>
+__device__ __forceinline__ typename A::C run_sum(const LdsVec<A> &V, int vo, const uint16_t *e, int rows)
+{
+    using C = typename A::C;
+    struct alignas(2 * NP) Row {
+        uint16_t v[NP];
+    };
+    constexpr int kStep = kRankBlock * kParts;
+    C part[NP];
+    Row nx{};
+    if (rows > 0) nx = *reinterpret_cast<const Row *>(e);
+    for (int i0 = 0; i0 == 0 || i0 < rows; i0 += kRunBlock) {
+        RunAcc<A> acc[NP];
+#pragma unroll
+        for (int q = 0; q < NP; ++q) acc[q].clear();
+        const int i1 = min(rows, i0 + kRunBlock);
+        for (int i = i0; i < i1; ++i) {
+            const Row r = nx;
+            e += kStep;
+            if (i + 1 < rows) nx = *reinterpret_cast<const Row *>(e);
+#pragma unroll
+            for (int q = 0; q < NP; ++q)
+                acc[q].add(V.get(vo + (int)(r.v[q] & ((1 << kEntryBits) - 1))),
+                           (double)(r.v[q] >> kEntryBits));
+        }
+#pragma unroll
+        for (int q = 0; q < NP; ++q) part[q] = i0 == 0 ? acc[q].get() : A::sum(part[q], acc[q].get());
+    }
+    if constexpr (NP == 4) return A::sum(A::sum(part[0], part[1]), A::sum(part[2], part[3]));
+    if constexpr (NP == 2) return Pts<A>::template sum_over<1>(A::sum(part[0], part[1]));
+    return Pts<A>::template sum_over<2>(Pts<A>::template sum_over<1>(part[0]));
+}
+
+// The sums of chunk ck (number ci): with jac the outputs' runs, and the sum
+// of the values.  put(o, v) gets output o's sum on one lane.
+template <class A, int NP, class Put>
+__device__ __forceinline__ void chunk_sums(const QuotArgs &a, int ci, const int4 &ck, const QuotLds<A> &lds,
+                                           int vo, bool jac, const Put &put)
+{
+    using C = typename A::C;
+    using P = Pts<A>;
+    constexpr int S = kParts / NP;
+    const int lane = (int)threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int nw = (int)blockDim.x >> 6;
+    const int n_rank = a.n_blk * kRankBlock;
+    const int items = jac ? (n_rank * S + 63) / 64 : 0;  // waves' worth of runs
+    for (int k = 0; k * nw <= items; ++k) {
+        // waves in turn, backwards in odd rounds: the values' sum, the last
+        // item, falls on a wave with short runs
+        const int it = k * nw + ((k & 1) ? nw - 1 - wave : wave);
+        if (it > items) continue;
+        if (it < items) {
+            const int rank = (it * 64 + lane) / S, sub = lane & (S - 1);
+            const int blk = rank / kRankBlock;
+            const bool on = rank < n_rank;
+            const int2 bh = on ? a.block[ck.w + blk] : make_int2(0, 0);
+            const uint16_t *e = a.runs + ((int64_t)bh.x * kRankBlock + (rank & (kRankBlock - 1))) * kParts +
+                                sub * NP;
+            const int o = on ? (int)a.out[(int64_t)ci * n_rank + rank] : 0xFFFF;
+            const C v = run_sum<A, NP>(lds.V, vo, e, bh.y);
+            if (sub == 0 && o != 0xFFFF) put(o, v);
+        } else {
+            // at most kMaxQuotChunk / 64 <= kRunBlock terms per lane
+            RunAcc<A> acc;
+            acc.clear();
+            for (int i = lane; i < ck.y; i += 64) acc.add(lds.V.get(vo + i), 1.0);
+            C v = acc.get();
+            v = P::template sum_over<1>(v);
+            v = P::template sum_over<2>(v);
+            v = P::template sum_over<4>(v);
+            v = P::template sum_over<8>(v);
+            v = P::template sum_over<16>(v);
+            v = P::template sum_over<32>(v);
+            if (lane == 0) put(a.n_vars, v);
+        }
+    }
+}
+
+// Polynomial p at points pt .. pt+npt-1 of which those with their bit set in
+// live are written; vo is the buffer in use (it alternates).  on_refused()
+// runs on the lane that finds a value refused.
+template <class A, class Refused>
+__device__ __forceinline__ void quot_poly(const QuotArgs &a, const QuotLds<A> &lds, int64_t pt, uint32_t live,
+                                          int p, int &vo, bool jac, const Refused &on_refused)
+{
+    using C = typename A::C;
+    using P = Pts<A>;
+    using One = typename P::One;
+    const int n = a.n_vars;
+    const int4 pl = a.poly[p];
+    for (int c = pl.x; c < pl.y; ++c) {
+        const int4 ck = a.chunk[c];
+        chunk_values<A>(a, ck, lds, vo);
+        __syncthreads();
+        const bool first = c == pl.x, last = c + 1 == pl.y;
+        auto put = [&](int o, C v) {
+            if (!first)
+                v = A::sum(lds.acc.get(o), v);
+            else if (o == n && pl.z > 0)
+                v = A::sum(P::all(Io<One>::coef(a.sys_coef, pl.z - 1)), v);
+            if (!last) {
+                lds.acc.put(o, v);
+                return;
+            }
+            if (o != n) v = A::mul(lds.y.get(o), v);
+#pragma unroll
+            for (int t = 0; t < P::T; ++t) {
+                if (P::T > 1 && !((live >> t) & 1u)) continue;
+                typename One::C w = P::at(v, t);
+                if (o == n) {
+                    // a product out of range left a NaN among the values
+                    if (!isfinite(lead_re(w)) || !isfinite(lead_im(w))) {
+                        a.f[0][(pt + t) * a.n_polys + p] = refused();
+                        on_refused();
+                    } else {
+                        Io<One>::store(a.f, (pt + t) * a.n_polys + p, w);
+                    }
+                } else {
+                    Io<One>::store(a.J, ((pt + t) * n + o) * a.n_polys + p, plus_zero(w));
+                }
+            }
+        };
+        if (a.log2S == 0)
+            chunk_sums<A, 4>(a, c, ck, lds, vo, jac, put);
+        else if (a.log2S == 1)
+            chunk_sums<A, 2>(a, c, ck, lds, vo, jac, put);
+        else
+            chunk_sums<A, 1>(a, c, ck, lds, vo, jac, put);
+        // with two buffers the next item writes the other one; it comes back
+        // to this one only after a barrier that follows these reads
+        if (a.nbuf > 1)
+            vo = vo ? 0 : a.CH;
+        else
+            __syncthreads();
+    }
+    if (pl.x == pl.y) {
+        // no monomials but a folded constant, or none at all
+        for (int t = 0; t < P::T; ++t) {
+            if (P::T > 1 && !((live >> t) & 1u)) continue;
+            if (threadIdx.x == 0)
+                Io<One>::store(a.f, (pt + t) * a.n_polys + p,
+                               pl.z > 0 ? Io<One>::coef(a.sys_coef, pl.z - 1) : One::zero());
+            if (jac)
+                for (int o = (int)threadIdx.x; o < n; o += (int)blockDim.x)
+                    Io<One>::store(a.J, ((pt + t) * n + o) * a.n_polys + p, One::zero());
+        }
+    }
+}
+
+}  // namespace pe

@@ -1,0 +1,175 @@
+// Host-side packing for the quotient kernels.  See quotient.hpp.
+#include "quotient.hpp"
+
+#include <algorithm>
+#include <climits>
+
+#include "lds_budget.hpp"
+
+namespace pe {
+
+size_t quot_lds_bytes(int n_vars, int max_exp, bool pad, int CH, bool multi, int nbuf, int words)
+{
+    const size_t n = (size_t)n_vars;
+    const size_t values =
+        (size_t)max_exp * n + (pad ? 1 : 0) + n + (size_t)nbuf * (size_t)CH + (multi ? n + 1 : 0);
+    return values * (size_t)words * sizeof(double);
+}
+
+int quot_chunk(int n_vars, int max_exp, bool pad, int64_t max_m, int words)
+{
+    if (max_exp > kMaxQuotExp || n_vars >= 0xFFFF || (int64_t)max_exp * n_vars >= 0xFFFF ||
+        quot_point_exp(max_exp) < 2)
+        return 0;
+    const int64_t whole = (std::max<int64_t>(1, max_m) + 63) / 64 * 64;
+    int ch = (int)std::min<int64_t>(whole, kMaxQuotChunk);
+    // equal chunks rather than full ones and a short last one
+    const int64_t parts = (whole + ch - 1) / ch;
+    ch = (int)((whole / 64 + parts - 1) / parts * 64);
+    for (; ch >= 64; ch -= 64)
+        if (quot_lds_bytes(n_vars, max_exp, pad, ch, ch < max_m, 1, words) <= kLdsBytes) return ch;
+    return 0;
+}
+
+void quot_shape(const CsrView &S, bool &pad, int64_t &max_m)
+{
+    pad = false;
+    max_m = 0;
+    int64_t kmax = 0;
+    for (int64_t s = 0; s < S.n_monos; ++s) kmax = std::max(kmax, S.mono_start[s + 1] - S.mono_start[s]);
+    if (kmax % kQuad) pad = true;
+    for (int p = 0; p < S.n_polys; ++p) {
+        int64_t constants = 0;
+        for (int64_t s = S.poly_start[p]; s < S.poly_start[p + 1]; ++s) {
+            const int64_t k = S.mono_start[s + 1] - S.mono_start[s];
+            if (k == 0)
+                ++constants;
+            else if (k != kmax)
+                pad = true;
+        }
+        if (constants > 1) pad = true;  // only one is folded
+        max_m = std::max(max_m, S.poly_start[p + 1] - S.poly_start[p] - (constants > 0 ? 1 : 0));
+    }
+}
+
+std::string build_quot_tables(const CsrView &S, QuotTables &t)
+{
+    const int n = S.n_vars, CH = t.CH;
+    if (CH < 64 || CH % 64 || CH > kMaxQuotChunk) return "invalid chunk";
+    if (S.n_monos >= (int64_t)INT32_MAX) return "too many monomials";
+    t.n_blk = (n + kRankBlock - 1) / kRankBlock;
+    const int n_rank = t.n_blk * kRankBlock;
+    int max_exp = 1;
+    for (int64_t e = 0; e < (S.n_monos ? S.mono_start[S.n_monos] : 0); ++e) max_exp = std::max(max_exp, S.exp[e]);
+    if (max_exp > kMaxQuotExp) return "exponents too large";
+    t.multi = false;
+    t.words.clear();
+    t.mono.clear();
+    t.slice.clear();
+    t.chunk.clear();
+    t.poly.clear();
+    t.block.clear();
+    t.runs.clear();
+    t.out.clear();
+    t.mono.reserve((size_t)S.n_monos);
+    std::vector<int32_t> len((size_t)n), rank((size_t)n), at((size_t)n), order((size_t)n), bin;
+    std::vector<int32_t> by_k[257];
+    int64_t rows_total = 0;
+    for (int p = 0; p < S.n_polys; ++p) {
+        const int64_t s0 = S.poly_start[p], s1 = S.poly_start[p + 1];
+        int32_t fold = 0;
+        int kmax = 0;
+        for (int64_t s = s0; s < s1; ++s) {
+            const int k = (int)(S.mono_start[s + 1] - S.mono_start[s]);
+            if (k > 256) return "a monomial has more than 256 variables";
+            if (k == 0) fold = (int32_t)s + 1;  // the last one
+            kmax = std::max(kmax, k);
+            by_k[k].push_back((int32_t)s);
+        }
+        const int64_t first = (int64_t)t.mono.size();
+        for (int k = kmax; k >= 0; --k) {
+            for (int32_t s : by_k[k])
+                if (s + 1 != fold) t.mono.push_back(s);
+            by_k[k].clear();
+        }
+        const int64_t m = (int64_t)t.mono.size() - first;
+        const int nch = (int)((m + CH - 1) / CH);
+        if (nch > 1) t.multi = true;
+        const int32_t chunk0 = (int32_t)(t.chunk.size() / 4);
+        for (int c = 0; c < nch; ++c) {
+            const int64_t a = first + (int64_t)c * CH;
+            const int cnt = (int)std::min<int64_t>(CH, first + m - a);
+            t.chunk.push_back((int32_t)a);
+            t.chunk.push_back(cnt);
+            t.chunk.push_back((int32_t)(t.slice.size() / 2));
+            t.chunk.push_back((int32_t)(t.block.size() / 2));
+            std::fill(len.begin(), len.end(), 0);
+            for (int b = 0; b < cnt; b += 64) {
+                const int sc = std::min(64, cnt - b);
+                int quads = 0;
+                for (int q = 0; q < sc; ++q) {
+                    const int32_t s = t.mono[(size_t)(a + b + q)];
+                    const int k = (int)(S.mono_start[s + 1] - S.mono_start[s]);
+                    quads = std::max(quads, (k + kQuad - 1) / kQuad);
+                }
+                const size_t w0 = t.words.size();
+                if (w0 / kQuad + (size_t)quads * sc > (size_t)INT32_MAX) return "tables too large";
+                t.slice.push_back((int32_t)(w0 / kQuad));
+                t.slice.push_back(quads);
+                t.words.resize(w0 + (size_t)quads * sc * kQuad, (uint16_t)(max_exp * n));
+                for (int q = 0; q < sc; ++q) {
+                    const int32_t s = t.mono[(size_t)(a + b + q)];
+                    const int64_t e0 = S.mono_start[s], k = S.mono_start[s + 1] - e0;
+                    for (int64_t j = 0; j < k; ++j) {
+                        const int pos = S.pos[e0 + j];
+                        t.words[w0 + ((size_t)(j / kQuad) * sc + q) * kQuad + j % kQuad] =
+                            (uint16_t)((S.exp[e0 + j] - 1) * n + pos);
+                        ++len[(size_t)pos];
+                    }
+                }
+            }
+            // outputs by run length, longest first (stable counting sort)
+            const int lmax = cnt;
+            bin.assign((size_t)lmax + 2, 0);
+            for (int o = 0; o < n; ++o) ++bin[(size_t)(lmax - len[(size_t)o]) + 1];
+            for (int l = 0; l <= lmax; ++l) bin[(size_t)l + 1] += bin[(size_t)l];
+            for (int o = 0; o < n; ++o) {
+                const int j = bin[(size_t)(lmax - len[(size_t)o])]++;
+                rank[(size_t)o] = j;
+                order[(size_t)j] = o;
+            }
+            for (int j = 0; j < n_rank; ++j)
+                t.out.push_back(j < n ? (uint16_t)order[(size_t)j] : (uint16_t)0xFFFF);
+            const size_t blk0 = t.block.size();
+            for (int b = 0; b < t.n_blk; ++b) {
+                const int rows = (len[(size_t)order[(size_t)b * kRankBlock]] + kParts - 1) / kParts;
+                if (rows_total + rows > (int64_t)INT32_MAX / (kRankBlock * kParts))
+                    return "tables too large";
+                t.block.push_back((int32_t)rows_total);
+                t.block.push_back(rows);
+                rows_total += rows;
+            }
+            t.runs.resize((size_t)rows_total * kRankBlock * kParts, (uint16_t)0);
+            std::fill(at.begin(), at.end(), 0);
+            for (int i = 0; i < cnt; ++i) {
+                const int32_t s = t.mono[(size_t)(a + i)];
+                for (int64_t e = S.mono_start[s]; e < S.mono_start[s + 1]; ++e) {
+                    const size_t o = (size_t)S.pos[e];
+                    const int j = rank[o], term = at[o]++;
+                    const size_t row = (size_t)t.block[blk0 + 2 * (size_t)(j / kRankBlock)] +
+                                       (size_t)(term / kParts);
+                    t.runs[(row * kRankBlock + (size_t)(j % kRankBlock)) * kParts + term % kParts] =
+                        (uint16_t)(i | (S.exp[e] << kEntryBits));
+                }
+            }
+        }
+        t.poly.push_back(chunk0);
+        t.poly.push_back(chunk0 + nch);
+        t.poly.push_back(fold);
+        t.poly.push_back(0);
+    }
+    t.n_chunks = (int)(t.chunk.size() / 4);
+    return std::string();
+}
+
+}  // namespace pe
