@@ -441,27 +441,39 @@ hipError_t System::run_quot(const Quot &q, int prec, int cc, int maxt, EvalArgs 
     return launch_eval(prec, cc, maxt, a, dim3((unsigned)n_polys, (unsigned)gy, 1), dim3(threads), lds, hs);
 }
 
-pe_status System::eval_locked(int64_t n_points, const double *const x[4], double *const f[4],
-                              double *const J[4], bool dd, hipStream_t hs, const int32_t *mask,
-                              bool no_alloc, bool quotients)
+pe_status System::eval_plan(int64_t n_points, bool dd, bool no_alloc, Schedule **out, int &T, int &nbuf,
+                            size_t &lds)
 {
     Schedule *sc = nullptr;
     pe_status st = no_alloc ? find_schedule(n_points, &sc) : schedule_for(n_points, &sc);
     if (st != PE_OK) return st;
     const int words = dd ? 4 : 2;
-    int T = 1, nbuf = 1;
     launch_shape(*sc, n_points, dd, T, nbuf);
     if (T == 0)
         return fail(PE_EUNSUPPORTED,
                     "tiles of %d points with %d staging buffers need %zu bytes of LDS (> 160 KiB)",
                     pin_T ? pin_T : 1, pin_nbuf ? pin_nbuf : 1,
                     sc->lds_bytes(words, pin_T ? pin_T : 1, pin_nbuf ? pin_nbuf : 1));
-    const size_t lds = sc->lds_bytes(words, T, nbuf);
+    lds = sc->lds_bytes(words, T, nbuf);
     if (lds > kMaxLds)
         return fail(PE_EUNSUPPORTED,
                     "schedule needs %zu bytes of LDS (> 160 KiB): n_vars=%d, power rows=%d, "
                     "staging slots=%d, threads=%d",
                     lds, n_vars, sc->R, sc->stage_slots, sc->nt);
+    *out = sc;
+    return PE_OK;
+}
+
+pe_status System::eval_locked(int64_t n_points, const double *const x[4], double *const f[4],
+                              double *const J[4], bool dd, hipStream_t hs, const int32_t *mask,
+                              bool no_alloc, bool quotients)
+{
+    Schedule *sc = nullptr;
+    int T = 1, nbuf = 1;
+    size_t lds = 0;
+    pe_status st = eval_plan(n_points, dd, no_alloc, &sc, T, nbuf, lds);
+    if (st != PE_OK) return st;
+    const int words = dd ? 4 : 2;
 
     EvalArgs a;
     fill_args(*sc, a);
@@ -632,7 +644,7 @@ pe_status pe_create_system(int32_t n_vars, int32_t n_polys, int64_t n_monos,
     if (he != hipSuccess) return hip_fail(he, "locating the static scratch");
     he = S->coef.upload(c.data(), c.size() * sizeof(double));
     if (he != hipSuccess) return hip_fail(he, "uploading coefficients");
-    if (S->quot_ok) S->coef_host = std::move(c);
+    S->coef_host = std::move(c);
     if (nnz >= ((int64_t)1 << 31)) return fail(PE_EUNSUPPORTED, "more than 2^31 support entries");
     {
         std::vector<int32_t> ms32((size_t)n_monos + 1);

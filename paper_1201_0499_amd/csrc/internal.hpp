@@ -67,10 +67,9 @@ struct System {
     std::vector<int64_t> poly_start, mono_start;
     std::vector<int32_t> pos, exp;
     DevBuf coef;  // [M][4]
-    // for the quotient kernels: coefficients (host), whether their range and
-    // the exponents allow these kernels at all, and the most monomials of a
-    // polynomial without its folded constant
-    std::vector<double> coef_host;
+    std::vector<double> coef_host;  // the same on the host
+    // for the quotient kernels: whether the coefficients' range and the
+    // exponents allow them at all, and see quot_shape
     bool quot_ok = false, quot_pad = true;
     int64_t quot_max_m = 0;
     std::vector<std::unique_ptr<Quot>> quots;
@@ -88,6 +87,10 @@ struct System {
     // path tracker: total degrees of the polynomials (uploaded once),
     // accepted points and per-path state
     DevBuf tk_deg, tk_xs, tk_state;
+    // tables of the one-wave tracker (track.hpp) and the schedule they follow
+    const Schedule *tk_sched = nullptr;
+    int tk_slots = 0, tk_n_out = 0, tk_n_run = 0;
+    DevBuf tk_word, tk_coef, tk_out, tk_start, tk_run, tk_fold;
     // the paper's three-kernel evaluation: monomial -> polynomial, prescaled
     // coefficients, common factors, dense term array (and its layout)
     DevBuf ab_mono_poly, ab_pcoef, ab_pcoef_start, ab_cf, ab_mons;
@@ -118,6 +121,10 @@ struct System {
     // kernel with maxt, threads and lds bytes serves what they refuse
     hipError_t run_quot(const Quot &q, int prec, int cc, int maxt, EvalArgs a, unsigned threads, size_t lds,
                         hipStream_t hs) const;
+    // schedule, tile, staging buffers and LDS of an evaluation, or why there
+    // is none (no_alloc: as below)
+    pe_status eval_plan(int64_t n_points, bool dd, bool no_alloc, Schedule **out, int &T, int &nbuf,
+                        size_t &lds);
     // evaluation with the lock held; J[0] == nullptr skips the Jacobian,
     // mask (optional) skips points whose entry is not -1.  no_alloc: use
     // only existing schedule tables and the static scratch, allocate nothing;
@@ -130,9 +137,9 @@ struct System {
 // Newton's method from n_starts starts (the body of pe_newton, called with
 // the system's lock held).  init: set every start running first; else only
 // the starts whose status is kRunning iterate and iters_out must be zero
-// for them.
+// for them.  quotients: as in eval_locked.
 pe_status newton_run(System *S, int64_t n_starts, pe_cvec x, double tol, int32_t max_iter,
                      bool mixed, double *res_out, int32_t *iters_out, int32_t *status_out,
-                     hipStream_t hs, bool init);
+                     hipStream_t hs, bool init, bool quotients = true);
 
 }  // namespace pe

@@ -42,7 +42,7 @@ namespace pe {
 // 2: mixed with quad-double residual and x (x has 8 planes).
 static pe_status newton_core(System *S, int64_t n_starts, double *const *x, int kind, double tol,
                              int32_t max_iter, double *res_out, int32_t *iters_out,
-                             int32_t *status_out, hipStream_t hs, bool init)
+                             int32_t *status_out, hipStream_t hs, bool init, bool quotients)
 {
     const bool mixed = kind != 1;
     const bool qd = kind == 2;
@@ -113,7 +113,7 @@ static pe_status newton_core(System *S, int64_t n_starts, double *const *x, int 
             if ((e = launch_resid(ra, qd ? 2 : 1, hs)) != hipSuccess)
                 return hip_fail(e, "residual kernel");
         } else {
-            st = S->eval_locked(n_starts, xview, rp, Jp, true, hs, status_out);
+            st = S->eval_locked(n_starts, xview, rp, Jp, true, hs, status_out, false, quotients);
             if (st != PE_OK) return st;
         }
         if ((e = hipMemsetAsync(counter, 0, sizeof(int32_t), hs)) != hipSuccess)
@@ -128,7 +128,7 @@ static pe_status newton_core(System *S, int64_t n_starts, double *const *x, int 
             return hip_fail(e, "reading the running count");
         if (running == 0) break;
         if (mixed) {
-            st = S->eval_locked(n_starts, xview, fp64, Jp, false, hs, status_out);
+            st = S->eval_locked(n_starts, xview, fp64, Jp, false, hs, status_out, false, quotients);
             if (st != PE_OK) return st;
             if ((e = launch_lu_solve(0, n_starts, n, Jp, rview, dp, status_out, hs)) != hipSuccess)
                 return hip_fail(e, "FP64 solve");
@@ -156,11 +156,11 @@ static pe_status newton_core(System *S, int64_t n_starts, double *const *x, int 
 
 pe_status newton_run(System *S, int64_t n_starts, pe_cvec x, double tol, int32_t max_iter,
                      bool mixed, double *res_out, int32_t *iters_out, int32_t *status_out,
-                     hipStream_t hs, bool init)
+                     hipStream_t hs, bool init, bool quotients)
 {
     double *xp[4] = {x.re_hi, x.re_lo, x.im_hi, x.im_lo};
     return newton_core(S, n_starts, xp, mixed ? 0 : 1, tol, max_iter, res_out, iters_out,
-                       status_out, hs, init);
+                       status_out, hs, init, quotients);
 }
 
 }  // namespace pe
@@ -215,5 +215,5 @@ extern "C" pe_status pe_newton_qd(pe_system sys, int64_t n_starts, double *const
 
     std::lock_guard<std::mutex> lock(S->mu);
     return newton_core(S, n_starts, x, 2, tol, max_iter, res_out, iters_out, status_out,
-                       reinterpret_cast<hipStream_t>(stream), true);
+                       reinterpret_cast<hipStream_t>(stream), true, true);
 }

@@ -8,7 +8,9 @@
 // and its Jacobian at each running path's current x (one masked launch of
 // the evaluator), forms the homotopy's Jacobian and right-hand side for the
 // path's phase, solves (the batched elimination), and applies the phase's
-// update.  Finding roots of polynomial systems by continuation is the use
+// update.  Systems of few variables and terms are tracked by one wave per
+// path instead, which keeps the path's state and the system's terms on chip
+// through all its rounds.  Finding roots of polynomial systems by continuation is the use
 // the paper's introduction names for fast evaluation (Section 1).
 #pragma once
 
@@ -47,6 +49,45 @@ struct TrackArgs {
     int32_t *status;       // [P] kRunning while tracking
     int32_t *running;      // count of running paths after a round (zeroed by the caller)
 };
+
+// F and its Jacobian for the one-wave tracker (track.hip), which evaluates
+// them with the general kernel's arithmetic in that kernel's order, for a
+// schedule of one lane per monomial and one chunk per polynomial: the same
+// bits.  Each polynomial's monomials take consecutive slots, padded to the
+// groups of VG monomials whose values are added by a butterfly (pads: the
+// variable n, which reads 1, and coefficient 0).  A slot's terms are its CC
+// derivatives; the values' groups follow the slots' terms.
+struct TrackTerms {
+    int32_t CC;               // variables per slot
+    int32_t n_slots, log2VG;
+    int32_t n_out;
+    int32_t log2S;            // lanes per run of the general kernel's summation
+    int32_t R;                // power-table rows x^1 .. x^R
+    const uint32_t *word;     // [n_slots][CC] packed variables
+    const double *coef;       // [n_slots][2]
+    const uint16_t *out;      // [n_out]: i (n + 1) + c of dF_i/dx_c, c = n: F_i
+    const uint16_t *start;    // [n_out + 1]: an output's first entry in run
+    const uint16_t *run;      // terms of each output, in monomial order
+    int32_t n_run;
+    const double *fold;       // [n][2]: the constant F_i's sum starts with
+};
+
+// The one-wave tracker takes systems of at most this many variables whose
+// tables fit kTrackSmallLds (four workgroups per CU: one wave per SIMD).
+constexpr int kTrackSmallVars = 16;
+constexpr size_t kTrackSmallLds = 40 * 1024;
+inline size_t track_small_lds(int n, const TrackTerms &t)
+{
+    const size_t slots = (size_t)t.n_slots;
+    const size_t values = (size_t)t.R * (n + 1) + slots + slots * t.CC + (slots >> t.log2VG) +
+                          (size_t)n * (n + 1) + n + 2 * kTrackSmallVars + 1;
+    return 16 * values + 4 * slots * t.CC + 2 * (2 * (size_t)t.n_out + 1 + (size_t)t.n_run);
+}
+
+// Up to `rounds` rounds of every running path (evaluation, solve, update),
+// from and to the state in `a`; counts the paths still running into
+// *a.running.
+hipError_t launch_track_small(const TrackArgs &a, const TrackTerms &terms, int rounds, hipStream_t stream);
 
 // x planes (dd, [P][n]) <- start solutions first .. first+P-1 of G: path
 // index q has mixed-radix digits k_i in base d_i (digit of variable 0

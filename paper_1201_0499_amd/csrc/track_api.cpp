@@ -10,6 +10,7 @@
 #include "polyeval.h"
 #include "internal.hpp"
 #include "newton.hpp"
+#include "packing.hpp"
 #include "track.hpp"
 
 using namespace pe;
@@ -41,6 +42,99 @@ pe_status upload_degrees(System *S)
     }
     hipError_t e = S->tk_deg.upload(deg.data(), deg.size() * sizeof(int32_t));
     if (e != hipSuccess) return hip_fail(e, "uploading the degrees");
+    return PE_OK;
+}
+
+// Tables of the one-wave tracker for schedule sc (kept while it is the one
+// in use); ok = false: the system or the schedule is outside that kernel.
+pe_status small_terms(System *S, const Schedule &sc, TrackTerms &tt, bool &ok)
+{
+    const int n = S->n_vars, np1 = n + 1, VG = sc.VG, CC = sc.cc;
+    ok = false;
+    if (n > kTrackSmallVars || sc.L != 1 || sc.G != 1) return PE_OK;
+    EvalArgs ea;
+    S->fill_args(sc, ea);
+    tt = TrackTerms{};
+    tt.CC = CC;
+    tt.log2VG = ea.log2VG;
+    tt.log2S = ea.log2S;
+    tt.R = sc.R;
+    // monomials of polynomial p that take slots: all but a constant last one,
+    // which the packing of the schedule folds into the value
+    const auto slots_of = [&](int p) {
+        const int64_t s0 = S->poly_start[(size_t)p], s1 = S->poly_start[(size_t)p + 1];
+        const bool folded = s1 > s0 && S->mono_start[(size_t)s1] == S->mono_start[(size_t)s1 - 1];
+        return s1 - s0 - (folded ? 1 : 0);
+    };
+    int64_t n_slots = 0;
+    for (int p = 0; p < n; ++p) {
+        const int64_t m = slots_of(p);
+        // one chunk, and at most one block of terms per lane of a run
+        if (m > sc.MC || m > (int64_t)kRunBlock << ea.log2S) return PE_OK;
+        n_slots += (m + VG - 1) / VG * VG;
+    }
+    if (n_slots * CC > 0x7FFF) return PE_OK;
+    tt.n_slots = (int)n_slots;
+    // outputs with terms: at most one per derivative and one value per polynomial
+    if (S->tk_sched != &sc) {
+        std::vector<uint32_t> word((size_t)n_slots * CC, (uint32_t)n);
+        std::vector<double> coef((size_t)n_slots * 2, 0.0), fold((size_t)n * 2, 0.0);
+        std::vector<std::vector<uint16_t>> at((size_t)n * np1);
+        const size_t n_terms = (size_t)n_slots * CC;
+        size_t slot = 0;
+        for (int p = 0; p < n; ++p) {
+            const int64_t s0 = S->poly_start[(size_t)p], m = slots_of(p);
+            if (s0 + m < S->poly_start[(size_t)p + 1]) {
+                fold[2 * (size_t)p] = S->coef_host[4 * (size_t)(s0 + m)];
+                fold[2 * (size_t)p + 1] = S->coef_host[4 * (size_t)(s0 + m) + 2];
+            }
+            for (int64_t q = 0; q < m; ++q) {
+                const size_t s = (size_t)(s0 + q), sl = slot + (size_t)q;
+                coef[2 * sl] = S->coef_host[4 * s];
+                coef[2 * sl + 1] = S->coef_host[4 * s + 2];
+                for (int64_t j = S->mono_start[s]; j < S->mono_start[s + 1]; ++j) {
+                    const size_t t = sl * CC + (size_t)(j - S->mono_start[s]);
+                    word[t] = pack_word(S->pos[(size_t)j], S->exp[(size_t)j]);
+                    at[(size_t)p * np1 + S->pos[(size_t)j]].push_back((uint16_t)t);
+                }
+                if (q % VG == 0) at[(size_t)p * np1 + n].push_back((uint16_t)(n_terms + sl / VG));
+            }
+            slot += (size_t)((m + VG - 1) / VG * VG);
+        }
+        std::vector<uint16_t> out, start{0}, run;
+        for (size_t o = 0; o < at.size(); ++o) {
+            // (a constant polynomial has no start system, so every value has terms)
+            if (at[o].empty()) continue;
+            out.push_back((uint16_t)o);
+            run.insert(run.end(), at[o].begin(), at[o].end());
+            start.push_back((uint16_t)run.size());
+        }
+        S->tk_sched = nullptr;
+        hipError_t e = hipSuccess;
+#define PE_UP(buf, v) \
+    if (e == hipSuccess) e = S->buf.upload(v.data(), v.size() * sizeof(v[0]));
+        PE_UP(tk_word, word)
+        PE_UP(tk_coef, coef)
+        PE_UP(tk_out, out)
+        PE_UP(tk_start, start)
+        PE_UP(tk_run, run)
+        PE_UP(tk_fold, fold)
+#undef PE_UP
+        if (e != hipSuccess) return hip_fail(e, "uploading the tracker's tables");
+        S->tk_slots = (int)n_slots;
+        S->tk_n_out = (int)out.size();
+        S->tk_n_run = (int)run.size();
+        S->tk_sched = &sc;
+    }
+    tt.n_out = S->tk_n_out;
+    tt.n_run = S->tk_n_run;
+    tt.word = (const uint32_t *)S->tk_word.ptr;
+    tt.coef = (const double *)S->tk_coef.ptr;
+    tt.out = (const uint16_t *)S->tk_out.ptr;
+    tt.start = (const uint16_t *)S->tk_start.ptr;
+    tt.run = (const uint16_t *)S->tk_run.ptr;
+    tt.fold = (const double *)S->tk_fold.ptr;
+    ok = track_small_lds(n, tt) <= kTrackSmallLds;
     return PE_OK;
 }
 
@@ -177,8 +271,31 @@ extern "C" pe_status pe_track(pe_system sys, int64_t n_paths, pe_cvec x,
     if ((e = launch_track_init(a, P.h_init, xlo, hs)) != hipSuccess) return hip_fail(e, "tracker init");
     // every step attempt takes at most 1 + corr_iters rounds
     const int64_t max_rounds = (int64_t)P.max_steps * (1 + P.corr_iters) + 2;
-    for (int64_t round = 0; round < max_rounds; ++round) {
-        st = S->eval_locked(n_paths, xpc, fq, Jq, false, hs, status_out);
+    // a schedule that the evaluation refuses is refused for either kernel
+    Schedule *sc = nullptr;
+    int tile = 1, nbuf = 1;
+    size_t lds = 0;
+    if ((st = S->eval_plan(n_paths, false, false, &sc, tile, nbuf, lds)) != PE_OK) return st;
+    TrackTerms tt{};
+    bool small = false;
+    if ((st = small_terms(S, *sc, tt, small)) != PE_OK) return st;
+    if (small) {
+        // a launch's rounds are bounded (to some 10 ms), not the path's
+        constexpr int kRounds = 2048;
+        for (int64_t round = 0; round < max_rounds; round += kRounds) {
+            int32_t running = 0;
+            if ((e = hipMemsetAsync(counter, 0, sizeof(int32_t), hs)) != hipSuccess)
+                return hip_fail(e, "clearing the counter");
+            if ((e = launch_track_small(a, tt, kRounds, hs)) != hipSuccess) return hip_fail(e, "tracker kernel");
+            if ((e = hipMemcpyAsync(&running, counter, sizeof running, hipMemcpyDeviceToHost, hs)) !=
+                    hipSuccess ||
+                (e = hipStreamSynchronize(hs)) != hipSuccess)
+                return hip_fail(e, "reading the running count");
+            if (running == 0) break;
+        }
+    }
+    for (int64_t round = 0; !small && round < max_rounds; ++round) {
+        st = S->eval_locked(n_paths, xpc, fq, Jq, false, hs, status_out, false, false);
         if (st != PE_OK) return st;
         if ((e = launch_track_homotopy(a, hs)) != hipSuccess) return hip_fail(e, "homotopy kernel");
         if ((e = launch_lu_solve(0, n_paths, n, Jq, rq, dq, status_out, hs)) != hipSuccess)
@@ -200,8 +317,9 @@ extern "C" pe_status pe_track(pe_system sys, int64_t n_paths, pe_cvec x,
         if ((e = launch_track_endgame(n_paths, tracked, status_out, hs)) != hipSuccess ||
             (e = hipMemsetAsync(end_iters, 0, NP * sizeof(int32_t), hs)) != hipSuccess)
             return hip_fail(e, "starting the endgame");
+        // (with the general kernel, as the tracking: see track_small_kernel)
         st = newton_run(S, n_paths, x, P.end_tol, P.end_iters, true, res_out, end_iters, status_out,
-                        hs, false);
+                        hs, false, false);
         if (st != PE_OK && st != PE_ENOTCONVERGED) return st;
         if ((e = launch_track_end(n_paths, tracked, status_out, hs)) != hipSuccess)
             return hip_fail(e, "ending the endgame");
