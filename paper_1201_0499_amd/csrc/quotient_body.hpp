@@ -177,15 +177,46 @@ struct RunAcc<ArithDD> {
     __device__ __forceinline__ ArithDD::C get() const { return {dw_acc_get(re), dw_acc_get(im)}; }
 };
 
+// Sums of the orders u^0 .. u^3, kept apart, and the rest: every term by
+// TwoSum, whose errors join the next order.  The sums outgrow the terms, and
+// so do their errors; only errors of order u^4 of the sums and u^3 a|v| u of a
+// term are rounded.
 template <>
 struct RunAcc<ArithQD> {
-    ArithQD::C s;
-    __device__ __forceinline__ void clear() { s = ArithQD::zero(); }
+    struct Sums {
+        double s0, s1, s2, s3, s4;
+    } re, im;
+    __device__ __forceinline__ void clear()
+    {
+        re = {0.0, 0.0, 0.0, 0.0, 0.0};
+        im = {0.0, 0.0, 0.0, 0.0, 0.0};
+    }
+    __device__ __forceinline__ static void one(Sums &s, const qd &v, double a)
+    {
+        const dd p0 = two_prod(a, v.x0), p1 = two_prod(a, v.x1), p2 = two_prod(a, v.x2);
+        const dd t0 = two_sum(s.s0, p0.hi);
+        const dd a1 = two_sum(p1.hi, p0.lo), b1 = two_sum(a1.hi, t0.lo), t1 = two_sum(s.s1, b1.hi);
+        const dd a2 = two_sum(p2.hi, p1.lo), b2 = two_sum(a1.lo, b1.lo), c2 = two_sum(a2.hi, b2.hi);
+        const dd d2 = two_sum(c2.hi, t1.lo), t2 = two_sum(s.s2, d2.hi);
+        const dd a3 = two_sum(b2.lo, c2.lo), b3 = two_sum(d2.lo, t2.lo), c3 = two_sum(a3.hi, b3.hi);
+        const dd d3 = two_sum(c3.hi, fma(a, v.x3, p2.lo) + a2.lo), t3 = two_sum(s.s3, d3.hi);
+        s.s0 = t0.hi;
+        s.s1 = t1.hi;
+        s.s2 = t2.hi;
+        s.s3 = t3.hi;
+        s.s4 += ((a3.lo + b3.lo) + c3.lo) + (d3.lo + t3.lo);
+    }
     __device__ __forceinline__ void add(const ArithQD::C &v, double a)
     {
-        s = ArithQD::add(s, ArithQD::scale(v, a));
+        one(re, v.re, a);
+        one(im, v.im, a);
     }
-    __device__ __forceinline__ ArithQD::C get() const { return s; }
+    __device__ __forceinline__ static qd sum(const Sums &s)
+    {
+        double e[5] = {s.s0, s.s1, s.s2, s.s3, s.s4};
+        return distill<5>(e);
+    }
+    __device__ __forceinline__ ArithQD::C get() const { return {sum(re), sum(im)}; }
 };
 
 // 1 / x
