@@ -387,6 +387,32 @@ void quot_lanes(QuotArgs &a, int m, int nt)
     a.log2S = ranks * 4 <= nt ? 2 : (ranks * 2 <= nt ? 1 : 0);
 }
 
+hipError_t System::run_values(const Quot &q, int prec, QuotArgs qa, hipStream_t hs) const
+{
+    const int words = prec == 0 ? 2 : (prec == 1 ? 4 : 8);
+    const int cap = prec == 2 ? 512 : 1024;
+    const int64_t P = qa.n_points, units = P * n_polys;
+    // the power table alone
+    const auto lds_for = [&](int T) {
+        return ((size_t)max_exp * n_vars + (quot_pad ? 1 : 0)) * T * words * sizeof(double);
+    };
+    const int T = prec == 0 && P >= kPointsF64 && lds_for(kPointsF64) <= (size_t)kMaxLds ? kPointsF64 : 1;
+    const size_t lds = lds_for(T);
+    const int per_cu = (int)std::max<size_t>(1, kMaxLds / lds);
+    // the smallest workgroups that fill the CU's registers, at most a wave
+    // for each polynomial
+    int nt = 64;
+    while (nt < cap && nt * per_cu < cap && nt < 64 * n_polys) nt *= 2;
+    const int nw = nt / 64, resident = 256 * std::max(1, std::min(per_cu, cap / nt));
+    const int64_t tiles = (P + T - 1) / T;
+    // four rounds of the chip, if there is work for them; whole rounds of waves
+    int64_t pp = std::max<int64_t>(1, std::min<int64_t>(n_polys, units / T / ((int64_t)resident * 4)));
+    qa.PP = (int)((pp + nw - 1) / nw * nw);
+    qa.nbuf = 1;
+    const dim3 grid((unsigned)((n_polys + qa.PP - 1) / qa.PP), (unsigned)std::min<int64_t>(tiles, 65535), 1);
+    return launch_quot(prec, T, qa, grid, (unsigned)nt, lds, hs);
+}
+
 hipError_t System::run_quot(const Quot &q, int prec, int cc, int maxt, EvalArgs a, unsigned threads,
                             size_t lds, hipStream_t hs) const
 {
@@ -416,6 +442,14 @@ hipError_t System::run_quot(const Quot &q, int prec, int cc, int maxt, EvalArgs 
         return launch_small(prec, cc, maxt, a, qa, dim3((unsigned)n_polys, (unsigned)P, 1), threads,
                             std::max(lds, lds_for(1, 1) + 16), hs);
     }
+    // few workgroups, so that looking for work costs little when there is none
+    const int64_t gy = std::min<int64_t>((P + a.T - 1) / a.T, std::max<int64_t>(1, 2048 / n_polys));
+    const dim3 rgrid((unsigned)n_polys, (unsigned)gy, 1);
+    if (!jac) {
+        hipError_t e = run_values(q, prec, qa, hs);
+        if (e != hipSuccess) return e;
+        return launch_eval(prec, cc, maxt, a, rgrid, dim3(threads), lds, hs);
+    }
     const int cap = prec == 2 ? 512 : 1024;  // threads a CU's registers hold (and a workgroup's limit)
     const int T = prec == 0 && P >= kPointsF64 && lds_for(kPointsF64, 1) <= (size_t)kMaxLds ? kPointsF64 : 1;
     if (lds_for(T, 2) <= (size_t)kMaxLds) qa.nbuf = 2;
@@ -425,7 +459,7 @@ hipError_t System::run_quot(const Quot &q, int prec, int cc, int maxt, EvalArgs 
     // one round of lanes can use
     int nt = 64;
     while (nt < cap && nt * per_cu < cap) nt *= 2;
-    const int most = (std::max(m, jac ? q.n_blk * kRankBlock : 1) * kParts + 63) / 64 * 64;
+    const int most = (std::max(m, q.n_blk * kRankBlock) * kParts + 63) / 64 * 64;
     nt = std::min(nt, most);
     quot_lanes(qa, m, nt);
     // several polynomials per workgroup share one power table, while the
@@ -436,9 +470,7 @@ hipError_t System::run_quot(const Quot &q, int prec, int cc, int maxt, EvalArgs 
     const dim3 grid((unsigned)((n_polys + qa.PP - 1) / qa.PP), (unsigned)std::min<int64_t>(tiles, 65535), 1);
     hipError_t e = launch_quot(prec, T, qa, grid, (unsigned)nt, qlds, hs);
     if (e != hipSuccess) return e;
-    // few workgroups, so that looking for work costs little when there is none
-    const int64_t gy = std::min<int64_t>((P + a.T - 1) / a.T, std::max<int64_t>(1, 2048 / n_polys));
-    return launch_eval(prec, cc, maxt, a, dim3((unsigned)n_polys, (unsigned)gy, 1), dim3(threads), lds, hs);
+    return launch_eval(prec, cc, maxt, a, rgrid, dim3(threads), lds, hs);
 }
 
 pe_status System::eval_plan(int64_t n_points, bool dd, bool no_alloc, Schedule **out, int &T, int &nbuf,

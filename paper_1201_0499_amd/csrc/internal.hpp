@@ -116,6 +116,9 @@ struct System {
     // launch arguments of the quotient kernels (points, outputs, mask and
     // launch shape unset)
     void fill_quot(const Quot &q, QuotArgs &a) const;
+    // values only, of the points, values and mask of qa (made by fill_quot),
+    // leaving what the range rules refuse
+    hipError_t run_values(const Quot &q, int prec, QuotArgs qa, hipStream_t hs) const;
     // evaluation by quotients (prec 0 = FP64, 1 = double-double, 2 =
     // quad-double) of the points, outputs and mask of `a`, whose general
     // kernel with maxt, threads and lds bytes serves what they refuse

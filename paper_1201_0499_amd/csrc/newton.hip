@@ -44,6 +44,11 @@ __global__ __launch_bounds__(NT) void resid_kernel(const ResidArgs a)
     const int n = a.n_vars;
     const int np1 = n + 1;
     const int tid = threadIdx.x;
+    if (a.repair) {
+        bool any = false;
+        for (int p = tid; p < a.n_polys; p += NT) any = any || is_refused(a.f[0][pt * a.n_polys + p]);
+        if (!__syncthreads_or(any)) return;
+    }
     double2 *next = lds_raw;
     const LdsVec<A> pw = LdsVec<A>::at(lds_raw, a.R * np1, next);  // [R][np1]: x^1 .. x^R
 
@@ -62,6 +67,7 @@ __global__ __launch_bounds__(NT) void resid_kernel(const ResidArgs a)
     const int wave = tid >> 6;
     const int n_waves = NT >> 6;
     for (int p = wave; p < a.n_polys; p += n_waves) {
+        if (a.repair && !is_refused(a.f[0][pt * a.n_polys + p])) continue;
         C sum = A::zero();
         for (int64_t s = a.poly_start[p] + lane; s < a.poly_start[p + 1]; s += 64) {
             C v = IO::coef(a.coef, s);

@@ -33,6 +33,7 @@ struct ResidArgs {
     const double *x[8];            // points [P][n]: dd planes 0..3, or quad-double 0..7
     double *f[8];                  // values [P][n_polys], planes as x
     const int32_t *status;         // [P] or nullptr: only kRunning points are evaluated
+    int32_t repair;                // 1: only values that a quotient kernel left (eval.hpp)
 };
 
 // Raise the dynamic LDS limit of the residual kernels (once per process).

@@ -105,11 +105,32 @@ static pe_status newton_core(System *S, int64_t n_starts, double *const *x, int 
     if (!lu_solve_fits(mixed ? 0 : 1, n))
         return fail(PE_EUNSUPPORTED, "the elimination panel (n = %d) does not fit in LDS", n);
 
+    // the residual's values by quotient tables where the system has them, the
+    // residual kernel on what those refuse
+    Quot *quot = nullptr;
+    QuotArgs qa;
+    if (mixed && quotients) {
+        pe_status qs = S->quot_for(rw, false, &quot);
+        if (qs != PE_OK) return qs;
+        if (quot) {
+            S->fill_quot(*quot, qa);
+            qa.n_points = n_starts;
+            for (int q = 0; q < rw; ++q) {
+                qa.x[q] = x[q];
+                qa.f[q] = rp[q];
+            }
+            qa.mask = status_out;
+            ra.repair = 1;
+        }
+    }
+
     if (init && (e = launch_newton_init(n_starts, status_out, iters_out, hs)) != hipSuccess)
         return hip_fail(e, "starting Newton");
     for (;;) {
         pe_status st;
         if (mixed) {
+            if (quot && (e = S->run_values(*quot, qd ? 2 : 1, qa, hs)) != hipSuccess)
+                return hip_fail(e, "residual values");
             if ((e = launch_resid(ra, qd ? 2 : 1, hs)) != hipSuccess)
                 return hip_fail(e, "residual kernel");
         } else {

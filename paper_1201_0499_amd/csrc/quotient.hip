@@ -33,7 +33,8 @@ constexpr int kQuotMaxThreads = 1024;  // 128 registers per lane
 template <>
 constexpr int kQuotMaxThreads<ArithQD> = 512;  // quad-double values take eight registers per part
 
-template <class A, bool JAC>
+// With the Jacobian.
+template <class A>
 __global__ __launch_bounds__(kQuotMaxThreads<A>) void quot_kernel(const QuotArgs a)
 {
     constexpr int T = Pts<A>::T;
@@ -52,10 +53,39 @@ __global__ __launch_bounds__(kQuotMaxThreads<A>) void quot_kernel(const QuotArgs
         if (!live) continue;
         if (!first) __syncthreads();  // the previous points are done with LDS
         first = false;
-        quot_table<A>(a, lds, pt, npt, JAC);
+        quot_table<A>(a, lds, pt, npt, true);
         __syncthreads();
         int vo = 0;
-        for (int p = p0; p < p1; ++p) quot_poly<A>(a, lds, pt, live, p, vo, JAC, [] {});
+        for (int p = p0; p < p1; ++p) quot_poly<A>(a, lds, pt, live, p, vo, true, [] {});
+    }
+}
+
+// Values only: a wave takes whole polynomials, so that nothing but the power
+// table is shared and no wave waits for another.
+template <class A>
+__global__ __launch_bounds__(kQuotMaxThreads<A>) void quot_values_kernel(const QuotArgs a)
+{
+    constexpr int T = Pts<A>::T;
+    HIP_DYNAMIC_SHARED(double2, lds_raw)
+    const int b = xcd_order(blockIdx.x, gridDim.x);
+    const int p0 = b * a.PP, p1 = min(a.n_polys, p0 + a.PP);
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), nw = (int)blockDim.x >> 6;
+    double2 *end;
+    QuotLds<A> lds{};
+    lds.u = LdsVec<A>::at(lds_raw, a.D * a.n_vars + a.pad, end);
+    bool first = true;
+    for (int64_t pt = (int64_t)blockIdx.y * T; pt < a.n_points; pt += (int64_t)gridDim.y * T) {
+        const int npt = (int)min<int64_t>(T, a.n_points - pt);
+        uint32_t live = (1u << npt) - 1;
+        if (a.mask)
+            for (int t = 0; t < npt; ++t)
+                if (a.mask[pt + t] != kMaskLive) live &= ~(1u << t);
+        if (!live) continue;
+        if (!first) __syncthreads();  // the previous points are done with LDS
+        first = false;
+        quot_table<A>(a, lds, pt, npt, false);
+        __syncthreads();
+        for (int p = p0 + wave; p < p1; p += nw) quot_value<A>(a, lds.u, pt, live, p);
     }
 }
 
@@ -85,8 +115,13 @@ __global__ __launch_bounds__(kQuotMaxThreads<A>) void quot_batch_kernel(const Qu
         __syncthreads();  // the previous task is done with LDS
         quot_table<A>(a, lds, task.pt, 1, JAC);
         __syncthreads();
-        int vo = 0;
-        for (int p = task.p0; p < task.p1; ++p) quot_poly<A>(a, lds, task.pt, 1u, p, vo, JAC, [] {});
+        if constexpr (JAC) {
+            int vo = 0;
+            for (int p = task.p0; p < task.p1; ++p) quot_poly<A>(a, lds, task.pt, 1u, p, vo, true, [] {});
+        } else {
+            const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), nw = (int)blockDim.x >> 6;
+            for (int p = task.p0 + wave; p < task.p1; p += nw) quot_value<A>(a, lds.u, task.pt, 1u, p);
+        }
     }
 }
 
@@ -95,11 +130,11 @@ using QuotBatchFn = void (*)(const QuotBatchArgs);
 
 static QuotFn pick_quot(int prec, int T, bool jac)
 {
-    if (prec == 2) return jac ? quot_kernel<ArithQD, true> : quot_kernel<ArithQD, false>;
-    if (prec == 1) return jac ? quot_kernel<ArithDD, true> : quot_kernel<ArithDD, false>;
+    if (prec == 2) return jac ? quot_kernel<ArithQD> : quot_values_kernel<ArithQD>;
+    if (prec == 1) return jac ? quot_kernel<ArithDD> : quot_values_kernel<ArithDD>;
     if (T == kPointsF64)
-        return jac ? quot_kernel<PointsF64<kPointsF64>, true> : quot_kernel<PointsF64<kPointsF64>, false>;
-    return jac ? quot_kernel<Arith64, true> : quot_kernel<Arith64, false>;
+        return jac ? quot_kernel<PointsF64<kPointsF64>> : quot_values_kernel<PointsF64<kPointsF64>>;
+    return jac ? quot_kernel<Arith64> : quot_values_kernel<Arith64>;
 }
 
 static QuotBatchFn pick_quot_batch(int prec, bool jac)

@@ -342,6 +342,57 @@ __device__ __forceinline__ void quot_table(const QuotArgs &a, const QuotLds<A> &
     if (a.pad && threadIdx.x == 0) lds.u.put(a.D * n, A::one());
 }
 
+// Factors of one lane's monomial: the quads of words wp[0], wp[cnt], ...
+// (Q of them) in the canonical order (quotient.hpp).
+template <class A>
+struct Factors {
+    using C = typename A::C;
+    const LdsVec<A> &u;
+    const uint2 *wp;
+    int cnt, Q, qs;  // stride between quads, quads, quads per range
+    Worst<A> &worst;
+
+    __device__ __forceinline__ Factors(const LdsVec<A> &table, const uint2 *words, int stride, int quads,
+                                       Worst<A> &w)
+        : u(table), wp(words), cnt(stride), Q(quads), qs((quads + kParts - 1) / kParts), worst(w)
+    {
+    }
+    __device__ __forceinline__ C quad(const uint2 &w) const
+    {
+        const C u0 = u.get((int)(w.x & 0xFFFFu)), u1 = u.get((int)(w.x >> 16));
+        const C u2 = u.get((int)(w.y & 0xFFFFu)), u3 = u.get((int)(w.y >> 16));
+        return A::mul(A::mul(u0, u1), A::mul(u2, u3));
+    }
+    __device__ __forceinline__ bool has(int r) const { return r * qs < Q; }
+    // product of range r (quads r qs .. ), which has at least one quad
+    __device__ __forceinline__ C range(int r) const
+    {
+        const int j0 = r * qs, j1 = min(Q, j0 + qs);
+        C p = quad(wp[(int64_t)j0 * cnt]);
+        worst.see(p);
+        for (int j = j0 + 1; j < j1; ++j) {
+            p = A::mul(p, quad(wp[(int64_t)j * cnt]));
+            worst.see(p);
+        }
+        return p;
+    }
+    // product of all ranges by one lane
+    __device__ __forceinline__ C all() const
+    {
+        C prod = A::one();
+        for (int h = 0; h < 2 && has(2 * h); ++h) {
+            C t = range(2 * h);
+            if (has(2 * h + 1)) {
+                t = A::mul(t, range(2 * h + 1));
+                worst.see(t);
+            }
+            prod = h == 0 ? t : A::mul(prod, t);
+        }
+        worst.see(prod);
+        return prod;
+    }
+};
+
 // Values of the monomials of chunk ck into V at entry vo.
 template <class A>
 __device__ __forceinline__ void chunk_values(const QuotArgs &a, const int4 &ck, const QuotLds<A> &lds, int vo)
@@ -357,47 +408,22 @@ __device__ __forceinline__ void chunk_values(const QuotArgs &a, const int4 &ck, 
         const bool on = s < ck.y;
         const int sl = __builtin_amdgcn_readfirstlane(s >> 6);
         const int2 sh = a.slice[ck.z + sl];
-        const int cnt = min(64, ck.y - 64 * sl);
-        const uint2 *wp = a.words + (int64_t)sh.x + (on ? s - 64 * sl : 0);
-        const int Q = sh.y, qs = (Q + kParts - 1) / kParts;
-        const typename One::C coef = Io<One>::coef(a.coef, (int64_t)ck.x + (on ? s : 0));
         Worst<A> worst;
-        auto quad = [&](const uint2 &w) {
-            const C u0 = lds.u.get((int)(w.x & 0xFFFFu)), u1 = lds.u.get((int)(w.x >> 16));
-            const C u2 = lds.u.get((int)(w.y & 0xFFFFu)), u3 = lds.u.get((int)(w.y >> 16));
-            return A::mul(A::mul(u0, u1), A::mul(u2, u3));
-        };
-        // product of range r (quads r qs .. ), which has at least one quad
-        auto range = [&](int r) {
-            const int j0 = r * qs, j1 = min(Q, j0 + qs);
-            C p = quad(wp[(int64_t)j0 * cnt]);
-            worst.see(p);
-            for (int j = j0 + 1; j < j1; ++j) {
-                p = A::mul(p, quad(wp[(int64_t)j * cnt]));
-                worst.see(p);
-            }
-            return p;
-        };
+        const Factors<A> fac(lds.u, a.words + (int64_t)sh.x + (on ? s - 64 * sl : 0), min(64, ck.y - 64 * sl),
+                             sh.y, worst);
+        const typename One::C coef = Io<One>::coef(a.coef, (int64_t)ck.x + (on ? s : 0));
         C prod = A::one();
         if (log2L == 0) {
-            for (int h = 0; h < 2 && 2 * h * qs < Q; ++h) {
-                C t = range(2 * h);
-                if ((2 * h + 1) * qs < Q) {
-                    t = A::mul(t, range(2 * h + 1));
-                    worst.see(t);
-                }
-                prod = h == 0 ? t : A::mul(prod, t);
-            }
-            worst.see(prod);
+            prod = fac.all();
         } else {
             // ranges 2 sub, 2 sub + 1 of two lanes, or range sub of four; a
             // lower lane's product is the left factor, and only what reaches
             // the group's first lane counts
             const int r0 = log2L == 1 ? 2 * sub : sub;
-            if (r0 * qs < Q) {
-                prod = range(r0);
-                if (log2L == 1 && (r0 + 1) * qs < Q) {
-                    prod = A::mul(prod, range(r0 + 1));
+            if (fac.has(r0)) {
+                prod = fac.range(r0);
+                if (log2L == 1 && fac.has(r0 + 1)) {
+                    prod = A::mul(prod, fac.range(r0 + 1));
                     worst.see(prod);
                 }
             }
@@ -411,6 +437,80 @@ __device__ __forceinline__ void chunk_values(const QuotArgs &a, const int4 &ck, 
         worst.mark(prod);
         if (on && sub == 0) lds.V.put(vo + s, prod);
     }
+}
+
+// Sum over the wave, by a butterfly.
+template <class A>
+__device__ __forceinline__ typename A::C wave_sum(typename A::C v)
+{
+    using P = Pts<A>;
+    v = P::template sum_over<1>(v);
+    v = P::template sum_over<2>(v);
+    v = P::template sum_over<4>(v);
+    v = P::template sum_over<8>(v);
+    v = P::template sum_over<16>(v);
+    return P::template sum_over<32>(v);
+}
+
+// f_p (o == n) or df_p/dx_o at the live points from pt on.  on_refused() runs
+// on the lane that finds a value refused.
+template <class A, class Refused>
+__device__ __forceinline__ void quot_store(const QuotArgs &a, int64_t pt, uint32_t live, int p, int o,
+                                           const typename A::C &v, const Refused &on_refused)
+{
+    using P = Pts<A>;
+    using One = typename P::One;
+    const int n = a.n_vars;
+#pragma unroll
+    for (int t = 0; t < P::T; ++t) {
+        if (P::T > 1 && !((live >> t) & 1u)) continue;
+        const typename One::C w = P::at(v, t);
+        if (o == n) {
+            // a product out of range left a NaN among the values
+            if (!isfinite(lead_re(w)) || !isfinite(lead_im(w))) {
+                a.f[0][(pt + t) * a.n_polys + p] = refused();
+                on_refused();
+            } else {
+                Io<One>::store(a.f, (pt + t) * a.n_polys + p, w);
+            }
+        } else {
+            Io<One>::store(a.J, ((pt + t) * n + o) * a.n_polys + p, plus_zero(w));
+        }
+    }
+}
+
+// The value of polynomial p by one wave, without the Jacobian: lane l
+// multiplies monomials l, l + 64, ... of a chunk and adds their values, then
+// the wave adds the lanes; the same operations in the same order as
+// chunk_values and chunk_sums.
+template <class A>
+__device__ __forceinline__ void quot_value(const QuotArgs &a, const LdsVec<A> &u, int64_t pt, uint32_t live, int p)
+{
+    using C = typename A::C;
+    using P = Pts<A>;
+    using One = typename P::One;
+    const int lane = (int)threadIdx.x & 63;
+    const int4 pl = a.poly[p];
+    C f = pl.z > 0 ? P::all(Io<One>::coef(a.sys_coef, pl.z - 1)) : A::zero();
+    for (int c = pl.x; c < pl.y; ++c) {
+        const int4 ck = a.chunk[c];
+        RunAcc<A> acc;
+        acc.clear();
+        for (int sl = 0; 64 * sl < ck.y; ++sl) {
+            const int2 sh = a.slice[ck.z + sl];
+            const int cnt = min(64, ck.y - 64 * sl);
+            if (lane >= cnt) break;  // the chunk's last slice
+            Worst<A> worst;
+            const Factors<A> fac(u, a.words + (int64_t)sh.x + lane, cnt, sh.y, worst);
+            const typename One::C coef = Io<One>::coef(a.coef, (int64_t)ck.x + 64 * sl + lane);
+            C v = A::mul(fac.all(), P::all(coef));
+            worst.mark(v);
+            acc.add(v, 1.0);
+        }
+        const C v = wave_sum<A>(acc.get());
+        f = c == pl.x && pl.z == 0 ? v : A::sum(f, v);
+    }
+    if (lane == 0) quot_store<A>(a, pt, live, p, a.n_vars, f, [] {});
 }
 
 // Sum of a run by one lane's NP of its kParts partial sums, combined with
@@ -455,7 +555,6 @@ __device__ __forceinline__ void chunk_sums(const QuotArgs &a, int ci, const int4
                                            int vo, bool jac, const Put &put)
 {
     using C = typename A::C;
-    using P = Pts<A>;
     constexpr int S = kParts / NP;
     const int lane = (int)threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int nw = (int)blockDim.x >> 6;
@@ -481,21 +580,15 @@ __device__ __forceinline__ void chunk_sums(const QuotArgs &a, int ci, const int4
             RunAcc<A> acc;
             acc.clear();
             for (int i = lane; i < ck.y; i += 64) acc.add(lds.V.get(vo + i), 1.0);
-            C v = acc.get();
-            v = P::template sum_over<1>(v);
-            v = P::template sum_over<2>(v);
-            v = P::template sum_over<4>(v);
-            v = P::template sum_over<8>(v);
-            v = P::template sum_over<16>(v);
-            v = P::template sum_over<32>(v);
+            const C v = wave_sum<A>(acc.get());
             if (lane == 0) put(a.n_vars, v);
         }
     }
 }
 
-// Polynomial p at points pt .. pt+npt-1 of which those with their bit set in
-// live are written; vo is the buffer in use (it alternates).  on_refused()
-// runs on the lane that finds a value refused.
+// Polynomial p at the points from pt on, of which those with their bit set in
+// live are written; vo is the buffer in use (it alternates).  on_refused: see
+// quot_store.
 template <class A, class Refused>
 __device__ __forceinline__ void quot_poly(const QuotArgs &a, const QuotLds<A> &lds, int64_t pt, uint32_t live,
                                           int p, int &vo, bool jac, const Refused &on_refused)
@@ -520,22 +613,7 @@ __device__ __forceinline__ void quot_poly(const QuotArgs &a, const QuotLds<A> &l
                 return;
             }
             if (o != n) v = A::mul(lds.y.get(o), v);
-#pragma unroll
-            for (int t = 0; t < P::T; ++t) {
-                if (P::T > 1 && !((live >> t) & 1u)) continue;
-                typename One::C w = P::at(v, t);
-                if (o == n) {
-                    // a product out of range left a NaN among the values
-                    if (!isfinite(lead_re(w)) || !isfinite(lead_im(w))) {
-                        a.f[0][(pt + t) * a.n_polys + p] = refused();
-                        on_refused();
-                    } else {
-                        Io<One>::store(a.f, (pt + t) * a.n_polys + p, w);
-                    }
-                } else {
-                    Io<One>::store(a.J, ((pt + t) * n + o) * a.n_polys + p, plus_zero(w));
-                }
-            }
+            quot_store<A>(a, pt, live, p, o, v, on_refused);
         };
         if (a.log2S == 0)
             chunk_sums<A, 4>(a, c, ck, lds, vo, jac, put);
