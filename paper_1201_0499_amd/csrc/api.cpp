@@ -379,12 +379,14 @@ void System::fill_quot(const Quot &q, QuotArgs &a) const
     a.sys_coef = (const double *)coef.ptr;
 }
 
-// Lanes per monomial and per run on nt threads: as many as fit one round.
-void quot_lanes(QuotArgs &a, int m, int nt)
+// Lanes per monomial and per run on nt threads.  Calls of few workgroups: as
+// many as fit one round.  Others: two lanes per run, whose reads of the
+// values the packer spread over the LDS banks.
+void quot_lanes(QuotArgs &a, int m, int nt, bool few)
 {
     const int ranks = a.n_blk * kRankBlock;
     a.log2L = m * 4 <= nt ? 2 : (m * 2 <= nt ? 1 : 0);
-    a.log2S = ranks * 4 <= nt ? 2 : (ranks * 2 <= nt ? 1 : 0);
+    a.log2S = few ? (ranks * 4 <= nt ? 2 : (ranks * 2 <= nt ? 1 : 0)) : 1;
 }
 
 hipError_t System::run_values(const Quot &q, int prec, QuotArgs qa, hipStream_t hs) const
@@ -438,7 +440,7 @@ hipError_t System::run_quot(const Quot &q, int prec, int cc, int maxt, EvalArgs 
         return quot_lds_bytes(n_vars, max_exp, quot_pad, q.CH, q.multi, nbuf, T * words);
     };
     if (units <= kSmallUnits && a.T == 1 && a.nbuf == 1) {
-        quot_lanes(qa, m, (int)threads);
+        quot_lanes(qa, m, (int)threads, true);
         return launch_small(prec, cc, maxt, a, qa, dim3((unsigned)n_polys, (unsigned)P, 1), threads,
                             std::max(lds, lds_for(1, 1) + 16), hs);
     }
@@ -461,7 +463,7 @@ hipError_t System::run_quot(const Quot &q, int prec, int cc, int maxt, EvalArgs 
     while (nt < cap && nt * per_cu < cap) nt *= 2;
     const int most = (std::max(m, q.n_blk * kRankBlock) * kParts + 63) / 64 * 64;
     nt = std::min(nt, most);
-    quot_lanes(qa, m, nt);
+    quot_lanes(qa, m, nt, false);
     // several polynomials per workgroup share one power table, while the
     // workgroups still make eight rounds of the chip
     const int64_t resident = 256 * std::max(1, std::min(per_cu, cap / nt));

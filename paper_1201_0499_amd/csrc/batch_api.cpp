@@ -117,7 +117,7 @@ static pe_status build_quot(Batch &B, const std::vector<BatchDesc> &descs, int d
         QuotArgs &a = qd[(size_t)i].a;
         if (a.CH == 0) continue;
         a.nbuf = nbuf;
-        quot_lanes(a, (int)std::max<int64_t>(1, std::min<int64_t>(B.sys[(size_t)i]->quot_max_m, a.CH)), nt);
+        quot_lanes(a, (int)std::max<int64_t>(1, std::min<int64_t>(B.sys[(size_t)i]->quot_max_m, a.CH)), nt, false);
     }
     const hipError_t e = ql.desc.upload(qd.data(), qd.size() * sizeof(QuotBatchDesc));
     if (e != hipSuccess) return hip_fail(e, "uploading batch tables");

@@ -57,7 +57,7 @@ struct Quot {
 };
 
 // lanes per monomial (of at most m in a chunk) and per run for nt threads
-void quot_lanes(QuotArgs &a, int m, int nt);
+void quot_lanes(QuotArgs &a, int m, int nt, bool few);
 
 struct System {
     int32_t n_vars = 0, n_polys = 0;

@@ -58,7 +58,9 @@ inline int quot_point_exp(int d)
 // Packed tables of one system for chunks of CH monomials.  Monomials of a
 // polynomial are ordered by their number of variables, most first (stable),
 // so that the 64 monomials of a slice need about the same number of quads;
-// one constant monomial per polynomial is folded into the value output.
+// one constant monomial per polynomial is folded into the value output.  The
+// order of a monomial's factors and of a run's terms is chosen for the LDS
+// (quotient_tables.cpp).
 struct QuotTables {
     int CH = 0;            // monomials per chunk (a multiple of 64)
     int n_blk = 0;         // rank blocks per chunk

@@ -50,25 +50,29 @@ struct PointsF64 {
     }
 };
 
-// entries of T values of 16 bytes, so that one address serves all points
+// T arrays of 16-byte values: the packer spreads the entries that 16 lanes
+// read together over the banks (quotient_tables.cpp), for any array of them
 template <int T>
 struct LdsVec<PointsF64<T>> {
     using C = typename PointsF64<T>::C;
     double2 *p;
+    int count;
     __device__ __forceinline__ C get(int i) const
     {
-        const double2 *q = p + T * i;
-        return PointsF64<T>::each([&](int t) { return Arith64::C{q[t].x, q[t].y}; });
+        return PointsF64<T>::each([&](int t) {
+            const double2 v = p[t * count + i];
+            return Arith64::C{v.x, v.y};
+        });
     }
     __device__ __forceinline__ void put(int i, const C &c) const
     {
 #pragma unroll
-        for (int t = 0; t < T; ++t) p[T * i + t] = make_double2(c.v[t].re, c.v[t].im);
+        for (int t = 0; t < T; ++t) p[t * count + i] = make_double2(c.v[t].re, c.v[t].im);
     }
     __device__ __forceinline__ static LdsVec at(double2 *raw, int count, double2 *&next)
     {
         next = raw + T * (size_t)count;
-        return {raw};
+        return {raw, count};
     }
 };
 

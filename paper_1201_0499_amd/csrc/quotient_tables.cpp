@@ -52,6 +52,93 @@ void quot_shape(const CsrView &S, bool &pad, int64_t &max_m)
     }
 }
 
+namespace {
+
+// LDS reads of 16 bytes per lane serve 16 consecutive lanes at a time, each
+// from its own sixteenth of the banks (entry modulo 16) at best; random
+// entries need three times as long (3.1 lanes on the worst sixteenth).  The
+// order of a monomial's factors and of a run's terms is free, so the packer
+// chooses it: a pool holds one lane's entries by bank, and each step of 16
+// lanes takes one from each, on banks not yet used where there are such.
+struct Pool {
+    std::vector<uint16_t> item;  // the entries, by bank
+    int next[17];                // next[b] .. end of bank b in item
+    int left[16];                // entries left on each bank
+    unsigned mask = 0;           // banks with entries left
+    int total = 0;               // entries left
+
+    template <class Bank>
+    void fill(const uint16_t *src, int n, const Bank &bank)
+    {
+        std::fill(left, left + 16, 0);
+        for (int i = 0; i < n; ++i) ++left[bank(src[i])];
+        next[0] = 0;
+        mask = 0;
+        for (int b = 0; b < 16; ++b) {
+            next[b + 1] = next[b] + left[b];
+            if (left[b]) mask |= 1u << b;
+        }
+        item.resize((size_t)n);
+        int at[16];
+        std::copy(next, next + 16, at);
+        for (int i = 0; i < n; ++i) item[(size_t)at[bank(src[i])]++] = src[i];
+        total = n;
+    }
+    uint16_t pop(int b) { return item[(size_t)next[b]++]; }
+    void reserve(int b)
+    {
+        if (--left[b] == 0) mask &= ~(1u << b);
+        --total;
+    }
+    void give_back(int b)
+    {
+        ++left[b];
+        mask |= 1u << b;
+        ++total;
+    }
+};
+
+// One step: a bank for each of `lanes` lanes (of pool lane_pool[l]; -1: the
+// pool is empty), distinct if that is easy: a lane without a free bank may
+// take another's if that one finds a free one instead.
+void choose_banks(Pool *const *lane_pool, int lanes, int (&bank)[16])
+{
+    unsigned free = 0xFFFFu;
+    int owner[16];
+    for (int l = 0; l < lanes; ++l) {
+        Pool &me = *lane_pool[l];
+        if (me.total == 0) {
+            bank[l] = -1;
+            continue;
+        }
+        int b = -1;
+        if (me.mask & free) {
+            b = __builtin_ctz(me.mask & free);
+        } else {
+            for (unsigned m = me.mask; m; m &= m - 1) {
+                const int c = __builtin_ctz(m), o = owner[c];
+                const unsigned other = lane_pool[o]->mask & free;
+                if (!other) continue;
+                const int d = __builtin_ctz(other);
+                lane_pool[o]->give_back(c);
+                lane_pool[o]->reserve(d);
+                bank[o] = d;
+                owner[d] = o;
+                free &= ~(1u << d);
+                b = c;
+                break;
+            }
+            if (b < 0) b = __builtin_ctz(me.mask);
+        }
+        me.reserve(b);
+        bank[l] = b;
+        owner[b] = l;
+        free &= ~(1u << b);
+    }
+}
+
+}  // namespace
+
 std::string build_quot_tables(const CsrView &S, QuotTables &t)
 {
     const int n = S.n_vars, CH = t.CH;
@@ -72,8 +159,12 @@ std::string build_quot_tables(const CsrView &S, QuotTables &t)
     t.runs.clear();
     t.out.clear();
     t.mono.reserve((size_t)S.n_monos);
-    std::vector<int32_t> len((size_t)n), rank((size_t)n), at((size_t)n), order((size_t)n), bin;
+    std::vector<int32_t> len((size_t)n), rank((size_t)n), at((size_t)n + 1), order((size_t)n), bin;
     std::vector<int32_t> by_k[257];
+    Pool pool[kRankBlock];
+    std::vector<uint16_t> list, terms;
+    std::vector<int32_t> first_term;
+    const uint16_t pad_word = (uint16_t)(max_exp * n);
     int64_t rows_total = 0;
     for (int p = 0; p < S.n_polys; ++p) {
         const int64_t s0 = S.poly_start[p], s1 = S.poly_start[p + 1];
@@ -116,15 +207,33 @@ std::string build_quot_tables(const CsrView &S, QuotTables &t)
                 if (w0 / kQuad + (size_t)quads * sc > (size_t)INT32_MAX) return "tables too large";
                 t.slice.push_back((int32_t)(w0 / kQuad));
                 t.slice.push_back(quads);
-                t.words.resize(w0 + (size_t)quads * sc * kQuad, (uint16_t)(max_exp * n));
-                for (int q = 0; q < sc; ++q) {
-                    const int32_t s = t.mono[(size_t)(a + b + q)];
-                    const int64_t e0 = S.mono_start[s], k = S.mono_start[s + 1] - e0;
-                    for (int64_t j = 0; j < k; ++j) {
-                        const int pos = S.pos[e0 + j];
-                        t.words[w0 + ((size_t)(j / kQuad) * sc + q) * kQuad + j % kQuad] =
-                            (uint16_t)((S.exp[e0 + j] - 1) * n + pos);
-                        ++len[(size_t)pos];
+                t.words.resize(w0 + (size_t)quads * sc * kQuad, pad_word);
+                // groups of 16 lanes (one lane per monomial) choose their
+                // factors position by position
+                for (int g = 0; g < sc; g += 16) {
+                    const int lanes = std::min(16, sc - g);
+                    int kmax_g = 0;
+                    for (int q = 0; q < lanes; ++q) {
+                        const int32_t s = t.mono[(size_t)(a + b + g + q)];
+                        const int64_t e0 = S.mono_start[s], k = S.mono_start[s + 1] - e0;
+                        list.resize((size_t)k);
+                        for (int64_t j = 0; j < k; ++j) {
+                            const int pos = S.pos[e0 + j];
+                            list[(size_t)j] = (uint16_t)((S.exp[e0 + j] - 1) * n + pos);
+                            ++len[(size_t)pos];
+                        }
+                        pool[q].fill(list.data(), (int)k, [](uint16_t v) { return v & 15; });
+                        kmax_g = std::max(kmax_g, (int)k);
+                    }
+                    Pool *lane_pool[16];
+                    int bank[16];
+                    for (int q = 0; q < lanes; ++q) lane_pool[q] = &pool[q];
+                    for (int j = 0; j < kmax_g; ++j) {
+                        choose_banks(lane_pool, lanes, bank);
+                        for (int q = 0; q < lanes; ++q)
+                            if (bank[q] >= 0)
+                                t.words[w0 + ((size_t)(j / kQuad) * sc + g + q) * kQuad + j % kQuad] =
+                                    pool[q].pop(bank[q]);
                     }
                 }
             }
@@ -150,16 +259,39 @@ std::string build_quot_tables(const CsrView &S, QuotTables &t)
                 rows_total += rows;
             }
             t.runs.resize((size_t)rows_total * kRankBlock * kParts, (uint16_t)0);
-            std::fill(at.begin(), at.end(), 0);
+            // the outputs' terms, one output after another, in monomial order
+            first_term.assign((size_t)n + 1, 0);
+            for (int o = 0; o < n; ++o) first_term[(size_t)o + 1] = first_term[(size_t)o] + len[(size_t)o];
+            terms.resize((size_t)first_term[(size_t)n]);
+            std::copy(first_term.begin(), first_term.end() - 1, at.begin());
             for (int i = 0; i < cnt; ++i) {
                 const int32_t s = t.mono[(size_t)(a + i)];
-                for (int64_t e = S.mono_start[s]; e < S.mono_start[s + 1]; ++e) {
-                    const size_t o = (size_t)S.pos[e];
-                    const int j = rank[o], term = at[o]++;
-                    const size_t row = (size_t)t.block[blk0 + 2 * (size_t)(j / kRankBlock)] +
-                                       (size_t)(term / kParts);
-                    t.runs[(row * kRankBlock + (size_t)(j % kRankBlock)) * kParts + term % kParts] =
-                        (uint16_t)(i | (S.exp[e] << kEntryBits));
+                for (int64_t e = S.mono_start[s]; e < S.mono_start[s + 1]; ++e)
+                    terms[(size_t)at[(size_t)S.pos[e]]++] = (uint16_t)(i | (S.exp[e] << kEntryBits));
+            }
+            // 16 lanes take eight runs, two terms of each (parts p and p + 2:
+            // two lanes per run)
+            for (int blk = 0; blk < t.n_blk; ++blk) {
+                const size_t row0 = (size_t)t.block[blk0 + 2 * (size_t)blk];
+                const int rows = t.block[blk0 + 2 * (size_t)blk + 1];
+                for (int h = 0; h < kRankBlock; h += 8) {
+                    for (int q = 0; q < 8; ++q) {
+                        const int j = blk * kRankBlock + h + q;
+                        const int o = j < n ? order[(size_t)j] : -1;
+                        pool[q].fill(o < 0 ? nullptr : terms.data() + first_term[(size_t)o],
+                                     o < 0 ? 0 : len[(size_t)o], [](uint16_t v) { return v & 15; });
+                    }
+                    Pool *lane_pool[16];
+                    int bank[16];
+                    for (int q = 0; q < 16; ++q) lane_pool[q] = &pool[q % 8];
+                    for (int r = 0; r < rows; ++r)
+                        for (int part = 0; part < 2; ++part) {
+                            uint16_t *row = t.runs.data() + ((row0 + (size_t)r) * kRankBlock + (size_t)h) * kParts;
+                            choose_banks(lane_pool, 16, bank);
+                            for (int q = 0; q < 16; ++q)
+                                if (bank[q] >= 0)
+                                    row[q % 8 * kParts + part + q / 8 * 2] = pool[q % 8].pop(bank[q]);
+                        }
                 }
             }
         }

@@ -38,13 +38,7 @@ std::string build_schedule_tables(const CsrView &S, ScheduleTables &t)
     t.group_chunk0.clear();
     t.any_fold = 0;
     int stage_slots = 1, max_rows = 0;
-    std::vector<int32_t> len_of, order, rank_of;
-
-    struct Term {
-        int32_t out;
-        int32_t seq;  // monomial * KP + variable: monomial order within an output
-    };
-    std::vector<Term> terms;
+    std::vector<int32_t> len_of, order, rank_of, bin, at;
 
     std::vector<int32_t> folded((size_t)S.n_polys, 0);
     for (int p = 0; p < S.n_polys; ++p) {
@@ -64,65 +58,65 @@ std::string build_schedule_tables(const CsrView &S, ScheduleTables &t)
         for (int c = 0; c < nch; ++c) {
             const int64_t a = s0 + (int64_t)c * MC;
             const int64_t b = std::min<int64_t>(s1, a + MC);
-            terms.clear();
+            // lengths of the outputs' runs: derivative terms, and the value
+            // terms of the monomials sl = 0, VG, ...
+            len_of.assign((size_t)n + 1, 0);
+            int T = 0;
             for (int64_t s = a; s < b; ++s) {
-                const int sl = (int)(s - a);
                 const int64_t e0 = S.mono_start[s], e1 = S.mono_start[s + 1];
-                const int k = (int)(e1 - e0);
-                if (k > KP) return "a monomial has more variables than lanes*chunk_vars";
-                for (int j = 0; j < k; ++j) {
-                    t.word[(size_t)s * KP + j] = pack_word(S.pos[e0 + j], S.exp[e0 + j]);
-                    terms.push_back({S.pos[e0 + j], sl * KP + j});
+                if (e1 - e0 > KP) return "a monomial has more variables than lanes*chunk_vars";
+                for (int64_t e = e0; e < e1; ++e) {
+                    t.word[(size_t)(s * KP + (e - e0))] = pack_word(S.pos[e], S.exp[e]);
+                    ++len_of[(size_t)S.pos[e]];
                 }
-                if (sl % VG == 0) terms.push_back({n, sl * KP});  // value of sl .. sl+VG-1
+                T += (int)(e1 - e0);
+                if ((s - a) % VG == 0) {
+                    ++len_of[(size_t)n];
+                    ++T;
+                }
             }
-            std::sort(terms.begin(), terms.end(), [](const Term &x, const Term &y) {
-                return x.out != y.out ? x.out < y.out : x.seq < y.seq;
-            });
-            const int T = (int)terms.size();
             if (T + 1 > 65535) return "too many terms in one chunk";
             if (t.max_stage > 0 && T + 1 > t.max_stage)
                 return "the term staging of a chunk does not fit (too many terms)";
-            // outputs by run length, longest first (ties by output); row i
-            // holds the i-th term (in monomial order) of every output whose
-            // run is longer than i, the j-th longest output at row_start[i] + j
-            len_of.assign((size_t)n + 1, 0);
-            for (const Term &x : terms) ++len_of[(size_t)x.out];
+            // outputs by run length, longest first (ties by output; a stable
+            // counting sort); row i holds the i-th term (in monomial order) of
+            // every output whose run is longer than i, the j-th longest
+            // output at row_start[i] + j
+            const int lmax = (int)(b - a);
+            bin.assign((size_t)lmax + 2, 0);
+            for (int o = 0; o <= n; ++o) ++bin[(size_t)(lmax - len_of[(size_t)o]) + 1];
+            for (int l = 0; l <= lmax; ++l) bin[(size_t)l + 1] += bin[(size_t)l];
             order.resize((size_t)n + 1);
-            for (int o = 0; o <= n; ++o) order[(size_t)o] = o;
-            std::stable_sort(order.begin(), order.end(),
-                             [&](int x, int y) { return len_of[(size_t)x] > len_of[(size_t)y]; });
-            rank_of.assign((size_t)n + 1, 0);
-            for (int j = 0; j <= n; ++j) {
-                rank_of[(size_t)order[(size_t)j]] = j;
+            rank_of.resize((size_t)n + 1);
+            for (int o = 0; o <= n; ++o) {
+                const int j = bin[(size_t)(lmax - len_of[(size_t)o])]++;
+                order[(size_t)j] = o;
+                rank_of[(size_t)o] = j;
+            }
+            for (int j = 0; j <= n; ++j)
                 t.run_info.push_back((uint32_t)order[(size_t)j] |
                                      ((uint32_t)len_of[(size_t)order[(size_t)j]] << 16));
-            }
             const int rows = len_of[(size_t)order[0]];
             const int row0 = (int)t.row_start.size();
-            int acc_rows = 0;
+            int acc_rows = 0, cnt = n + 1;
             for (int i = 0; i < rows; ++i) {
                 t.row_start.push_back((uint16_t)acc_rows);
-                int cnt = 0;
-                while (cnt <= n && len_of[(size_t)order[(size_t)cnt]] > i) ++cnt;
+                while (cnt > 0 && len_of[(size_t)order[(size_t)cnt - 1]] <= i) --cnt;
                 acc_rows += cnt;
             }
             t.row_start.push_back((uint16_t)acc_rows);  // == T
             max_rows = std::max(max_rows, rows);
-            // terms are sorted by (output, monomial): the i-th term of each
-            // output is the i-th of its run
-            for (int q = 0; q < T;) {
-                const int o = terms[q].out;
-                int i = 0;
-                for (; q < T && terms[q].out == o; ++q, ++i) {
-                    const int slot = t.row_start[(size_t)row0 + i] + rank_of[(size_t)o];
-                    const int sl = terms[q].seq / KP;
-                    const int j = terms[q].seq % KP;
-                    if (o == n)
-                        t.vdest[(size_t)(a + sl)] = (uint16_t)slot;
-                    else
-                        t.dest[(size_t)(a + sl) * KP + j] = (uint16_t)slot;
-                }
+            // in monomial order, the i-th term of each output is the i-th of
+            // its run
+            at.assign((size_t)n + 1, 0);
+            auto slot_of = [&](int o) {
+                const int i = at[(size_t)o]++;
+                return (uint16_t)(t.row_start[(size_t)(row0 + i)] + rank_of[(size_t)o]);
+            };
+            for (int64_t s = a; s < b; ++s) {
+                const int64_t e0 = S.mono_start[s], e1 = S.mono_start[s + 1];
+                for (int64_t e = e0; e < e1; ++e) t.dest[(size_t)(s * KP + (e - e0))] = slot_of(S.pos[e]);
+                if ((s - a) % VG == 0) t.vdest[(size_t)s] = slot_of(n);
             }
             stage_slots = std::max(stage_slots, T + 1);
             const int32_t chunk = (int32_t)(t.chunk_info.size() / 4);
