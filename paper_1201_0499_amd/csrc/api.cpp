@@ -379,14 +379,25 @@ void System::fill_quot(const Quot &q, QuotArgs &a) const
     a.sys_coef = (const double *)coef.ptr;
 }
 
-// Lanes per monomial and per run on nt threads.  Calls of few workgroups: as
-// many as fit one round.  Others: two lanes per run, whose reads of the
-// values the packer spread over the LDS banks.
-void quot_lanes(QuotArgs &a, int m, int nt, bool few)
+// Lanes per monomial (of at most m in a chunk) and per run on nt threads in
+// calls of few workgroups: as many as fit one round.
+static void few_lanes(QuotArgs &a, int m, int nt)
 {
     const int ranks = a.n_blk * kRankBlock;
     a.log2L = m * 4 <= nt ? 2 : (m * 2 <= nt ? 1 : 0);
-    a.log2S = few ? (ranks * 4 <= nt ? 2 : (ranks * 2 <= nt ? 1 : 0)) : 1;
+    a.log2S = ranks * 4 <= nt ? 2 : (ranks * 2 <= nt ? 1 : 0);
+}
+
+// Workgroup size of the other calls, with one lane per monomial and two per
+// run, whose reads of the values the packer spread over the LDS banks: the
+// smallest that fills the CU's registers (cap threads) with the workgroups
+// its LDS holds, no larger than one round of lanes can use.
+int quot_threads(int m, int ranks, size_t lds, int cap)
+{
+    const int per_cu = (int)std::max<size_t>(1, kMaxLds / lds);
+    int nt = 64;
+    while (nt < cap && nt * per_cu < cap) nt *= 2;
+    return std::min(nt, (std::max(m, ranks * 2) + 63) / 64 * 64);
 }
 
 hipError_t System::run_values(const Quot &q, int prec, QuotArgs qa, hipStream_t hs) const
@@ -440,7 +451,7 @@ hipError_t System::run_quot(const Quot &q, int prec, int cc, int maxt, EvalArgs 
         return quot_lds_bytes(n_vars, max_exp, quot_pad, q.CH, q.multi, nbuf, T * words);
     };
     if (units <= kSmallUnits && a.T == 1 && a.nbuf == 1) {
-        quot_lanes(qa, m, (int)threads, true);
+        few_lanes(qa, m, (int)threads);
         return launch_small(prec, cc, maxt, a, qa, dim3((unsigned)n_polys, (unsigned)P, 1), threads,
                             std::max(lds, lds_for(1, 1) + 16), hs);
     }
@@ -457,20 +468,24 @@ hipError_t System::run_quot(const Quot &q, int prec, int cc, int maxt, EvalArgs 
     if (lds_for(T, 2) <= (size_t)kMaxLds) qa.nbuf = 2;
     const size_t qlds = lds_for(T, qa.nbuf);
     const int per_cu = (int)std::max<size_t>(1, kMaxLds / qlds);
-    // the smallest workgroups that fill the CU's registers, no larger than
-    // one round of lanes can use
-    int nt = 64;
-    while (nt < cap && nt * per_cu < cap) nt *= 2;
-    const int most = (std::max(m, q.n_blk * kRankBlock) * kParts + 63) / 64 * 64;
-    nt = std::min(nt, most);
-    quot_lanes(qa, m, nt, false);
+    const int nt = quot_threads(m, q.n_blk * kRankBlock, qlds, cap);
     // several polynomials per workgroup share one power table, while the
-    // workgroups still make eight rounds of the chip
+    // workgroups still make eight rounds of the chip.  With at least 128
+    // workgroups' worth of polynomials each XCD takes 16 neighbouring ones of
+    // several points at a time (full lines of J, tables shared in its L2);
+    // with fewer, whole points.
     const int64_t resident = 256 * std::max(1, std::min(per_cu, cap / nt));
     const int64_t tiles = (P + T - 1) / T;
-    qa.PP = (int)std::max<int64_t>(1, std::min<int64_t>(8, tiles * n_polys / (resident * 8)));
-    const dim3 grid((unsigned)((n_polys + qa.PP - 1) / qa.PP), (unsigned)std::min<int64_t>(tiles, 65535), 1);
-    hipError_t e = launch_quot(prec, T, qa, grid, (unsigned)nt, qlds, hs);
+    const int pp = (int)std::max<int64_t>(1, std::min<int64_t>(8, tiles * n_polys / (resident * 8)));
+    qa.blocks = (n_polys + pp - 1) / pp;
+    qa.by_point = 1;
+    if (n_polys >= 256 || tiles < 16) {
+        qa.blocks = std::max(qa.blocks, std::min(n_polys, 64));
+        qa.by_point = 0;
+    }
+    const int64_t work = qa.by_point ? (tiles + 7) / 8 * 8 * qa.blocks : tiles * ((qa.blocks + 7) / 8 * 8);
+    hipError_t e = launch_quot(prec, T, qa, dim3((unsigned)std::min<int64_t>(work, 1 << 30)), (unsigned)nt,
+                               qlds, hs);
     if (e != hipSuccess) return e;
     return launch_eval(prec, cc, maxt, a, rgrid, dim3(threads), lds, hs);
 }

@@ -80,7 +80,7 @@ static pe_status build_quot(Batch &B, const std::vector<BatchDesc> &descs, int d
     const int words = dd ? 4 : 2, ns = (int)B.sys.size();
     std::vector<QuotBatchDesc> qd((size_t)ns);
     size_t lds1 = 0, lds2 = 0;
-    int most = 0;
+    int most_m = 1, most_ranks = 1;
     ql.threads = 0;
     for (int i = 0; i < ns; ++i) {
         System &S = *B.sys[(size_t)i];
@@ -102,23 +102,17 @@ static pe_status build_quot(Batch &B, const std::vector<BatchDesc> &descs, int d
         };
         lds1 = std::max(lds1, lds(1));
         lds2 = std::max(lds2, lds(2));
-        most = std::max(most, (int)std::max<int64_t>(std::min<int64_t>(S.quot_max_m, q->CH),
-                                                     q->n_blk * kRankBlock));
+        most_m = std::max(most_m, (int)std::min<int64_t>(S.quot_max_m, q->CH));
+        most_ranks = std::max(most_ranks, q->n_blk * kRankBlock);
     }
     if (lds1 == 0) return PE_OK;
     // two buffers of values unless they cost residency
     const int nbuf = (size_t)kMaxLds / lds2 >= std::min<size_t>(4, kMaxLds / lds1) ? 2 : 1;
     ql.lds = nbuf == 2 ? lds2 : lds1;
     const int per_cu = (int)std::max<size_t>(1, kMaxLds / ql.lds);
-    int nt = 64;
-    while (nt < 1024 && nt * per_cu < 1024) nt *= 2;
-    nt = std::max(64, std::min(nt, (most * kParts + 63) / 64 * 64));
-    for (int i = 0; i < ns; ++i) {
-        QuotArgs &a = qd[(size_t)i].a;
-        if (a.CH == 0) continue;
-        a.nbuf = nbuf;
-        quot_lanes(a, (int)std::max<int64_t>(1, std::min<int64_t>(B.sys[(size_t)i]->quot_max_m, a.CH)), nt, false);
-    }
+    const int nt = quot_threads(most_m, most_ranks, ql.lds, 1024);
+    for (int i = 0; i < ns; ++i)
+        if (qd[(size_t)i].a.CH > 0) qd[(size_t)i].a.nbuf = nbuf;
     const hipError_t e = ql.desc.upload(qd.data(), qd.size() * sizeof(QuotBatchDesc));
     if (e != hipSuccess) return hip_fail(e, "uploading batch tables");
     ql.threads = nt;
@@ -131,11 +125,12 @@ static pe_status build_batch(Batch &B, const std::vector<int64_t> &pps, hipStrea
 {
     const int ns = (int)B.sys.size();
     std::vector<BatchDesc> descs((size_t)ns);
-    struct HostTask {
-        BatchTask t;
-        double cost;
+    struct PointTasks {
+        int sys, R;
+        int64_t pt;
+        double cost;  // of one task
     };
-    std::vector<HostTask> tasks;
+    std::vector<PointTasks> points;
     int64_t x_off = 0, f_off = 0, J_off = 0;
     size_t lds_max = 0;
     for (int i = 0; i < ns; ++i) {
@@ -153,35 +148,34 @@ static pe_status build_batch(Batch &B, const std::vector<int64_t> &pps, hipStrea
         f_off += pps[(size_t)i] * S.n_polys;
         J_off += pps[(size_t)i] * (int64_t)S.n_vars * S.n_polys;
         lds_max = std::max(lds_max, sc->lds_bytes(4));
-        // polynomial ranges of about task_terms derivative terms
-        std::vector<int> cut{0};
-        int64_t acc = 0;
-        for (int p = 0; p < S.n_polys; ++p) {
-            acc += S.mono_start[S.poly_start[p + 1]] - S.mono_start[S.poly_start[p]] +
-                   (S.poly_start[p + 1] - S.poly_start[p]);
-            if (acc >= B.cfg.task_terms) {
-                cut.push_back(p + 1);
-                acc = 0;
-            }
-        }
-        if (cut.back() != S.n_polys) cut.push_back(S.n_polys);
-        for (int64_t pt = 0; pt < pps[(size_t)i]; ++pt)
-            for (size_t r = 0; r + 1 < cut.size(); ++r) {
-                const int p0 = cut[r], p1 = cut[r + 1];
-                double cost = (double)S.n_vars * sc->R;  // power table
-                for (int p = p0; p < p1; ++p) {
-                    const int64_t mp = S.poly_start[p + 1] - S.poly_start[p];
-                    cost += (double)mp * (6.0 * std::max(1, S.max_k) - 5.0) + S.n_vars;
-                }
-                tasks.push_back({{i, p0, p1, 0, pt}, cost});
-            }
+        // tasks of about task_terms derivative terms: task r of R takes the
+        // polynomials r, r + R, ..., so that neighbouring polynomials, whose
+        // entries of J share cache lines, are at the same step of the R tasks
+        const int64_t terms = S.n_monos + (S.n_monos ? S.mono_start[(size_t)S.n_monos] : 0);
+        const int R = (int)std::max<int64_t>(1, std::min<int64_t>(S.n_polys, terms / B.cfg.task_terms));
+        // cost of a point's tasks
+        const double cost = ((double)S.n_vars * sc->R * R +
+                             (double)S.n_monos * (6.0 * std::max(1, S.max_k) - 5.0) +
+                             (double)S.n_vars * S.n_polys) / R;
+        for (int64_t pt = 0; pt < pps[(size_t)i]; ++pt) points.push_back({i, R, pt, cost});
     }
     if (lds_max > kMaxLds)
         return fail(PE_EUNSUPPORTED, "a system of the batch needs %zu bytes of LDS", lds_max);
-    std::stable_sort(tasks.begin(), tasks.end(),
-                     [](const HostTask &a, const HostTask &b) { return a.cost > b.cost; });
-    std::vector<BatchTask> tv(tasks.size());
-    for (size_t j = 0; j < tasks.size(); ++j) tv[j] = tasks[j].t;
+    // longest first; eight points at a time, so that the tasks of one point
+    // are eight apart in the list: workgroups eight apart share an XCD
+    std::stable_sort(points.begin(), points.end(),
+                     [](const PointTasks &a, const PointTasks &b) { return a.cost > b.cost; });
+    std::vector<BatchTask> tv;
+    for (size_t k = 0; k < points.size(); k += 8) {
+        const size_t end = std::min(points.size(), k + 8);
+        int most = 0;
+        for (size_t q = k; q < end; ++q) most = std::max(most, points[q].R);
+        for (int r = 0; r < most; ++r)
+            for (size_t q = k; q < end; ++q)
+                if (r < points[q].R)
+                    tv.push_back({points[q].sys, r, B.sys[(size_t)points[q].sys]->n_polys, points[q].R,
+                                  points[q].pt});
+    }
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(hs, &cs) == hipSuccess && cs != hipStreamCaptureStatusNone)
         return fail(PE_EUNSUPPORTED,

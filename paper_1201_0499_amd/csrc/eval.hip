@@ -159,7 +159,7 @@ eval_kernel(const EvalArgs a)
 
 // Many systems in one persistent launch: workgroup b takes the tasks
 // b, b + gridDim.x, ... of a host-ordered list (longest first); a task is one
-// point of one system and a range of its polynomials, which share the power
+// point of one system and some of its polynomials, which share the power
 // table built once for the task.
 template <class A, int CC, int MAXT>
 __global__ __launch_bounds__(MAXT) void batch_kernel(const BatchArgs b)
@@ -176,7 +176,7 @@ __global__ __launch_bounds__(MAXT) void batch_kernel(const BatchArgs b)
             const BatchTask task = b.tasks[t];
             const BatchDesc &d = b.desc[task.sys];
             const double *f = b.f[0] + d.f_off + task.pt * d.a.n_polys;
-            for (int p = task.p0; p < task.p1; ++p) any = any || is_refused(f[p]);
+            for (int p = task.p0; p < task.p1; p += task.step) any = any || is_refused(f[p]);
         }
         if (!__syncthreads_or(any)) return;
     }
@@ -192,7 +192,7 @@ __global__ __launch_bounds__(MAXT) void batch_kernel(const BatchArgs b)
         const LdsLayout<A> lds = lds_layout<A, false>(lds_raw, a);
         __syncthreads();  // the previous task is done with LDS
         bool begun = false;
-        for (int p = task.p0; p < task.p1; ++p) {
+        for (int p = task.p0; p < task.p1; p += task.step) {
             // (f of polynomial p is written only by this task, below)
             if (b.repair && !is_refused(a.f[0][task.pt * a.n_polys + p])) continue;
             const int4 g0 = a.group_info[2 * p];

@@ -66,10 +66,10 @@ struct BatchDesc {
     int64_t x_off, f_off, J_off;
 };
 
-// One task of the persistent batch kernel: point pt of system sys,
-// polynomials p0 .. p1-1.
+// One task of the persistent batch kernels: point pt of system sys,
+// polynomials p0, p0 + step, ... below p1.
 struct BatchTask {
-    int32_t sys, p0, p1, pad;
+    int32_t sys, p0, p1, step;
     int64_t pt;
 };
 

@@ -56,8 +56,8 @@ struct Quot {
     DevBuf words, coef, slice, chunk, poly, block, runs, out;
 };
 
-// lanes per monomial (of at most m in a chunk) and per run for nt threads
-void quot_lanes(QuotArgs &a, int m, int nt, bool few);
+// workgroup size of a quotient kernel: see api.cpp
+int quot_threads(int m, int ranks, size_t lds, int cap);
 
 struct System {
     int32_t n_vars = 0, n_polys = 0;

@@ -20,9 +20,9 @@
 // Bound: instruction issue (in double-double 38 FP64 instructions per factor
 // and 23 per scaled addition).  Against the general kernel's forward and
 // backward products, one MI355X: n = 512, m = 1024, k = 32, d = 5, 256 points
-// in double-double 58.1 -> 13.8 ms; n = 100, m = 200, k up to 16, 1000 points
-// in FP64 1130 -> 455 us; values only, n = 150, m = 299, k up to 12, 333
-// points in double-double 2912 -> 467 us.  Errors against 64-bit and exact
+// in double-double 58.2 -> 12.8 ms; n = 100, m = 200, k up to 16, 1000 points
+// in FP64 1130 -> 325 us; values only, n = 150, m = 299, k up to 12, 333
+// points in double-double 2912 -> 237 us.  Errors against 64-bit and exact
 // references are the same or smaller: a term now takes k products, not 2k.
 #include "quotient_body.hpp"
 
@@ -33,7 +33,13 @@ constexpr int kQuotMaxThreads = 1024;  // 128 registers per lane
 template <>
 constexpr int kQuotMaxThreads<ArithQD> = 512;  // quad-double values take eight registers per part
 
-// With the Jacobian.
+// With the Jacobian.  Work item w is a tile of T points and a block, whose
+// polynomials lie `blocks` apart: neighbouring polynomials, whose entries of J
+// share cache lines (J is polynomial-minor), are then at the same step of
+// neighbouring workgroups, and those run on one XCD (workgroup i on XCD i mod
+// 8, grid a multiple of 8), whose L2 merges the lines.  With consecutive
+// polynomials one after another in a workgroup the lines left the L2 in
+// between: at n = 512, 256 points, 11.5 GB written for 2.1 GB of J.
 template <class A>
 __global__ __launch_bounds__(kQuotMaxThreads<A>) void quot_kernel(const QuotArgs a)
 {
@@ -41,10 +47,18 @@ __global__ __launch_bounds__(kQuotMaxThreads<A>) void quot_kernel(const QuotArgs
     HIP_DYNAMIC_SHARED(double2, lds_raw)
     double2 *end;
     const QuotLds<A> lds = quot_lds<A>(lds_raw, a, end);
-    const int b = xcd_order(blockIdx.x, gridDim.x);
-    const int p0 = b * a.PP, p1 = min(a.n_polys, p0 + a.PP);
+    const int64_t tiles = (a.n_points + T - 1) / T;
+    const int per_xcd = a.by_point ? a.blocks : (a.blocks + 7) / 8;
+    const int64_t rounds = a.by_point ? (tiles + 7) / 8 : tiles;
     bool first = true;
-    for (int64_t pt = (int64_t)blockIdx.y * T; pt < a.n_points; pt += (int64_t)gridDim.y * T) {
+    for (int64_t w = blockIdx.x; w < 8 * per_xcd * rounds; w += gridDim.x) {
+        const int xcd = (int)(w & 7);
+        const int64_t round = (w >> 3) / per_xcd;
+        const int slot = (int)((w >> 3) - round * per_xcd);
+        const int64_t tile = a.by_point ? round * 8 + xcd : round;
+        const int block = a.by_point ? slot : xcd * per_xcd + slot;
+        if (tile >= tiles || block >= a.blocks) continue;
+        const int64_t pt = tile * T;
         const int npt = (int)min<int64_t>(T, a.n_points - pt);
         uint32_t live = (1u << npt) - 1;
         if (a.mask)
@@ -56,7 +70,7 @@ __global__ __launch_bounds__(kQuotMaxThreads<A>) void quot_kernel(const QuotArgs
         quot_table<A>(a, lds, pt, npt, true);
         __syncthreads();
         int vo = 0;
-        for (int p = p0; p < p1; ++p) quot_poly<A>(a, lds, pt, live, p, vo, true, [] {});
+        for (int p = block; p < a.n_polys; p += a.blocks) quot_poly<A, false>(a, lds, pt, live, p, vo, true, [] {});
     }
 }
 
@@ -106,7 +120,7 @@ __global__ __launch_bounds__(kQuotMaxThreads<A>) void quot_batch_kernel(const Qu
             a.J[q] = b.J[q] ? b.J[q] + d.J_off : nullptr;
         }
         if (a.CH == 0) {
-            for (int p = task.p0 + (int)threadIdx.x; p < task.p1; p += (int)blockDim.x)
+            for (int p = task.p0 + (int)threadIdx.x * task.step; p < task.p1; p += (int)blockDim.x * task.step)
                 a.f[0][task.pt * a.n_polys + p] = refused();
             continue;
         }
@@ -117,10 +131,10 @@ __global__ __launch_bounds__(kQuotMaxThreads<A>) void quot_batch_kernel(const Qu
         __syncthreads();
         if constexpr (JAC) {
             int vo = 0;
-            for (int p = task.p0; p < task.p1; ++p) quot_poly<A>(a, lds, task.pt, 1u, p, vo, true, [] {});
+            for (int p = task.p0; p < task.p1; p += task.step) quot_poly<A, false>(a, lds, task.pt, 1u, p, vo, true, [] {});
         } else {
             const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), nw = (int)blockDim.x >> 6;
-            for (int p = task.p0 + wave; p < task.p1; p += nw) quot_value<A>(a, lds.u, task.pt, 1u, p);
+            for (int p = task.p0 + wave * task.step; p < task.p1; p += nw * task.step) quot_value<A>(a, lds.u, task.pt, 1u, p);
         }
     }
 }

@@ -19,7 +19,11 @@ struct QuotArgs {
     int32_t multi;       // some polynomial has more than one chunk
     int32_t log2L;       // lanes per monomial: 1, 2 or 4
     int32_t log2S;       // lanes per run of terms: 1, 2 or 4
-    int32_t PP;          // polynomials per workgroup
+    int32_t PP;          // polynomials per workgroup (values only)
+    int32_t blocks;      // workgroups that share a point's polynomials: block b takes
+                         //   b, b + blocks, ...
+    int32_t by_point;    // 1: a point's workgroups run on one XCD; 0: an XCD's
+                         //   workgroups take neighbouring polynomials of every point
     int32_t nbuf;        // buffers of chunk values: 1, or 2 (one barrier per chunk)
     uint32_t x_lo, x_span;  // high words of admitted |x| parts: x_lo .. x_lo + x_span - 1
     const uint2 *words;  // see QuotTables

@@ -347,7 +347,8 @@ __device__ __forceinline__ void quot_table(const QuotArgs &a, const QuotLds<A> &
 }
 
 // Factors of one lane's monomial: the quads of words wp[0], wp[cnt], ...
-// (Q of them) in the canonical order (quotient.hpp).
+// (Q of them) in the canonical order (quotient.hpp).  Checked after every
+// product of quads: a factor there is a quad (within kQuadExp) or was checked.
 template <class A>
 struct Factors {
     using C = typename A::C;
@@ -373,7 +374,6 @@ struct Factors {
     {
         const int j0 = r * qs, j1 = min(Q, j0 + qs);
         C p = quad(wp[(int64_t)j0 * cnt]);
-        worst.see(p);
         for (int j = j0 + 1; j < j1; ++j) {
             p = A::mul(p, quad(wp[(int64_t)j * cnt]));
             worst.see(p);
@@ -390,21 +390,26 @@ struct Factors {
                 t = A::mul(t, range(2 * h + 1));
                 worst.see(t);
             }
-            prod = h == 0 ? t : A::mul(prod, t);
+            if (h == 0) {
+                prod = t;
+            } else {
+                prod = A::mul(prod, t);
+                worst.see(prod);
+            }
         }
-        worst.see(prod);
         return prod;
     }
 };
 
-// Values of the monomials of chunk ck into V at entry vo.
-template <class A>
+// Values of the monomials of chunk ck into V at entry vo, one lane per
+// monomial (ONE) or as many as the launch says.
+template <class A, bool ONE>
 __device__ __forceinline__ void chunk_values(const QuotArgs &a, const int4 &ck, const QuotLds<A> &lds, int vo)
 {
     using C = typename A::C;
     using P = Pts<A>;
     using One = typename P::One;
-    const int log2L = a.log2L, sub = (int)threadIdx.x & ((1 << log2L) - 1);
+    const int log2L = ONE ? 0 : a.log2L, sub = (int)threadIdx.x & ((1 << log2L) - 1);
     const int items = ck.y << log2L;
     // whole waves take part (lane exchanges), so the trip count is uniform
     for (int w0 = (int)threadIdx.x & ~63; w0 < items; w0 += (int)blockDim.x) {
@@ -591,9 +596,10 @@ __device__ __forceinline__ void chunk_sums(const QuotArgs &a, int ci, const int4
 }
 
 // Polynomial p at the points from pt on, of which those with their bit set in
-// live are written; vo is the buffer in use (it alternates).  on_refused: see
-// quot_store.
-template <class A, class Refused>
+// live are written; vo is the buffer in use (it alternates).  FEW: lanes per
+// monomial and per run as the launch says (calls of few workgroups); else one
+// lane per monomial and two per run.  on_refused: see quot_store.
+template <class A, bool FEW, class Refused>
 __device__ __forceinline__ void quot_poly(const QuotArgs &a, const QuotLds<A> &lds, int64_t pt, uint32_t live,
                                           int p, int &vo, bool jac, const Refused &on_refused)
 {
@@ -604,7 +610,7 @@ __device__ __forceinline__ void quot_poly(const QuotArgs &a, const QuotLds<A> &l
     const int4 pl = a.poly[p];
     for (int c = pl.x; c < pl.y; ++c) {
         const int4 ck = a.chunk[c];
-        chunk_values<A>(a, ck, lds, vo);
+        chunk_values<A, !FEW>(a, ck, lds, vo);
         __syncthreads();
         const bool first = c == pl.x, last = c + 1 == pl.y;
         auto put = [&](int o, C v) {
@@ -619,10 +625,10 @@ __device__ __forceinline__ void quot_poly(const QuotArgs &a, const QuotLds<A> &l
             if (o != n) v = A::mul(lds.y.get(o), v);
             quot_store<A>(a, pt, live, p, o, v, on_refused);
         };
-        if (a.log2S == 0)
-            chunk_sums<A, 4>(a, c, ck, lds, vo, jac, put);
-        else if (a.log2S == 1)
+        if (!FEW || a.log2S == 1)
             chunk_sums<A, 2>(a, c, ck, lds, vo, jac, put);
+        else if (a.log2S == 0)
+            chunk_sums<A, 4>(a, c, ck, lds, vo, jac, put);
         else
             chunk_sums<A, 1>(a, c, ck, lds, vo, jac, put);
         // with two buffers the next item writes the other one; it comes back

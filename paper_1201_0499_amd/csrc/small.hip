@@ -30,7 +30,7 @@ small_kernel(const EvalArgs a, const QuotArgs qa)
         quot_table<A>(qa, lds, pt, 1, jac);
         __syncthreads();
         int vo = 0;
-        quot_poly<A>(qa, lds, pt, 1u, p, vo, jac, [&] { *flag = 1; });
+        quot_poly<A, true>(qa, lds, pt, 1u, p, vo, jac, [&] { *flag = 1; });
         __syncthreads();
         if (*flag == 0) return;
         __syncthreads();  // the flag has been read
