@@ -17,7 +17,7 @@ import os
 
 import numpy as np
 
-from ._abi import (PE_DD, PE_FP64, PE_NEWTON_DD, PE_NEWTON_MIXED, PolyevalError, cvec,
+from ._abi import (PE_DD, PE_FP64, PE_NEWTON_DD, PE_NEWTON_MIXED, PolyevalError, cvec, pe_cvec,
                    check, lib, LIB_PATH,
                    pe_track_params)
 
@@ -68,26 +68,50 @@ def system_info(handle):
                 max_exp=me.value)
 
 
+_NO_PLANES = pe_cvec()
+_FLOAT64 = None  # torch.float64, once torch has been imported
+
+
 def _dev_planes(planes, required_lo: bool):
+    global _FLOAT64
     if planes is None:
-        return cvec([0, 0, 0, 0])
+        return _NO_PLANES
+    if _FLOAT64 is None:
+        import torch
+        _FLOAT64 = torch.float64
     ptrs = []
     for j, t in enumerate(planes):
         if t is None:
             if required_lo or j in (0, 2):
                 raise ValueError("missing plane")
-            ptrs.append(0)
+            ptrs.append(None)
             continue
-        if not t.is_cuda or t.dtype.__str__() != "torch.float64" or not t.is_contiguous():
+        if not t.is_cuda or t.dtype != _FLOAT64 or not t.is_contiguous():
             raise ValueError("planes must be contiguous float64 CUDA tensors")
         ptrs.append(t.data_ptr())
-    return cvec(ptrs)
+    return pe_cvec(*ptrs)
+
+
+_RAW_STREAM = None  # () -> hipStream_t of torch's current stream, as an int
+
+
+def _raw_stream():
+    """The current stream without building a Stream object, where this torch
+    offers that."""
+    import torch
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    if raw is None:
+        return lambda: torch.cuda.current_stream().cuda_stream
+    current_device = torch.cuda.current_device
+    return lambda: raw(current_device())
 
 
 def _stream(stream):
+    global _RAW_STREAM
     if stream is None:
-        import torch
-        return torch.cuda.current_stream().cuda_stream
+        if _RAW_STREAM is None:
+            _RAW_STREAM = _raw_stream()
+        return _RAW_STREAM()
     return stream if isinstance(stream, int) else stream.cuda_stream
 
 
@@ -95,18 +119,20 @@ def eval_jac(handle, n_points, points, out_f, out_J=None, precision=PE_DD, strea
     """``pe_eval_jac`` on device tensors: points ``[P][n]``, out_f
     ``[P][n_polys]``, out_J ``[P][n][n_polys]`` (or None)."""
     dd = precision == PE_DD
-    check(lib().pe_eval_jac(C.c_void_p(handle), int(n_points), _dev_planes(points, dd),
-                            _dev_planes(out_f, dd), _dev_planes(out_J, dd), int(precision),
-                            C.c_void_p(_stream(stream))), "pe_eval_jac")
+    status = lib().pe_eval_jac(handle, int(n_points), _dev_planes(points, dd), _dev_planes(out_f, dd),
+                               _dev_planes(out_J, dd), int(precision), _stream(stream))
+    if status:
+        check(status, "pe_eval_jac")
 
 
 def eval_jac_noalloc(handle, n_points, points, out_f, out_J=None, precision=PE_DD, stream=None):
     """``pe_eval_jac_noalloc``: as eval_jac, allocating nothing (the schedule's
     tables must exist: call eval_jac once with n_points first)."""
     dd = precision == PE_DD
-    check(lib().pe_eval_jac_noalloc(C.c_void_p(handle), int(n_points), _dev_planes(points, dd),
-                                    _dev_planes(out_f, dd), _dev_planes(out_J, dd), int(precision),
-                                    C.c_void_p(_stream(stream))), "pe_eval_jac_noalloc")
+    status = lib().pe_eval_jac_noalloc(handle, int(n_points), _dev_planes(points, dd), _dev_planes(out_f, dd),
+                                       _dev_planes(out_J, dd), int(precision), _stream(stream))
+    if status:
+        check(status, "pe_eval_jac_noalloc")
 
 
 def _plane8(tensors):
@@ -114,7 +140,7 @@ def _plane8(tensors):
         return None
     if len(tensors) != 8:
         raise ValueError("quad-double values need 8 planes")
-    arr = (C.c_void_p * 8)(*[C.c_void_p(t.data_ptr()) for t in tensors])
+    arr = (C.c_void_p * 8)(*[t.data_ptr() for t in tensors])
     return C.cast(arr, C.POINTER(C.c_void_p)), arr
 
 
