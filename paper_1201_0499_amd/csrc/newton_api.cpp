@@ -149,7 +149,11 @@ static pe_status newton_core(System *S, int64_t n_starts, double *const *x, int 
             return hip_fail(e, "reading the running count");
         if (running == 0) break;
         if (mixed) {
-            st = S->eval_locked(n_starts, xview, fp64, Jp, false, hs, status_out, false, quotients);
+            // In quad-double the steps past the second gain only what the
+            // Jacobian's FP64 rounding errors leave (the residuals are those
+            // errors), so the iteration counts depend on them: there the
+            // Jacobian stays the general kernel's, bit for bit.
+            st = S->eval_locked(n_starts, xview, fp64, Jp, false, hs, status_out, false, quotients && !qd);
             if (st != PE_OK) return st;
             if ((e = launch_lu_solve(0, n_starts, n, Jp, rview, dp, status_out, hs)) != hipSuccess)
                 return hip_fail(e, "FP64 solve");
