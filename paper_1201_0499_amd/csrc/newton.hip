@@ -1088,6 +1088,166 @@ __global__ __launch_bounds__((NCOL / CPT) * 64) void gj_panel_kernel(int64_t n_s
     }
 }
 
+// Gauss-Jordan elimination with partial pivoting in complex double-double, the
+// matrix and the right-hand side (column n) in the registers of eight waves:
+// wave w holds columns w, w + 8, ..., lane q of it rows q and (RPT = 2)
+// q + 64.  One workgroup takes a start, so that few starts leave a SIMD with
+// two waves; the blocked kernel, whose matrix lives in global memory, gives it
+// one and a serial chain through memory at every panel.  Step k:
+//   * the wave that holds column k has found the pivot (the largest |re| +
+//     |im| of the rows not yet pivoted, the smallest row on ties) and written
+//     the multipliers l_r = a_rk / a_pk (l_p = 0) to LDS;
+//   * after one barrier every wave subtracts l_r a_pc in its columns right of
+//     k, a_pc by readlane; the wave that holds column k + 1 updates that one
+//     first, and looks for its pivot (the serial part) while the others update
+//     the rest: the multipliers alternate between two buffers, and no wave
+//     reads step k + 1's before the barrier that follows their writing.
+// Columns are dealt round, so every wave has as many left as the others.  Rows
+// never move; x_k = b_p / a_pk, p the pivot row of column k.  n < 8 CPT, and
+// n <= 64 RPT.  Bound: FP64 issue, with one or two workgroups on a CU (the
+// matrix takes up to 208 of a lane's 256 registers).  Blocked -> here, one
+// MI355X: n = 103, 256 starts 1447 -> 627 us, 1024 starts 4342 -> 2497 us; n =
+// 63, 1024 starts 1583 -> 488 us.
+template <int RPT, int CPT>
+__global__ __launch_bounds__(512) void gj_dd_kernel(int64_t n_starts, int32_t n, LuPlanes planes,
+                                                    int32_t *status)
+{
+    using A = ArithDD;
+    using C = A::C;
+    static_assert(RPT <= 2, "row slots");
+    __shared__ double2 s_l[2][2 * 64 * RPT];  // multipliers of a step (two planes)
+    __shared__ double2 s_inv[2 * 8 * CPT];    // 1 / pivot of each column
+    __shared__ int s_piv[8 * CPT];            // pivot row of each column, -1: none
+    const int64_t st = blockIdx.x;
+    if (status[st] != kRunning) return;
+    const int tid = threadIdx.x, q = tid & 63;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    double2 *next;
+    const LdsVec<A> inv_of = LdsVec<A>::at(s_inv, 8 * CPT, next);
+    const Mat<A> M = make_mat<A>(planes.J, st * (int64_t)n * n);
+    C a[RPT][CPT];
+#pragma unroll
+    for (int j = 0; j < CPT; ++j) {
+        const int c = w + 8 * j;
+#pragma unroll
+        for (int i = 0; i < RPT; ++i) {
+            const int r = q + 64 * i;
+            a[i][j] = A::zero();
+            if (r < n && c < n) a[i][j] = M.get((int64_t)c * n + r);
+            if (r < n && c == n) a[i][j] = Io<A>::load(planes.r, st * (int64_t)n + r);
+        }
+    }
+    uint32_t done = 0;  // bit i: row q + 64 i already pivoted (or past n)
+    int col[RPT];       // the column it was the pivot of
+#pragma unroll
+    for (int i = 0; i < RPT; ++i) {
+        col[i] = -1;
+        if (q + 64 * i >= n) done |= 1u << i;
+    }
+    // column j of this wave, number k: its pivot and multipliers
+    auto factor = [&](const C (&v)[RPT], int k) {
+        double m[RPT], gm = -1.0;
+#pragma unroll
+        for (int i = 0; i < RPT; ++i) {
+            m[i] = ((done >> i) & 1u) ? -1.0 : A::mag(v[i]);
+            if (!(m[i] >= 0.0)) m[i] = -1.0;
+            gm = fmax(gm, m[i]);
+        }
+        gm = max_step<1>(gm);
+        gm = max_step<2>(gm);
+        gm = max_step<4>(gm);
+        gm = max_step<8>(gm);
+        gm = max_step<16>(gm);
+        gm = max_step<32>(gm);
+        const unsigned long long at0 = __ballot(m[0] == gm);
+        const unsigned long long at1 = RPT > 1 ? __ballot(m[RPT - 1] == gm) : 0;
+        const bool low = RPT == 1 || at0 != 0;
+        const int qp = __ffsll(low ? at0 : at1) - 1;
+        const bool ok = __builtin_amdgcn_readfirstlane((int)(gm > 0.0 && isfinite(gm))) != 0;
+        const int p = ok ? qp + (low ? 0 : 64) : -1;
+        if (q == 0) s_piv[k] = p;
+        if (!ok) return;
+        const C piv = low ? read_lane_c(v[0], qp) : read_lane_c(v[RPT - 1], qp);
+        const C inv = A::inv(piv);
+        if (q == 0) inv_of.put(k, inv);
+        const LdsVec<A> l = LdsVec<A>::at(s_l[k & 1], 64 * RPT, next);
+#pragma unroll
+        for (int i = 0; i < RPT; ++i) {
+            const int r = q + 64 * i;
+            l.put(r, r == p ? A::zero() : A::neg(A::mul(v[i], inv)));
+        }
+    };
+    // slot j of this wave's columns: step k's update, multipliers from LDS
+    auto update = [&](int j, const LdsVec<A> &l, int p) {
+        asm volatile("" ::: "memory");
+        C u;
+        if (RPT == 1 || p < 64) {
+            u = read_lane_c(a[0][j], p & 63);
+        } else {
+            asm volatile("" ::: "memory");
+            u = read_lane_c(a[RPT - 1][j], p & 63);
+        }
+#pragma unroll
+        for (int i = 0; i < RPT; ++i) a[i][j] = A::add(a[i][j], A::mul(l.get(q + 64 * i), u));
+    };
+    auto pivots = [&](int j, int k) {
+        C v[RPT];
+#pragma unroll
+        for (int i = 0; i < RPT; ++i) v[i] = a[i][j];
+        factor(v, k);
+    };
+    if (w == 0) pivots(0, 0);
+    // steps 8 J ... of the columns in slot J; one copy per slot, as registers
+    // have no index (shifting the slots instead doubles the registers)
+    auto block = [&](auto slot, auto &&self) -> void {
+        constexpr int J = decltype(slot)::value;
+        const int last = min(8, n - 8 * J);
+        for (int s = 0; s < last; ++s) {
+            const int k = 8 * J + s;
+            __syncthreads();
+            const int p = __builtin_amdgcn_readfirstlane(s_piv[k]);
+            if (p < 0) {
+                if (tid == 0) status[st] = 2;
+                return;
+            }
+            const LdsVec<A> l = LdsVec<A>::at(s_l[k & 1], 64 * RPT, next);
+#pragma unroll
+            for (int i = 0; i < RPT; ++i)
+                if (q + 64 * i == p) {
+                    done |= 1u << i;
+                    col[i] = k;
+                }
+            const bool serial = w == ((s + 1) & 7) && k + 1 < n;  // holds column k + 1
+            if (serial) __builtin_amdgcn_s_setprio(3);
+            if (w > s && w + 8 * J <= n) {
+                update(J, l, p);
+                if (serial) pivots(J, k + 1);
+            }
+            if constexpr (J + 1 < CPT) {
+                if (w + 8 * (J + 1) <= n) {
+                    update(J + 1, l, p);
+                    if (s == 7 && serial) pivots(J + 1, k + 1);
+                }
+            }
+            if (serial) __builtin_amdgcn_s_setprio(0);
+#pragma unroll
+            for (int j = J + 2; j < CPT; ++j)
+                if (w + 8 * j <= n) update(j, l, p);
+        }
+        if (last < 8) {
+            // the right-hand side, column n, is in this slot of wave n mod 8
+            if (w != (n & 7)) return;
+            const Mat<A> d = make_mat<A>(planes.d, st * (int64_t)n);
+#pragma unroll
+            for (int i = 0; i < RPT; ++i)
+                if (col[i] >= 0) d.put(col[i], A::mul(a[i][J], inv_of.get(col[i])));
+        } else if constexpr (J + 1 < CPT) {
+            self(std::integral_constant<int, J + 1>{}, self);
+        }
+    };
+    block(std::integral_constant<int, 0>{}, block);
+}
+
 // Panel width: 16 columns in FP64 and 8 in double-double, or fewer when
 // the panel (width x n complex values) and the kernel's static arrays would
 // not fit in LDS; 0 if none fits.
@@ -1156,6 +1316,17 @@ hipError_t launch_lu_solve(int prec, int64_t n_starts, int32_t n, double *const 
         pl.J[q] = J[q];
         pl.r[q] = r[q];
         pl.d[q] = d[q];
+    }
+    if (prec == 1 && n <= 103) {
+        // as many columns as the registers hold; the register kernel is the
+        // faster one at every number of starts (64 to 1024 measured)
+        if (n <= 63)
+            hipLaunchKernelGGL((gj_dd_kernel<1, 8>), dim3((unsigned)n_starts), dim3(512), 0, stream,
+                               n_starts, n, pl, status);
+        else
+            hipLaunchKernelGGL((gj_dd_kernel<2, 13>), dim3((unsigned)n_starts), dim3(512), 0,
+                               stream, n_starts, n, pl, status);
+        return hipGetLastError();
     }
     const size_t lds = (prec == 0 ? sizeof(Arith64::C) : sizeof(ArithDD::C)) * (size_t)nb * n;
     void *args[] = {&n_starts, &n, &pl, &status};
