@@ -111,8 +111,8 @@ __global__ __launch_bounds__(kQuotMaxThreads<A>) void quot_batch_kernel(const Qu
 {
     HIP_DYNAMIC_SHARED(double2, lds_raw)
     for (int64_t t = blockIdx.x; t < b.n_tasks; t += gridDim.x) {
-        const BatchTask task = b.tasks[t];
-        const QuotBatchDesc &d = b.desc[task.sys];
+        const BatchTask task = uniform_struct(b.tasks + t);
+        const QuotBatchDesc d = uniform_struct(b.desc + task.sys);
         QuotArgs a = d.a;
         for (int q = 0; q < 4; ++q) {
             a.x[q] = b.x[q] ? b.x[q] + d.x_off : nullptr;

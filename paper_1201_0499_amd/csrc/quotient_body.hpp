@@ -15,6 +15,38 @@
 
 namespace pe {
 
+// Entry of a table that no kernel writes, at an address that is the same on
+// every lane: read through the scalar cache into scalar registers.  Read as
+// ordinary memory, which the kernel's stores might change, it would sit in a
+// vector register of every lane.
+__device__ __forceinline__ int4 uniform_int4(const int4 *p)
+{
+    typedef int V __attribute__((ext_vector_type(4)));
+    const V v = *(const __attribute__((address_space(4))) V *)p;
+    return make_int4(v.x, v.y, v.z, v.w);
+}
+
+__device__ __forceinline__ int2 uniform_int2(const int2 *p)
+{
+    typedef int V __attribute__((ext_vector_type(2)));
+    const V v = *(const __attribute__((address_space(4))) V *)p;
+    return make_int2(v.x, v.y);
+}
+
+// A whole structure of such memory, of 4-byte words.
+template <class S>
+__device__ __forceinline__ S uniform_struct(const S *p)
+{
+    static_assert(sizeof(S) % 4 == 0, "words");
+    const auto *src = (const __attribute__((address_space(4))) uint32_t *)p;
+    uint32_t w[sizeof(S) / 4];
+#pragma unroll
+    for (size_t i = 0; i < sizeof(S) / 4; ++i) w[i] = src[i];
+    S s;
+    __builtin_memcpy(&s, w, sizeof(S));
+    return s;
+}
+
 // ---------------------------------------------------------------------------
 // T points in FP64
 // ---------------------------------------------------------------------------
@@ -416,7 +448,7 @@ __device__ __forceinline__ void chunk_values(const QuotArgs &a, const int4 &ck, 
         const int s = (w0 + ((int)threadIdx.x & 63)) >> log2L;
         const bool on = s < ck.y;
         const int sl = __builtin_amdgcn_readfirstlane(s >> 6);
-        const int2 sh = a.slice[ck.z + sl];
+        const int2 sh = uniform_int2(a.slice + ck.z + sl);
         Worst<A> worst;
         const Factors<A> fac(lds.u, a.words + (int64_t)sh.x + (on ? s - 64 * sl : 0), min(64, ck.y - 64 * sl),
                              sh.y, worst);
@@ -499,14 +531,14 @@ __device__ __forceinline__ void quot_value(const QuotArgs &a, const LdsVec<A> &u
     using P = Pts<A>;
     using One = typename P::One;
     const int lane = (int)threadIdx.x & 63;
-    const int4 pl = a.poly[p];
+    const int4 pl = uniform_int4(a.poly + p);
     C f = pl.z > 0 ? P::all(Io<One>::coef(a.sys_coef, pl.z - 1)) : A::zero();
     for (int c = pl.x; c < pl.y; ++c) {
-        const int4 ck = a.chunk[c];
+        const int4 ck = uniform_int4(a.chunk + c);
         RunAcc<A> acc;
         acc.clear();
         for (int sl = 0; 64 * sl < ck.y; ++sl) {
-            const int2 sh = a.slice[ck.z + sl];
+            const int2 sh = uniform_int2(a.slice + ck.z + sl);
             const int cnt = min(64, ck.y - 64 * sl);
             if (lane >= cnt) break;  // the chunk's last slice
             Worst<A> worst;
@@ -607,9 +639,9 @@ __device__ __forceinline__ void quot_poly(const QuotArgs &a, const QuotLds<A> &l
     using P = Pts<A>;
     using One = typename P::One;
     const int n = a.n_vars;
-    const int4 pl = a.poly[p];
+    const int4 pl = uniform_int4(a.poly + p);
     for (int c = pl.x; c < pl.y; ++c) {
-        const int4 ck = a.chunk[c];
+        const int4 ck = uniform_int4(a.chunk + c);
         chunk_values<A, !FEW>(a, ck, lds, vo);
         __syncthreads();
         const bool first = c == pl.x, last = c + 1 == pl.y;
