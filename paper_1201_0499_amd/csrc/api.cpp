@@ -309,48 +309,58 @@ void System::fill_args(const Schedule &sc, EvalArgs &a) const
 }
 
 // Tables of the quotient kernels, packed and uploaded once per chunk size.
-pe_status System::quot_for(int words, bool find_only, Quot **out)
+// nullptr leaves the call to the general kernel: also while hs is being
+// captured, when nothing may be uploaded, and if memory for them runs out.
+Quot *System::quot_for(int words, bool find_only, hipStream_t hs)
 {
-    *out = nullptr;
-    if (!quot_ok) return PE_OK;
+    if (!quot_ok) return nullptr;
     const int CH = quot_chunk(n_vars, max_exp, quot_pad, quot_max_m, words);
-    if (CH == 0) return PE_OK;
+    if (CH == 0) return nullptr;
     for (auto &q : quots)
-        if (q->CH == CH) {
-            *out = q.get();
-            return PE_OK;
-        }
-    if (find_only) return PE_OK;
-    QuotTables t;
-    t.CH = CH;
-    t.pad = quot_pad;
-    CsrView v{n_vars, n_polys, n_monos, poly_start.data(), mono_start.data(), pos.data(), exp.data()};
-    if (!build_quot_tables(v, t).empty()) {
-        quot_ok = false;  // outside the packing: the general kernel serves
-        return PE_OK;
+        if (q->CH == CH) return q.get();
+    if (find_only) return nullptr;
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(hs, &cs) != hipSuccess) {
+        (void)hipGetLastError();
+        return nullptr;
     }
-    std::vector<double> c(t.mono.size() * 4);
-    for (size_t i = 0; i < t.mono.size(); ++i)
-        std::copy_n(coef_host.data() + 4 * (size_t)t.mono[i], 4, c.data() + 4 * i);
-    std::unique_ptr<Quot> q(new Quot());
-    q->CH = CH;
-    q->n_blk = t.n_blk;
-    q->multi = t.multi;
-    hipError_t e = q->coef.upload(c.data(), c.size() * sizeof(double));
+    if (cs != hipStreamCaptureStatusNone) return nullptr;
+    try {
+        QuotTables t;
+        t.CH = CH;
+        t.pad = quot_pad;
+        CsrView v{n_vars, n_polys, n_monos, poly_start.data(), mono_start.data(), pos.data(), exp.data()};
+        if (!build_quot_tables(v, t).empty()) {
+            quot_ok = false;  // outside the packing: the general kernel serves
+            return nullptr;
+        }
+        std::vector<double> c(t.mono.size() * 4);
+        for (size_t i = 0; i < t.mono.size(); ++i)
+            std::copy_n(coef_host.data() + 4 * (size_t)t.mono[i], 4, c.data() + 4 * i);
+        std::unique_ptr<Quot> q(new Quot());
+        q->CH = CH;
+        q->n_blk = t.n_blk;
+        q->multi = t.multi;
+        hipError_t e = q->coef.upload(c.data(), c.size() * sizeof(double));
 #define PE_UP(buf)                                                          \
     if (e == hipSuccess) e = q->buf.upload(t.buf.data(), t.buf.size() * sizeof(t.buf[0]));
-    PE_UP(words)
-    PE_UP(slice)
-    PE_UP(chunk)
-    PE_UP(poly)
-    PE_UP(block)
-    PE_UP(runs)
-    PE_UP(out)
+        PE_UP(words)
+        PE_UP(slice)
+        PE_UP(chunk)
+        PE_UP(poly)
+        PE_UP(block)
+        PE_UP(runs)
+        PE_UP(out)
 #undef PE_UP
-    if (e != hipSuccess) return hip_fail(e, "uploading the quotient tables");
-    *out = q.get();
-    quots.push_back(std::move(q));
-    return PE_OK;
+        if (e != hipSuccess) {
+            (void)hipGetLastError();
+            return nullptr;
+        }
+        quots.push_back(std::move(q));
+        return quots.back().get();
+    } catch (const std::bad_alloc &) {
+        return nullptr;
+    }
 }
 
 void System::fill_quot(const Quot &q, QuotArgs &a) const
@@ -388,16 +398,50 @@ static void few_lanes(QuotArgs &a, int m, int nt)
     a.log2S = ranks * 4 <= nt ? 2 : (ranks * 2 <= nt ? 1 : 0);
 }
 
-// Workgroup size of the other calls, with one lane per monomial and two per
-// run, whose reads of the values the packer spread over the LDS banks: the
-// smallest that fills the CU's registers (cap threads) with the workgroups
-// its LDS holds, no larger than one round of lanes can use.
-int quot_threads(int m, int ranks, size_t lds, int cap)
+// Lanes that a workgroup of the other calls can use: one per monomial and two
+// per run, whose reads of the values the packer spread over the LDS banks.
+// Runs of fewer than four terms on average are mostly latency, which more
+// workgroups hide better than more lanes: then 256 are enough (n = 292, m =
+// 37, k = 15, 2 points in double-double: 20 us at 512 lanes, 15.7 us).
+int System::quot_lanes(const Quot &q) const
 {
-    const int per_cu = (int)std::max<size_t>(1, kMaxLds / lds);
+    const int m = (int)std::max<int64_t>(1, std::min<int64_t>(quot_max_m, q.CH));
+    const int sums = q.n_blk * kRankBlock * 2;
+    return std::max(m, quot_max_m * max_k >= 4 * (int64_t)n_vars ? sums : std::min(sums, 256));
+}
+
+// Workgroup size: the smallest that fills the CU's registers (cap threads)
+// with the workgroups that its LDS holds or, if fewer, that there are.
+int quot_threads(int lanes, size_t lds, int64_t workgroups, int cap)
+{
+    const int64_t per_cu =
+        std::max<int64_t>(1, std::min<int64_t>((int64_t)(kMaxLds / lds), (workgroups + 255) / 256));
     int nt = 64;
     while (nt < cap && nt * per_cu < cap) nt *= 2;
-    return std::min(nt, (std::max(m, ranks * 2) + 63) / 64 * 64);
+    return std::min(nt, (lanes + 63) / 64 * 64);
+}
+
+// Whether the Jacobian's runs are too long for the quotient kernels: a few
+// lanes then add one long run each while the others wait, and the general
+// kernel, whose lanes share the terms evenly, is the faster one.  One MI355X,
+// general against quotients:
+//   FP64: n = 8, m = 1000, k = 8, 512 points 91 and 174 us; n = 16, k = 16,
+//     one point 24 and 37 us; but n = 32 and one point 14 and 13 us;
+//   double-double: n = 8, m = 1000, k = 8, 512 points 315 and 547 us; but m =
+//     256 92 and 79 us, and n = 16, k = 16, 32 points 241 and 89 us;
+//   quad-double: n = 8, m = 1000, k = 8, 512 points 5660 and 4780 us.
+// mono: monomials that a workgroup of a small call (0: none) takes at once;
+// if they make up the polynomial, the general kernel is as short a chain:
+// n = 16, m = 256, k = 16, one point in double-double 15.3 and 17.1 us, in
+// quad-double 63 and 71 us; n = 32, m = 256, k = 8, 32 points in FP64 12.6 and
+// 13.7 us.  The same with and without the Jacobian, so that
+// both give the same values bit for bit.
+bool System::long_runs(int words, int64_t mono) const
+{
+    const int64_t run = quot_max_m * (int64_t)max_k / std::max(1, n_vars);
+    if (quot_max_m <= mono && (words == 2 ? run >= 64 && n_vars <= 32 : run > 192 && n_vars < 18)) return true;
+    if (words == 2) return run > 64 && n_vars < 24;
+    return words == 4 && run > 64 && n_vars < 12 && quot_max_m > 512;
 }
 
 hipError_t System::run_values(const Quot &q, int prec, QuotArgs qa, hipStream_t hs) const
@@ -440,7 +484,8 @@ hipError_t System::run_quot(const Quot &q, int prec, int cc, int maxt, EvalArgs 
         qa.J[p] = a.J[p];
     }
     qa.mask = a.mask;
-    // the general kernel takes whole polynomials
+    // the general kernel takes whole polynomials, one point at a time
+    a.T = a.nbuf = 1;
     a.repair = 1;
     a.merge = a.G;
     a.G = 1;
@@ -450,13 +495,13 @@ hipError_t System::run_quot(const Quot &q, int prec, int cc, int maxt, EvalArgs 
     const auto lds_for = [&](int T, int nbuf) {
         return quot_lds_bytes(n_vars, max_exp, quot_pad, q.CH, q.multi, nbuf, T * words);
     };
-    if (units <= kSmallUnits && a.T == 1 && a.nbuf == 1) {
+    if (units <= kSmallUnits) {
         few_lanes(qa, m, (int)threads);
         return launch_small(prec, cc, maxt, a, qa, dim3((unsigned)n_polys, (unsigned)P, 1), threads,
                             std::max(lds, lds_for(1, 1) + 16), hs);
     }
     // few workgroups, so that looking for work costs little when there is none
-    const int64_t gy = std::min<int64_t>((P + a.T - 1) / a.T, std::max<int64_t>(1, 2048 / n_polys));
+    const int64_t gy = std::min<int64_t>(P, std::max<int64_t>(1, 2048 / n_polys));
     const dim3 rgrid((unsigned)n_polys, (unsigned)gy, 1);
     if (!jac) {
         hipError_t e = run_values(q, prec, qa, hs);
@@ -464,19 +509,26 @@ hipError_t System::run_quot(const Quot &q, int prec, int cc, int maxt, EvalArgs 
         return launch_eval(prec, cc, maxt, a, rgrid, dim3(threads), lds, hs);
     }
     const int cap = prec == 2 ? 512 : 1024;  // threads a CU's registers hold (and a workgroup's limit)
-    const int T = prec == 0 && P >= kPointsF64 && lds_for(kPointsF64, 1) <= (size_t)kMaxLds ? kPointsF64 : 1;
+    // two points share the table reads of a workgroup, if its LDS leaves four
+    // on a CU (n = 400, m = 600, k = 24, 128 points: 1118 us with two points
+    // and two workgroups, 983 us with one point)
+    const int T = prec == 0 && P >= kPointsF64 && lds_for(kPointsF64, 1) * 4 <= (size_t)kMaxLds ? kPointsF64 : 1;
+    const int64_t tiles = (P + T - 1) / T;
     if (lds_for(T, 2) <= (size_t)kMaxLds) qa.nbuf = 2;
     const size_t qlds = lds_for(T, qa.nbuf);
     const int per_cu = (int)std::max<size_t>(1, kMaxLds / qlds);
-    const int nt = quot_threads(m, q.n_blk * kRankBlock, qlds, cap);
+    const int nt = quot_threads(quot_lanes(q), qlds, tiles * n_polys, cap);
     // several polynomials per workgroup share one power table, while the
     // workgroups still make eight rounds of the chip.  With at least 128
     // workgroups' worth of polynomials each XCD takes 16 neighbouring ones of
     // several points at a time (full lines of J, tables shared in its L2);
     // with fewer, whole points.
     const int64_t resident = 256 * std::max(1, std::min(per_cu, cap / nt));
-    const int64_t tiles = (P + T - 1) / T;
-    const int pp = (int)std::max<int64_t>(1, std::min<int64_t>(8, tiles * n_polys / (resident * 8)));
+    int pp = (int)std::max<int64_t>(1, std::min<int64_t>(8, tiles * n_polys / (resident * 8)));
+    // Fewer factors than entries of J: the stores bound it, so that whole
+    // lines of J at a time count for more than the power table (n = 507, m =
+    // 22, k = 4, 261 points in FP64: 1390 us with 8, 800 us with 1).
+    if (prec == 0 && m * (int64_t)max_k < n_vars) pp = 1;
     qa.blocks = (n_polys + pp - 1) / pp;
     qa.by_point = 1;
     if (n_polys >= 256 || tiles < 16) {
@@ -562,10 +614,11 @@ pe_status System::eval_locked(int64_t n_points, const double *const x[4], double
     }
     const int maxt = sc->nt <= 256 ? 256 : (sc->nt <= 512 ? 512 : 1024);
     Quot *quot = nullptr;
-    if (quotients) st = quot_for(words, no_alloc, &quot);
-    if (st != PE_OK) return st;
+    const int64_t mono = n_points * n_polys <= kSmallUnits ? (int64_t)sc->MC * sc->G : 0;
+    if (quotients && !long_runs(words, mono)) quot = quot_for(words, no_alloc, hs);
     if (quot) {
-        hipError_t e = run_quot(*quot, dd ? 1 : 0, sc->cc, maxt, a, (unsigned)sc->nt, lds, hs);
+        hipError_t e = run_quot(*quot, dd ? 1 : 0, sc->cc, maxt, a, (unsigned)sc->nt,
+                                sc->lds_bytes(words), hs);
         if (e != hipSuccess) return hip_fail(e, "launching the evaluation by quotients");
         return PE_OK;
     }
@@ -778,13 +831,13 @@ pe_status pe_get_schedule(pe_system sys, int64_t n_points, int32_t *lanes, int32
     if (groups) *groups = G;
     if (tile_points || stage_buffers) {
         // the tile shape depends on the schedule's tables (their LDS size)
-        Schedule *sc = nullptr;
+        Schedule *had = nullptr, *sc = nullptr;
+        (void)S->find_schedule(n_points, &had);
         pe_status st = S->schedule_for(n_points, &sc);
         if (st != PE_OK) return st;
         int T = 1, nbuf = 1;
         S->launch_shape(*sc, n_points, true, T, nbuf);
-        Quot *quot = nullptr;  // packed with them
-        if ((st = S->quot_for(4, false, &quot)) != PE_OK) return st;
+        if (!had) (void)S->quot_for(4, false, nullptr);  // packed with them
         if (tile_points) *tile_points = T;
         if (stage_buffers) *stage_buffers = nbuf;
     }
@@ -920,10 +973,8 @@ pe_status pe_eval_jac_qd(pe_system sys, int64_t n_points, const double *const *p
         }
         a.partial = (double *)S->partial.ptr;
     }
-    Quot *quot = nullptr;
-    st = S->quot_for(8, false, &quot);
-    if (st != PE_OK) return st;
-    if (quot) {
+    const int64_t mono = pairs <= kSmallUnits ? (int64_t)sc->MC * sc->G : 0;
+    if (Quot *quot = S->long_runs(8, mono) ? nullptr : S->quot_for(8, false, hs)) {
         hipError_t e = S->run_quot(*quot, 2, cc, nt, a, (unsigned)nt, lds, hs);
         if (e != hipSuccess) return hip_fail(e, "launching the quad-double evaluation by quotients");
         return PE_OK;

@@ -56,10 +56,11 @@ struct Batch {
     int grid = 0;
     DevBuf desc, tasks;
     // the quotient kernel's launch for each precision (0 = FP64, 1 = double-
-    // double): descriptors, workgroup size, LDS and grid; threads 0 if no
-    // system of the batch is within those kernels
+    // double): descriptors, tasks, workgroup size, LDS and grid; threads 0 if
+    // no system of the batch is within those kernels
     struct QuotLaunch {
-        DevBuf desc;
+        DevBuf desc, tasks;
+        int64_t n_tasks = 0;
         int threads = 0, grid = 0;
         size_t lds = 0;
     } quot[2];
@@ -72,15 +73,55 @@ static int lanes_for(int k, const BatchConfig &c)
     return std::min(L, 32);
 }
 
-// Descriptors and launch shape of the quotient kernel in one precision, for
-// the batch's systems and tasks.
-static pe_status build_quot(Batch &B, const std::vector<BatchDesc> &descs, int dd)
+// A point of a system, its polynomials split into R tasks of some cost each.
+struct PointTasks {
+    int sys, R;
+    int64_t pt;
+    double cost;
+};
+
+// The list of all tasks.  Task r of R takes the polynomials r, r + R, ..., so
+// that neighbouring polynomials, whose entries of J share cache lines, are at
+// the same step of the R tasks.  Longest first; eight points at a time, so
+// that the tasks of one point are eight apart in the list: workgroups eight
+// apart share an XCD.
+static std::vector<BatchTask> list_tasks(const Batch &B, std::vector<PointTasks> &points)
+{
+    std::stable_sort(points.begin(), points.end(),
+                     [](const PointTasks &a, const PointTasks &b) { return a.cost > b.cost; });
+    std::vector<BatchTask> tv;
+    for (size_t k = 0; k < points.size(); k += 8) {
+        const size_t end = std::min(points.size(), k + 8);
+        int most = 0;
+        for (size_t q = k; q < end; ++q) most = std::max(most, points[q].R);
+        for (int r = 0; r < most; ++r)
+            for (size_t q = k; q < end; ++q)
+                if (r < points[q].R)
+                    tv.push_back({points[q].sys, r, B.sys[(size_t)points[q].sys]->n_polys, points[q].R,
+                                  points[q].pt});
+    }
+    return tv;
+}
+
+// derivative terms and values of a point
+static int64_t system_terms(const System &S)
+{
+    return S.n_monos + (S.n_monos ? S.mono_start[(size_t)S.n_monos] : 0);
+}
+
+// Descriptors, tasks and launch shape of the quotient kernel in one
+// precision.  Systems without tables or with long runs are left out (their
+// descriptors say CH = 0); if memory runs out, all are.
+static void build_quot(Batch &B, const std::vector<BatchDesc> &descs, const std::vector<int64_t> &pps, int dd,
+                       hipStream_t hs)
 {
     Batch::QuotLaunch &ql = B.quot[dd];
     const int words = dd ? 4 : 2, ns = (int)B.sys.size();
     std::vector<QuotBatchDesc> qd((size_t)ns);
     size_t lds1 = 0, lds2 = 0;
-    int most_m = 1, most_ranks = 1;
+    int lanes = 1;
+    int64_t items = 0;
+    double terms = 0;
     ql.threads = 0;
     for (int i = 0; i < ns; ++i) {
         System &S = *B.sys[(size_t)i];
@@ -89,11 +130,11 @@ static pe_status build_quot(Batch &B, const std::vector<BatchDesc> &descs, int d
         qd[(size_t)i].x_off = descs[(size_t)i].x_off;
         qd[(size_t)i].f_off = descs[(size_t)i].f_off;
         qd[(size_t)i].J_off = descs[(size_t)i].J_off;
+        if (S.long_runs(words, 0)) continue;
         Quot *q = nullptr;
         {
             std::lock_guard<std::mutex> lock(S.mu);
-            pe_status st = S.quot_for(words, false, &q);
-            if (st != PE_OK) return st;
+            q = S.quot_for(words, false, hs);
         }
         if (!q) continue;
         S.fill_quot(*q, qd[(size_t)i].a);
@@ -102,22 +143,37 @@ static pe_status build_quot(Batch &B, const std::vector<BatchDesc> &descs, int d
         };
         lds1 = std::max(lds1, lds(1));
         lds2 = std::max(lds2, lds(2));
-        most_m = std::max(most_m, (int)std::min<int64_t>(S.quot_max_m, q->CH));
-        most_ranks = std::max(most_ranks, q->n_blk * kRankBlock);
+        lanes = std::max(lanes, S.quot_lanes(*q));
+        items += pps[(size_t)i] * S.n_polys;
+        terms += (double)pps[(size_t)i] * (double)system_terms(S);
     }
-    if (lds1 == 0) return PE_OK;
+    if (lds1 == 0) return;
     // two buffers of values unless they cost residency
     const int nbuf = (size_t)kMaxLds / lds2 >= std::min<size_t>(4, kMaxLds / lds1) ? 2 : 1;
     ql.lds = nbuf == 2 ? lds2 : lds1;
     const int per_cu = (int)std::max<size_t>(1, kMaxLds / ql.lds);
-    const int nt = quot_threads(most_m, most_ranks, ql.lds, 1024);
-    for (int i = 0; i < ns; ++i)
+    const int nt = quot_threads(lanes, ql.lds, items, 1024);
+    const int64_t resident = 256 * std::max(1, std::min(per_cu, 1024 / nt));
+    // tasks for several rounds of the chip, of at most as many terms as the
+    // general kernel's
+    const double target = std::min((double)B.cfg.task_terms, terms / (double)(resident * 6));
+    std::vector<PointTasks> points;
+    for (int i = 0; i < ns; ++i) {
         if (qd[(size_t)i].a.CH > 0) qd[(size_t)i].a.nbuf = nbuf;
-    const hipError_t e = ql.desc.upload(qd.data(), qd.size() * sizeof(QuotBatchDesc));
-    if (e != hipSuccess) return hip_fail(e, "uploading batch tables");
+        const System &S = *B.sys[(size_t)i];
+        const double t = (double)system_terms(S);
+        const int R = (int)std::max(1.0, std::min((double)S.n_polys, t / std::max(1.0, target)));
+        for (int64_t pt = 0; pt < pps[(size_t)i]; ++pt) points.push_back({i, R, pt, t / R});
+    }
+    const std::vector<BatchTask> tv = list_tasks(B, points);
+    if (ql.desc.upload(qd.data(), qd.size() * sizeof(QuotBatchDesc)) != hipSuccess ||
+        ql.tasks.upload(tv.data(), tv.size() * sizeof(BatchTask)) != hipSuccess) {
+        (void)hipGetLastError();
+        return;
+    }
+    ql.n_tasks = (int64_t)tv.size();
     ql.threads = nt;
-    ql.grid = 256 * std::max(1, std::min(per_cu, 1024 / nt));
-    return PE_OK;
+    ql.grid = (int)std::min<int64_t>(ql.n_tasks, resident);
 }
 
 // (Re)build descriptors and tasks for `pps` points per system.
@@ -125,11 +181,12 @@ static pe_status build_batch(Batch &B, const std::vector<int64_t> &pps, hipStrea
 {
     const int ns = (int)B.sys.size();
     std::vector<BatchDesc> descs((size_t)ns);
-    struct PointTasks {
-        int sys, R;
-        int64_t pt;
-        double cost;  // of one task
-    };
+    // tasks of about task_terms derivative terms, or fewer where that would
+    // leave the chip with few tasks: systems of 24 to 136 monomials and one
+    // point each in FP64 168 us with 46 tasks (quotients, 4 tasks per CU: 12 us)
+    double all = 0;
+    for (int i = 0; i < ns; ++i) all += (double)pps[(size_t)i] * (double)system_terms(*B.sys[(size_t)i]);
+    const int64_t target = (int64_t)std::max(1.0, std::min((double)B.cfg.task_terms, all / (256 * 8)));
     std::vector<PointTasks> points;
     int64_t x_off = 0, f_off = 0, J_off = 0;
     size_t lds_max = 0;
@@ -148,11 +205,7 @@ static pe_status build_batch(Batch &B, const std::vector<int64_t> &pps, hipStrea
         f_off += pps[(size_t)i] * S.n_polys;
         J_off += pps[(size_t)i] * (int64_t)S.n_vars * S.n_polys;
         lds_max = std::max(lds_max, sc->lds_bytes(4));
-        // tasks of about task_terms derivative terms: task r of R takes the
-        // polynomials r, r + R, ..., so that neighbouring polynomials, whose
-        // entries of J share cache lines, are at the same step of the R tasks
-        const int64_t terms = S.n_monos + (S.n_monos ? S.mono_start[(size_t)S.n_monos] : 0);
-        const int R = (int)std::max<int64_t>(1, std::min<int64_t>(S.n_polys, terms / B.cfg.task_terms));
+        const int R = (int)std::max<int64_t>(1, std::min<int64_t>(S.n_polys, system_terms(S) / target));
         // cost of a point's tasks
         const double cost = ((double)S.n_vars * sc->R * R +
                              (double)S.n_monos * (6.0 * std::max(1, S.max_k) - 5.0) +
@@ -161,21 +214,7 @@ static pe_status build_batch(Batch &B, const std::vector<int64_t> &pps, hipStrea
     }
     if (lds_max > kMaxLds)
         return fail(PE_EUNSUPPORTED, "a system of the batch needs %zu bytes of LDS", lds_max);
-    // longest first; eight points at a time, so that the tasks of one point
-    // are eight apart in the list: workgroups eight apart share an XCD
-    std::stable_sort(points.begin(), points.end(),
-                     [](const PointTasks &a, const PointTasks &b) { return a.cost > b.cost; });
-    std::vector<BatchTask> tv;
-    for (size_t k = 0; k < points.size(); k += 8) {
-        const size_t end = std::min(points.size(), k + 8);
-        int most = 0;
-        for (size_t q = k; q < end; ++q) most = std::max(most, points[q].R);
-        for (int r = 0; r < most; ++r)
-            for (size_t q = k; q < end; ++q)
-                if (r < points[q].R)
-                    tv.push_back({points[q].sys, r, B.sys[(size_t)points[q].sys]->n_polys, points[q].R,
-                                  points[q].pt});
-    }
+    const std::vector<BatchTask> tv = list_tasks(B, points);
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(hs, &cs) == hipSuccess && cs != hipStreamCaptureStatusNone)
         return fail(PE_EUNSUPPORTED,
@@ -184,11 +223,7 @@ static pe_status build_batch(Batch &B, const std::vector<int64_t> &pps, hipStrea
     hipError_t e = B.desc.upload(descs.data(), descs.size() * sizeof(BatchDesc));
     if (e == hipSuccess) e = B.tasks.upload(tv.data(), tv.size() * sizeof(BatchTask));
     if (e != hipSuccess) return hip_fail(e, "uploading batch tables");
-    for (int dd = 0; dd < 2; ++dd) {
-        pe_status st = build_quot(B, descs, dd);
-        if (st != PE_OK) return st;
-        B.quot[dd].grid = (int)std::min<int64_t>((int64_t)tv.size(), B.quot[dd].grid);
-    }
+    for (int dd = 0; dd < 2; ++dd) build_quot(B, descs, pps, dd, hs);
     B.n_tasks = (int64_t)tv.size();
     B.lds_dd = lds_max;
     B.lds_64 = lds_max / 2;
@@ -234,8 +269,8 @@ static pe_status launch_batch_eval(Batch &B, const std::vector<int64_t> &pps, pe
     if (quotients && ql.threads) {
         QuotBatchArgs qa{};
         qa.desc = (const QuotBatchDesc *)ql.desc.ptr;
-        qa.tasks = a.tasks;
-        qa.n_tasks = a.n_tasks;
+        qa.tasks = (const BatchTask *)ql.tasks.ptr;
+        qa.n_tasks = ql.n_tasks;
         for (int q = 0; q < 4; ++q) {
             qa.x[q] = a.x[q];
             qa.f[q] = a.f[q];

@@ -49,18 +49,13 @@
 
 namespace pe {
 
-// Whether a quotient kernel left polynomial p to this one at some point of
-// the tiles pt0, pt0 + gridDim.y T, ... of T points (the same answer on every
-// thread).
-__device__ __forceinline__ bool any_refused(const EvalArgs &a, int p, int64_t pt0, int T)
+// Whether a quotient kernel left polynomial p to this one at some of the
+// points pt0, pt0 + gridDim.y, ... (the same answer on every thread).
+__device__ __forceinline__ bool any_refused(const EvalArgs &a, int p, int64_t pt0)
 {
     bool any = false;
-    const int64_t step = (int64_t)gridDim.y * T;
-    for (int64_t i = threadIdx.x;; i += blockDim.x) {
-        const int64_t pt = pt0 + i / T * step + i % T;
-        if (pt0 + i / T * step >= a.n_points) break;
-        if (pt < a.n_points) any = any || is_refused(a.f[0][pt * a.n_polys + p]);
-    }
+    for (int64_t pt = pt0 + (int64_t)threadIdx.x * gridDim.y; pt < a.n_points; pt += (int64_t)blockDim.x * gridDim.y)
+        any = any || is_refused(a.f[0][pt * a.n_polys + p]);
     return __syncthreads_or(any);
 }
 
@@ -70,37 +65,45 @@ __device__ __forceinline__ bool any_refused(const EvalArgs &a, int p, int64_t pt
 // fetched again per tile.  The first point's entries are requested first, so
 // that their latency overlaps the dependent loads of the group header and the
 // chunk inputs.
-template <class A, int CC, int MAXT, bool TILE>
+// REPAIR: only the polynomials at the points that a quotient kernel refused,
+// with all shares of a polynomial on one workgroup (not tiled); in a kernel of
+// its own, as the tests for it cost the others 3%.
+template <class A, int CC, int MAXT, bool TILE, bool REPAIR = false>
 __global__ __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(kWavesPerEu<A>))) void
 eval_kernel(const EvalArgs a)
 {
+    static_assert(!(TILE && REPAIR), "repairs take one point at a time");
     if constexpr (!TILE) {
         using C = typename A::C;
         HIP_DYNAMIC_SHARED(double2, lds_raw)
         const LdsLayout<A> lds = lds_layout<A, false>(lds_raw, a);
         const int group = xcd_order(blockIdx.x, gridDim.x);
         const int64_t pt0 = blockIdx.y;
-        if (a.repair && !any_refused(a, group, pt0, 1)) return;
+        if constexpr (REPAIR) {
+            if (!any_refused(a, group, pt0)) return;
+        }
         const bool has_x = (int)threadIdx.x < a.n_vars;
         // the first point's entry is requested before the tables
         C x0 = A::zero();
         if (pt0 < a.n_points && has_x) x0 = Io<A>::load(a.x, pt0 * a.n_vars + threadIdx.x);
-        const int4 *gi = a.group_info + 2 * (int64_t)group * a.merge;
+        const int4 *gi = a.group_info + 2 * (int64_t)group * (REPAIR ? a.merge : 1);
         const int4 g0 = gi[0], g1 = gi[1];
-        const int c_begin = g0.x, c_end = a.merge == 1 ? g0.y : gi[2 * (a.merge - 1)].y;
+        const int c_begin = g0.x, c_end = REPAIR ? gi[2 * (a.merge - 1)].y : g0.y;
         const bool single = c_end - c_begin == 1;
         ChunkIn<A, CC> in;
         RunIn rin = 0u;
         bool loaded = false, first = true;
         for (int64_t pt = pt0; pt < a.n_points; pt += gridDim.y) {
             if (a.mask && a.mask[pt] != kMaskLive) continue;
-            if (a.repair && !is_refused(a.f[0][pt * a.n_polys + group])) continue;
+            if constexpr (REPAIR) {
+                if (!is_refused(a.f[0][pt * a.n_polys + group])) continue;
+            }
             if (!first) __syncthreads();  // the previous point is done with LDS
             first = false;
             if (pt != pt0 && has_x) x0 = Io<A>::load(a.x, pt * a.n_vars + threadIdx.x);
             if (!loaded && c_begin < c_end) {
                 // (merged shares: the first one may be empty, without a header)
-                in.ci = a.merge == 1 ? make_int4(g0.z, g0.w, g1.x, g1.y) : a.chunk_info[c_begin];
+                in.ci = REPAIR ? a.chunk_info[c_begin] : make_int4(g0.z, g0.w, g1.x, g1.y);
                 load_lane_in<A, CC>(a, in);
                 rin = load_run_in(a, in.ci);
                 loaded = single;
@@ -117,14 +120,13 @@ eval_kernel(const EvalArgs a)
         const int T = a.T;
         const int64_t n_tiles = (a.n_points + T - 1) / T;
         const int64_t tile0 = blockIdx.y;
-        if (a.repair && !any_refused(a, group, tile0 * T, T)) return;
         const bool has_x = (int)threadIdx.x < a.n_vars;
         // the first point's entry is requested before the tables
         C x0 = A::zero();
         if (tile0 < n_tiles && has_x) x0 = Io<A>::load(a.x, tile0 * T * a.n_vars + threadIdx.x);
-        const int4 *gi = a.group_info + 2 * (int64_t)group * a.merge;
+        const int4 *gi = a.group_info + 2 * (int64_t)group;
         const int4 g0 = gi[0], g1 = gi[1];
-        const int c_begin = g0.x, c_end = a.merge == 1 ? g0.y : gi[2 * (a.merge - 1)].y;
+        const int c_begin = g0.x, c_end = g0.y;
         const bool single = c_end - c_begin == 1;
         ChunkIn<A, CC> in;
         RunIn rin = 0u;
@@ -136,16 +138,12 @@ eval_kernel(const EvalArgs a)
             if (a.mask)
                 for (int t = 0; t < npt; ++t)
                     if (a.mask[pt0 + t] != kMaskLive) live &= ~(1u << t);
-            if (a.repair)
-                for (int t = 0; t < npt; ++t)
-                    if (!is_refused(a.f[0][(pt0 + t) * a.n_polys + group])) live &= ~(1u << t);
             if (!live) continue;
             if (!first) __syncthreads();  // the previous tile is done with LDS
             first = false;
             if (tile != tile0 && has_x) x0 = Io<A>::load(a.x, pt0 * a.n_vars + threadIdx.x);
             if (!loaded && c_begin < c_end) {
-                // (merged shares: the first one may be empty, without a header)
-                in.ci = a.merge == 1 ? make_int4(g0.z, g0.w, g1.x, g1.y) : a.chunk_info[c_begin];
+                in.ci = make_int4(g0.z, g0.w, g1.x, g1.y);
                 load_lane_in<A, CC>(a, in);
                 rin = load_run_in(a, in.ci);
                 loaded = single;
@@ -269,11 +267,11 @@ hipError_t launch_combine(int prec, const EvalArgs &args, hipStream_t stream)
 
 using KernelFn = void (*)(const EvalArgs);
 
-template <class A, bool TILE>
+template <class A, bool TILE, bool REPAIR>
 static KernelFn pick(int cc, int maxt)
 {
 #define PE_CASE(CCV, MT) \
-    if (cc == CCV && maxt == MT) return eval_kernel<A, CCV, MT, TILE>;
+    if (cc == CCV && maxt == MT) return eval_kernel<A, CCV, MT, TILE, REPAIR>;
     PE_CASE(2, 256) PE_CASE(2, 512) PE_CASE(2, 1024)
     PE_CASE(4, 256) PE_CASE(4, 512) PE_CASE(4, 1024)
     PE_CASE(8, 256) PE_CASE(8, 512) PE_CASE(8, 1024)
@@ -283,20 +281,28 @@ static KernelFn pick(int cc, int maxt)
 
 // quad-double: 256 threads with two or four variables per lane, or 512
 // threads with two (two waves per SIMD); one point per workgroup
+template <bool REPAIR>
 static KernelFn pick_qd(int cc, int maxt)
 {
-    if (maxt == 512) return cc == 2 ? eval_kernel<ArithQD, 2, 512, false> : nullptr;
+    if (maxt == 512) return cc == 2 ? eval_kernel<ArithQD, 2, 512, false, REPAIR> : nullptr;
     if (maxt != 256) return nullptr;
-    if (cc == 2) return eval_kernel<ArithQD, 2, 256, false>;
-    if (cc == 4) return eval_kernel<ArithQD, 4, 256, false>;
+    if (cc == 2) return eval_kernel<ArithQD, 2, 256, false, REPAIR>;
+    if (cc == 4) return eval_kernel<ArithQD, 4, 256, false, REPAIR>;
     return nullptr;
 }
 
-static KernelFn pick_any(int prec, int cc, int maxt, bool tile)
+// tile and repair: not both (the launch would be refused)
+static KernelFn pick_any(int prec, int cc, int maxt, bool tile, bool repair)
 {
-    if (prec == 2) return tile ? nullptr : pick_qd(cc, maxt);
-    if (prec == 1) return tile ? pick<ArithDD, true>(cc, maxt) : pick<ArithDD, false>(cc, maxt);
-    return tile ? pick<Arith64, true>(cc, maxt) : pick<Arith64, false>(cc, maxt);
+    if (tile && (repair || prec == 2)) return nullptr;
+    if (prec == 2) return repair ? pick_qd<true>(cc, maxt) : pick_qd<false>(cc, maxt);
+    if (prec == 1)
+        return tile     ? pick<ArithDD, true, false>(cc, maxt)
+               : repair ? pick<ArithDD, false, true>(cc, maxt)
+                        : pick<ArithDD, false, false>(cc, maxt);
+    return tile     ? pick<Arith64, true, false>(cc, maxt)
+           : repair ? pick<Arith64, false, true>(cc, maxt)
+                    : pick<Arith64, false, false>(cc, maxt);
 }
 
 // Tiles of one point with one staging buffer run the one-point kernel body;
@@ -304,7 +310,7 @@ static KernelFn pick_any(int prec, int cc, int maxt, bool tile)
 hipError_t launch_eval(int prec, int cc, int maxt, const EvalArgs &args, dim3 grid, dim3 block,
                        size_t lds_bytes, hipStream_t stream)
 {
-    KernelFn k = pick_any(prec, cc, maxt, args.T > 1 || args.nbuf > 1);
+    KernelFn k = pick_any(prec, cc, maxt, args.T > 1 || args.nbuf > 1, args.repair != 0);
     if (!k) return hipErrorInvalidValue;
     hipLaunchKernelGGL(k, grid, block, lds_bytes, stream, args);
     return hipGetLastError();
@@ -384,8 +390,9 @@ hipError_t eval_kernels_init()
     for (int prec = 0; prec < 2; ++prec)
         for (int c : ccs)
             for (int m : mts) {
-                const void *ks[3] = {reinterpret_cast<const void *>(pick_any(prec, c, m, false)),
-                                     reinterpret_cast<const void *>(pick_any(prec, c, m, true)),
+                const void *ks[4] = {reinterpret_cast<const void *>(pick_any(prec, c, m, false, false)),
+                                     reinterpret_cast<const void *>(pick_any(prec, c, m, false, true)),
+                                     reinterpret_cast<const void *>(pick_any(prec, c, m, true, false)),
                                      reinterpret_cast<const void *>(
                                          prec == 1 ? pick_batch<ArithDD>(c, m)
                                                    : pick_batch<Arith64>(c, m))};
@@ -396,9 +403,10 @@ hipError_t eval_kernels_init()
                         (void)hipGetLastError();
             }
     for (int c : {2, 4})
-        if (hipFuncSetAttribute(reinterpret_cast<const void *>(pick_qd(c, 256)),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLds) != hipSuccess)
-            (void)hipGetLastError();
+        for (KernelFn k : {pick_qd<false>(c, 256), pick_qd<true>(c, 256)})
+            if (hipFuncSetAttribute(reinterpret_cast<const void *>(k),
+                                    hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLds) != hipSuccess)
+                (void)hipGetLastError();
     return hipSuccess;
 }
 

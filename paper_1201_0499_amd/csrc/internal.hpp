@@ -46,8 +46,10 @@ struct Schedule {
 };
 
 // Calls of at most this many (polynomial, point) pairs run in one launch
-// (small.hip): two workgroups per CU.
-constexpr int64_t kSmallUnits = 512;
+// (small.hip): five workgroups per CU.  One MI355X, two launches against one:
+// n = 350, m = 69, k = 8, 3 points in FP64 17.5 and 14.7 us, n = 16, m = 64, k
+// = 16, 128 points (2048 pairs) 17 and 18.3 us.
+constexpr int64_t kSmallUnits = 1280;
 
 // Packed tables of one system for the quotient kernels (quotient.hpp).
 struct Quot {
@@ -57,7 +59,7 @@ struct Quot {
 };
 
 // workgroup size of a quotient kernel: see api.cpp
-int quot_threads(int m, int ranks, size_t lds, int cap);
+int quot_threads(int lanes, size_t lds, int64_t workgroups, int cap);
 
 struct System {
     int32_t n_vars = 0, n_polys = 0;
@@ -110,9 +112,12 @@ struct System {
     pe_status schedule_with(int L, int cc, int nt, int G, Schedule **out);
     // launch arguments of a schedule (points, outputs and mask unset)
     void fill_args(const Schedule &sc, EvalArgs &a) const;
-    // the quotient tables for values of `words` doubles: *out is nullptr if
-    // the system is outside those kernels (or, with find_only, not packed yet)
-    pe_status quot_for(int words, bool find_only, Quot **out);
+    // the quotient tables for values of `words` doubles: nullptr if the system
+    // is outside those kernels, or the tables are not there (find_only: not
+    // packed yet) and cannot be made
+    Quot *quot_for(int words, bool find_only, hipStream_t hs);
+    int quot_lanes(const Quot &q) const;
+    bool long_runs(int words, int64_t mono) const;
     // launch arguments of the quotient kernels (points, outputs, mask and
     // launch shape unset)
     void fill_quot(const Quot &q, QuotArgs &a) const;
@@ -121,7 +126,8 @@ struct System {
     hipError_t run_values(const Quot &q, int prec, QuotArgs qa, hipStream_t hs) const;
     // evaluation by quotients (prec 0 = FP64, 1 = double-double, 2 =
     // quad-double) of the points, outputs and mask of `a`, whose general
-    // kernel with maxt, threads and lds bytes serves what they refuse
+    // kernel with maxt, threads and lds bytes (for one point and one staging
+    // buffer) serves what they refuse
     hipError_t run_quot(const Quot &q, int prec, int cc, int maxt, EvalArgs a, unsigned threads, size_t lds,
                         hipStream_t hs) const;
     // schedule, tile, staging buffers and LDS of an evaluation, or why there

@@ -110,8 +110,7 @@ static pe_status newton_core(System *S, int64_t n_starts, double *const *x, int 
     Quot *quot = nullptr;
     QuotArgs qa;
     if (mixed && quotients) {
-        pe_status qs = S->quot_for(rw, false, &quot);
-        if (qs != PE_OK) return qs;
+        quot = S->quot_for(rw, false, hs);
         if (quot) {
             S->fill_quot(*quot, qa);
             qa.n_points = n_starts;
