@@ -80,3 +80,31 @@ def test_first_call_of_a_precision_under_capture(first):
         _check(s, pts, host(f), host(J), prec)
         run_eval(S, pts, prec)  # eager work between the replays, by quotients
     S.close()
+
+
+@pytest.mark.parametrize("prec", [1, 0], ids=["dd", "fp64"])
+def test_batch_takes_the_same_side(prec):
+    """Bitwise the same from a batch as from each system under the batch's
+    schedule, for systems on either side of the rules."""
+    systems = [synth.regular_system(n, m, k, (1, 3), seed=300 + n, n_polys=6)
+               for n, m, k in [(16, 64, 16), (33, 64, 16), (11, 600, 8), (40, 30, 4)]]
+    pps = np.array([3, 3, 40, 5], np.int64)
+    pts = [synth.points(int(P), s.n_vars, 17) for P, s in zip(pps, systems)]
+    handles = [pe.System.from_csr(s) for s in systems]
+    B = pe.Batch(handles)
+    _, fo, jo = B.layout(pps)
+    x = dev(tuple(np.concatenate([p[q].reshape(-1) for p in pts]) for q in range(4)))
+    f, J = alloc((int(fo[-1]),)), alloc((int(jo[-1]),))
+    B.eval_jac(pps, x, f, J, prec)
+    torch.cuda.synchronize()
+    f, J = host(f), host(J)
+    for i, (S, s) in enumerate(zip(handles, systems)):
+        lanes = max(1, 1 << (-(-s.max_k // 4) - 1).bit_length())
+        S.set_schedule(lanes=lanes, chunk_vars=4, threads=256, groups=1)
+        fs, Js = run_eval(S, pts[i], prec)
+        for q in (0, 1, 2, 3) if prec == 1 else (0, 2):
+            assert np.array_equal(fs[q].reshape(-1), f[q][fo[i]:fo[i + 1]])
+            assert np.array_equal(Js[q].reshape(-1), J[q][jo[i]:jo[i + 1]])
+    B.close()
+    for S in handles:
+        S.close()
