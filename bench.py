@@ -5,7 +5,8 @@ n = 512 variables and 512 polynomials of m = 1024 monomials, k = 32
 variables per monomial, exponents uniform in 1..5, unit-circle complex
 double-double coefficients, evaluated with its full Jacobian at 256
 unit-circle points per launch.  One step = one pe_eval_jac call over the 256
-points (one kernel launch), with the schedule chosen by the library's
+points (the quotient kernel and the general kernel, which finds nothing to
+do), with the schedule chosen by the library's
 autotuner (pe_autotune_system, cached in a text file).  Inputs are resident
 in HBM before the timed region; the timed region is exactly --steps launches
 between two device synchronizations, and HIP events recorded on the launch
@@ -56,7 +57,7 @@ GRAPH_LAUNCHES = 100
 C2_LAUNCHES = 10000          # the paper-scale workload is repeated 10,000 times
 COPY_BYTES = 512 << 20       # copy-calibration size
 
-HEADLINE_RECORD = os.path.join(ROOT, "profiles", "eval_kernel_dd_large_counters.json")
+HEADLINE_RECORD = os.path.join(ROOT, "profiles", "quot_kernel_dd_large_counters.json")
 TUNED_SCHEDULES = os.path.join(ROOT, "paper_1201_0499_amd", "tuned_schedules.txt")
 C2_RECORD = os.path.join(ROOT, "profiles", "eval_kernel_dd_paper_scale_traffic.json")
 
@@ -83,41 +84,36 @@ PAPER_C2050 = {
 
 def dd_flops_per_monomial(k: int) -> int:
     """Algorithmic flops of value + all k partials of one monomial in complex
-    double-double, the paper's method: (6k-5) complex dd products of 88
-    flops (four double-word products, two double-word sums) and (k+1)
-    complex dd sums of 40 flops."""
-    return 568 * k - 400
+    double-double, by quotients: k complex dd products of 88 flops (four
+    double-word products, two double-word sums) and (k+1) complex dd sums of
+    40 flops.  (The paper's forward and backward products take 6k-5
+    products: 568 k - 400 flops.)"""
+    return 128 * k + 40
 
 
 def f64_flops_per_monomial(k: int) -> int:
-    """The same in complex FP64: (6k-5) complex products of 6 flops and
-    (k+1) complex sums of 2."""
-    return 38 * k - 28
+    """The same in complex FP64: k complex products of 6 flops and (k+1)
+    complex sums of 2."""
+    return 8 * k + 2
 
 
 def log(msg):
     print(msg, file=sys.stderr, flush=True)
 
 
-def kernel_name(arith, sched):
-    """Name of the evaluation kernel instantiation a schedule launches (its
-    workgroup-size bound is 256, 512 or 1024)."""
-    nt = sched["threads"]
-    maxt = 256 if nt <= 256 else (512 if nt <= 512 else 1024)
-    return f"eval_kernel<{arith}, {sched['chunk_vars']}, {maxt}>"
-
-
 def kernel_sources_sha256():
-    """Hash of the sources that decide the evaluation kernel and its launch:
-    eval.hip, the schedule tables (schedule.cpp), the launch code (api.cpp)
-    and the headers of those three that define the evaluation.  A change to
+    """Hash of the sources that decide the evaluation kernels and their
+    launches: the quotient kernels, the general kernel, their tables and the
+    launch code (api.cpp) with the headers of those.  A change to
     the Newton, tracker, batch or ablation code leaves the evaluation's
     counters valid."""
     import hashlib
     h = hashlib.sha256()
     d = os.path.join(ROOT, "paper_1201_0499_amd", "csrc")
-    for f in ("api.cpp", "dd.hpp", "device.hpp", "eval.hip", "eval.hpp", "internal.hpp",
-              "monomial.hpp", "packing.hpp", "qd.hpp", "schedule.cpp", "schedule.hpp"):
+    for f in ("api.cpp", "dd.hpp", "device.hpp", "eval.hip", "eval.hpp", "eval_body.hpp",
+              "internal.hpp", "monomial.hpp", "packing.hpp", "qd.hpp", "quotient.hip",
+              "quotient.hpp", "quotient_args.hpp", "quotient_body.hpp", "quotient_tables.cpp",
+              "schedule.cpp", "schedule.hpp", "small.hip"):
         h.update(f.encode())
         with open(os.path.join(d, f), "rb") as fh:
             h.update(fh.read())
@@ -164,7 +160,7 @@ def roofline_block(kernel, sched, seconds, flops, rec):
                            "what it reads for a copy of known size)",
            "kernel": kernel, "schedule": sched, "kernel_us": seconds * 1e6,
            "flops_per_launch": flops,
-           "achieved_kind": "algorithmic: the paper's operation count per monomial "
+           "achieved_kind": "algorithmic: the operation count per monomial by quotients "
                             "(see flops_per_monomial) x monomials x points / time per launch"}
     if rec is not None:
         fs, ws = rec["fetch_scale"], rec["write_scale"]
@@ -228,8 +224,8 @@ def measure_headline(pe, torch, stream, args):
     log(f"[bench] dd: {wall / args.steps * 1e3:.3f} ms/step (wall), {gpu_s * 1e3:.3f} ms "
         f"(events), {value:.4e} evals/s")
     flops = M * P * dd_flops_per_monomial(k)
-    rec = counter_record(HEADLINE_RECORD, sched, "void pe::eval_kernel<pe::ArithDD")
-    roof = roofline_block(kernel_name("ArithDD", sched), sched, gpu_s, flops, rec)
+    rec = counter_record(HEADLINE_RECORD, sched, "void pe::quot_kernel<pe::ArithDD")
+    roof = roofline_block("quot_kernel<ArithDD> (+ eval_kernel on what it refuses)", sched, gpu_s, flops, rec)
     roof["flops_per_monomial"] = dd_flops_per_monomial(k)
     log(f"[bench] dd roofline: {roof['achieved']:.2f} TFLOP/s algorithmic = "
         f"{roof['frac']:.3f} of FP64 peak"
@@ -255,7 +251,7 @@ def measure_headline(pe, torch, stream, args):
         side["large_fp64"] = {
             "workload": "headline system and points, complex FP64", "ms_per_launch": s64 * 1e3,
             "evals_per_s": M * P / s64,
-            "roofline": roofline_block(kernel_name("Arith64", sch64), sch64, s64,
+            "roofline": roofline_block("quot_kernel<Arith64> (+ eval_kernel on what it refuses)", sch64, s64,
                                        M * P * f64_flops_per_monomial(k), None)}
         side["large_fp64"]["roofline"]["flops_per_monomial"] = f64_flops_per_monomial(k)
         log(f"[bench] large fp64: {s64 * 1e3:.3f} ms/launch, {M * P / s64:.4e} evals/s, "
@@ -374,8 +370,7 @@ def measure_paper_scale(pe, torch, stream, args):
             wall = time.perf_counter() - t0
         s = e0.elapsed_time(e1) * 1e-3 / C2_LAUNCHES
         per = dd_flops_per_monomial(k) if prec == pe.PE_DD else f64_flops_per_monomial(k)
-        kname = ("eval_kernel<ArithDD>" if prec == pe.PE_DD else "eval_kernel<Arith64>") + \
-            (" + combine_kernel" if sched["groups"] > 1 else "")
+        kname = "small_kernel<ArithDD>" if prec == pe.PE_DD else "small_kernel<Arith64>"
         rec = None
         if prec == pe.PE_DD:
             rec = c2_traffic_record(sched)

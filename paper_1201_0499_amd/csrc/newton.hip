@@ -6,11 +6,14 @@
 //             one workgroup per start builds the power table x_i^r,
 //             r = 1..d, in LDS; each wave takes whole polynomials, its lanes
 //             stride over the monomials (c * prod x^a from the table) and the
-//             wave sums them with a butterfly.  Deterministic order.
+//             wave sums them with a butterfly.  Deterministic order.  With
+//             repair set, only what the quotient kernel of values refused.
 //  check      residual norm max_p |f_p| and the per-start status.
 //  lu_solve   J d = r by Gaussian elimination with partial pivoting, one
 //             workgroup per start, J column-major in global memory, in
 //             complex FP64 or complex dd (templated on the arithmetic).
+//  gj_dd      the dd solve for n <= 103 by Gauss-Jordan elimination, the
+//             matrix in registers of one workgroup.
 //  gj_small, gj_panel
 //             the FP64 solve for n <= 128 by Gauss-Jordan elimination with
 //             partial pivoting, the matrix in registers of one workgroup.

@@ -21,8 +21,8 @@
 // and 23 per scaled addition).  Against the general kernel's forward and
 // backward products, one MI355X: n = 512, m = 1024, k = 32, d = 5, 256 points
 // in double-double 58.2 -> 12.8 ms; n = 100, m = 200, k up to 16, 1000 points
-// in FP64 1130 -> 325 us; values only, n = 150, m = 299, k up to 12, 333
-// points in double-double 2912 -> 237 us.  Errors against 64-bit and exact
+// in FP64 1130 -> 305 us; values only, n = 150, m = 299, k up to 12, 333
+// points in double-double 2912 -> 232 us.  Errors against 64-bit and exact
 // references are the same or smaller: a term now takes k products, not 2k.
 #include "quotient_body.hpp"
 
@@ -105,7 +105,10 @@ __global__ __launch_bounds__(kQuotMaxThreads<A>) void quot_values_kernel(const Q
 
 // Many systems in one persistent launch: workgroup b takes the tasks
 // b, b + gridDim.x, ... of the batch's list.  Tasks of systems outside these
-// kernels are refused whole.
+// kernels are refused whole.  24 systems of up to 160 variables and 512
+// monomials, 24 points each in double-double: 2108 us by the general kernel,
+// 1510 us with that kernel's coarse tasks and the descriptors in vector
+// registers, 887 us.
 template <class A, bool JAC>
 __global__ __launch_bounds__(kQuotMaxThreads<A>) void quot_batch_kernel(const QuotBatchArgs b)
 {

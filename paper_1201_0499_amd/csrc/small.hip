@@ -3,8 +3,9 @@
 // point by quotients (quotient.hip) and, if they refuse, evaluates it with
 // the general stages (eval.hip) itself, where larger calls leave the refused
 // ones to a second launch.  Bound: launch, point load and the chain of the
-// three stages; n = 128, m = 256, k = 16 at one point in double-double 16.5 ->
-// 13.0 us per call, in quad-double 116 -> 79 us (two launches: 17.4 and 82 us).
+// three stages; general kernel -> here, n = 128, m = 256, k = 16 at one point
+// in double-double 16.5 -> 10.4 us per call, in quad-double 117 -> 55 us.  Two
+// launches cost about 4 us more.
 #include "eval_body.hpp"
 #include "quotient_body.hpp"
 
