@@ -421,25 +421,35 @@ int quot_threads(int lanes, size_t lds, int64_t workgroups, int cap)
     return std::min(nt, (lanes + 63) / 64 * 64);
 }
 
-// Whether the Jacobian's runs are too long for the quotient kernels: a few
-// lanes then add one long run each while the others wait, and the general
-// kernel, whose lanes share the terms evenly, is the faster one.  One MI355X,
-// general against quotients:
+// Whether the general kernel is the faster one, for calls of `units`
+// (polynomial, point) pairs; chunk: monomials that its workgroups take of a
+// polynomial at once.  One MI355X, general against quotients:
+// * Long runs: a few lanes add one long run each while the others wait, where
+//   the general kernel's lanes share the terms evenly.
 //   FP64: n = 8, m = 1000, k = 8, 512 points 91 and 174 us; n = 16, k = 16,
 //     one point 24 and 37 us; but n = 32 and one point 14 and 13 us;
 //   double-double: n = 8, m = 1000, k = 8, 512 points 315 and 547 us; but m =
 //     256 92 and 79 us, and n = 16, k = 16, 32 points 241 and 89 us;
 //   quad-double: n = 8, m = 1000, k = 8, 512 points 5660 and 4780 us.
-// mono: monomials that a workgroup of a small call (0: none) takes at once;
-// if they make up the polynomial, the general kernel is as short a chain:
-// n = 16, m = 256, k = 16, one point in double-double 15.3 and 17.1 us, in
-// quad-double 63 and 71 us; n = 32, m = 256, k = 8, 32 points in FP64 12.6 and
-// 13.7 us.  The same with and without the Jacobian, so that
-// both give the same values bit for bit.
-bool System::long_runs(int words, int64_t mono) const
+// * Small calls whose polynomials the general kernel takes at once, and so in
+//   as short a chain: n = 16, m = 256, k = 16, one point in double-double 15.3
+//   and 17.1 us, in quad-double 63 and 71 us; n = 32, m = 256, k = 8, 32
+//   points in FP64 12.6 and 13.7 us.
+// * Monomials of two variables, which save the least, in calls whose
+//   workgroups build a power table, with its reciprocals, for one or two
+//   polynomials each: double-double, n = 186, m = 274, 29 points 88 and 97 us;
+//   but n = 11, m = 147, 719 points (7909 pairs) 69 and 48 us; quad-double, n
+//   = 11, m = 8, 4 points 27.7 and 29.7 us; but n = 52, m = 185, 7 points 44
+//   and 36 us.
+// The same with and without the Jacobian, so that both give the same values
+// bit for bit.
+bool System::general_faster(int words, int64_t units, int64_t chunk) const
 {
-    const int64_t run = quot_max_m * (int64_t)max_k / std::max(1, n_vars);
-    if (quot_max_m <= mono && (words == 2 ? run >= 64 && n_vars <= 32 : run > 192 && n_vars < 18)) return true;
+    const int64_t terms = quot_max_m * (int64_t)max_k, run = terms / std::max(1, n_vars);
+    const bool small = units <= kSmallUnits;
+    if (small && quot_max_m <= chunk && (words == 2 ? run >= 64 && n_vars <= 32 : run > 192 && n_vars < 18))
+        return true;
+    if (max_k <= 2 && (words == 4 ? units <= 6144 : words == 8 && small && run < 3)) return true;
     if (words == 2) return run > 64 && n_vars < 24;
     return words == 4 && run > 64 && n_vars < 12 && quot_max_m > 512;
 }
@@ -616,8 +626,8 @@ pe_status System::eval_locked(int64_t n_points, const double *const x[4], double
     }
     const int maxt = sc->nt <= 256 ? 256 : (sc->nt <= 512 ? 512 : 1024);
     Quot *quot = nullptr;
-    const int64_t mono = n_points * n_polys <= kSmallUnits ? (int64_t)sc->MC * sc->G : 0;
-    if (quotients && !long_runs(words, mono)) quot = quot_for(words, no_alloc, hs);
+    if (quotients && !general_faster(words, n_points * n_polys, (int64_t)sc->MC * sc->G))
+        quot = quot_for(words, no_alloc, hs);
     if (quot) {
         hipError_t e = run_quot(*quot, dd ? 1 : 0, sc->cc, maxt, a, (unsigned)sc->nt,
                                 sc->lds_bytes(words), hs);
@@ -975,8 +985,8 @@ pe_status pe_eval_jac_qd(pe_system sys, int64_t n_points, const double *const *p
         }
         a.partial = (double *)S->partial.ptr;
     }
-    const int64_t mono = pairs <= kSmallUnits ? (int64_t)sc->MC * sc->G : 0;
-    if (Quot *quot = S->long_runs(8, mono) ? nullptr : S->quot_for(8, false, hs)) {
+    if (Quot *quot = S->general_faster(8, pairs, (int64_t)sc->MC * sc->G) ? nullptr
+                                                                          : S->quot_for(8, false, hs)) {
         hipError_t e = S->run_quot(*quot, 2, cc, nt, a, (unsigned)nt, lds, hs);
         if (e != hipSuccess) return hip_fail(e, "launching the quad-double evaluation by quotients");
         return PE_OK;

@@ -110,10 +110,11 @@ static int64_t system_terms(const System &S)
 }
 
 // Descriptors, tasks and launch shape of the quotient kernel in one
-// precision.  Systems without tables or with long runs are left out (their
+// precision.  Systems without tables, or that the general kernel serves
+// faster, are left out (their
 // descriptors say CH = 0); if memory runs out, all are.
 static void build_quot(Batch &B, const std::vector<BatchDesc> &descs, const std::vector<int64_t> &pps,
-                       const std::vector<int64_t> &mono, int dd, hipStream_t hs)
+                       const std::vector<int64_t> &chunk, int dd, hipStream_t hs)
 {
     Batch::QuotLaunch &ql = B.quot[dd];
     const int words = dd ? 4 : 2, ns = (int)B.sys.size();
@@ -130,7 +131,8 @@ static void build_quot(Batch &B, const std::vector<BatchDesc> &descs, const std:
         qd[(size_t)i].x_off = descs[(size_t)i].x_off;
         qd[(size_t)i].f_off = descs[(size_t)i].f_off;
         qd[(size_t)i].J_off = descs[(size_t)i].J_off;
-        if (S.long_runs(words, mono[(size_t)i])) continue;  // as pe_eval_jac under this schedule
+        // as pe_eval_jac under this schedule
+        if (S.general_faster(words, pps[(size_t)i] * S.n_polys, chunk[(size_t)i])) continue;
         Quot *q = nullptr;
         {
             std::lock_guard<std::mutex> lock(S.mu);
@@ -188,7 +190,7 @@ static pe_status build_batch(Batch &B, const std::vector<int64_t> &pps, hipStrea
     for (int i = 0; i < ns; ++i) all += (double)pps[(size_t)i] * (double)system_terms(*B.sys[(size_t)i]);
     const int64_t target = (int64_t)std::max(1.0, std::min((double)B.cfg.task_terms, all / (256 * 8)));
     std::vector<PointTasks> points;
-    std::vector<int64_t> mono((size_t)ns, 0);  // see System::long_runs
+    std::vector<int64_t> chunk((size_t)ns);  // see System::general_faster
     int64_t x_off = 0, f_off = 0, J_off = 0;
     size_t lds_max = 0;
     for (int i = 0; i < ns; ++i) {
@@ -198,7 +200,7 @@ static pe_status build_batch(Batch &B, const std::vector<int64_t> &pps, hipStrea
         pe_status st = S.schedule_with(L, B.cfg.cc, B.cfg.nt, 1, &sc);
         if (st != PE_OK) return st;
         S.fill_args(*sc, descs[(size_t)i].a);
-        if (pps[(size_t)i] * S.n_polys <= kSmallUnits) mono[(size_t)i] = (int64_t)sc->MC * sc->G;
+        chunk[(size_t)i] = (int64_t)sc->MC * sc->G;
         descs[(size_t)i].a.n_points = pps[(size_t)i];
         descs[(size_t)i].x_off = x_off;
         descs[(size_t)i].f_off = f_off;
@@ -225,7 +227,7 @@ static pe_status build_batch(Batch &B, const std::vector<int64_t> &pps, hipStrea
     hipError_t e = B.desc.upload(descs.data(), descs.size() * sizeof(BatchDesc));
     if (e == hipSuccess) e = B.tasks.upload(tv.data(), tv.size() * sizeof(BatchTask));
     if (e != hipSuccess) return hip_fail(e, "uploading batch tables");
-    for (int dd = 0; dd < 2; ++dd) build_quot(B, descs, pps, mono, dd, hs);
+    for (int dd = 0; dd < 2; ++dd) build_quot(B, descs, pps, chunk, dd, hs);
     B.n_tasks = (int64_t)tv.size();
     B.lds_dd = lds_max;
     B.lds_64 = lds_max / 2;

@@ -117,7 +117,7 @@ struct System {
     // packed yet) and cannot be made
     Quot *quot_for(int words, bool find_only, hipStream_t hs);
     int quot_lanes(const Quot &q) const;
-    bool long_runs(int words, int64_t mono) const;
+    bool general_faster(int words, int64_t units, int64_t chunk) const;
     // launch arguments of the quotient kernels (points, outputs, mask and
     // launch shape unset)
     void fill_quot(const Quot &q, QuotArgs &a) const;

@@ -41,6 +41,8 @@ def _check(s, pts, f, J, prec):
     (1, 18, 4, 256, 16, 1),    # and two variables more
     (1, 20, 40, 12, 4, 32),    # 1280 pairs: one launch,
     (1, 20, 40, 12, 4, 33),    # and two
+    (1, 60, 64, 40, 2, 96),    # two variables per monomial, 6144 pairs,
+    (1, 60, 64, 40, 2, 97),    # and more
     (0, 260, 260, 3, 4, 40),   # fewer factors than entries of J in a row
     (0, 300, 3, 40, 6, 500),   # two points do not leave four workgroups on a CU
 ])
@@ -87,7 +89,7 @@ def test_batch_takes_the_same_side(prec):
     """Bitwise the same from a batch as from each system under the batch's
     schedule, for systems on either side of the rules."""
     systems = [synth.regular_system(n, m, k, (1, 3), seed=300 + n, n_polys=6)
-               for n, m, k in [(16, 64, 16), (33, 64, 16), (11, 600, 8), (40, 30, 4)]]
+               for n, m, k in [(16, 64, 16), (33, 64, 16), (11, 600, 8), (40, 30, 2)]]
     pps = np.array([3, 3, 40, 5], np.int64)
     pts = [synth.points(int(P), s.n_vars, 17) for P, s in zip(pps, systems)]
     handles = [pe.System.from_csr(s) for s in systems]
