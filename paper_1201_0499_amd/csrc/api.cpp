@@ -505,10 +505,10 @@ hipError_t System::run_quot(const Quot &q, int prec, int cc, int maxt, EvalArgs 
     const auto lds_for = [&](int T, int nbuf) {
         return quot_lds_bytes(n_vars, max_exp, quot_pad, q.CH, q.multi, nbuf, T * words);
     };
-    if (units <= kSmallUnits) {
+    if (single_launch(units, lds, lds_for(1, 1))) {
         few_lanes(qa, m, (int)threads);
         return launch_small(prec, cc, maxt, a, qa, dim3((unsigned)n_polys, (unsigned)P, 1), threads,
-                            std::max(lds, lds_for(1, 1) + 16), hs);
+                            small_lds_bytes(lds, lds_for(1, 1)), hs);
     }
     // few workgroups, so that looking for work costs little when there is none
     const int64_t gy = std::min<int64_t>(P, std::max<int64_t>(1, 2048 / n_polys));

@@ -45,12 +45,6 @@ struct Schedule {
     size_t lds_bytes(int words, int T = 1, int nbuf = 1) const;
 };
 
-// Calls of at most this many (polynomial, point) pairs run in one launch
-// (small.hip): five workgroups per CU.  One MI355X, two launches against one:
-// n = 350, m = 69, k = 8, 3 points in FP64 17.5 and 14.7 us, n = 16, m = 64, k
-// = 16, 128 points (2048 pairs) 17 and 18.3 us.
-constexpr int64_t kSmallUnits = 1280;
-
 // Packed tables of one system for the quotient kernels (quotient.hpp).
 struct Quot {
     int CH = 0, n_blk = 0;

@@ -92,6 +92,20 @@ int quot_chunk(int n_vars, int max_exp, bool pad, int64_t max_m, int words);
 // LDS bytes of a workgroup with nbuf buffers of chunk values.
 size_t quot_lds_bytes(int n_vars, int max_exp, bool pad, int CH, bool multi, int nbuf, int words);
 
+// Calls of at most this many (polynomial, point) pairs run in one launch
+// (small.hip): five workgroups per CU.  One MI355X, two launches against one:
+// n = 350, m = 69, k = 8, 3 points in FP64 17.5 and 14.7 us, n = 16, m = 64, k
+// = 16, 128 points (2048 pairs) 17 and 18.3 us.
+constexpr int64_t kSmallUnits = 1280;
+// ... whose workgroups hold the general stages' LDS (general_lds bytes), or
+// the quotients' (quot_lds, for one point and one buffer) and then a flag.
+constexpr size_t kSmallFlagBytes = 16;
+size_t small_lds_bytes(size_t general_lds, size_t quot_lds);
+// Whether a call of `units` pairs runs in one launch.  Tables of the quotients
+// may fill the LDS without the flag (n = 512, m = 512, d = 8 in
+// double-double): two launches then, whatever the number of pairs.
+bool single_launch(int64_t units, size_t general_lds, size_t quot_lds);
+
 // Whether the power table needs the entry 1 (see QuotTables::pad), and the
 // most monomials of a polynomial without its folded constant.
 void quot_shape(const CsrView &S, bool &pad, int64_t &max_m);

@@ -16,6 +16,16 @@ size_t quot_lds_bytes(int n_vars, int max_exp, bool pad, int CH, bool multi, int
     return values * (size_t)words * sizeof(double);
 }
 
+size_t small_lds_bytes(size_t general_lds, size_t quot_lds)
+{
+    return std::max(general_lds, quot_lds + kSmallFlagBytes);
+}
+
+bool single_launch(int64_t units, size_t general_lds, size_t quot_lds)
+{
+    return units <= kSmallUnits && small_lds_bytes(general_lds, quot_lds) <= kLdsBytes;
+}
+
 int quot_chunk(int n_vars, int max_exp, bool pad, int64_t max_m, int words)
 {
     if (max_exp > kMaxQuotExp || n_vars >= 0xFFFF || (int64_t)max_exp * n_vars >= 0xFFFF ||

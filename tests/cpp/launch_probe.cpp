@@ -1,0 +1,21 @@
+// Test-only shim: the host functions that size the launches of the quotient
+// kernels (quotient_tables.cpp).  Built with g++ by the tests.
+#include "quotient.hpp"
+
+extern "C" {
+
+int lp_chunk(int n_vars, int max_exp, int pad, int64_t max_m, int words)
+{
+    return pe::quot_chunk(n_vars, max_exp, pad != 0, max_m, words);
+}
+
+int64_t lp_lds(int n_vars, int max_exp, int pad, int CH, int multi, int nbuf, int words)
+{
+    return (int64_t)pe::quot_lds_bytes(n_vars, max_exp, pad != 0, CH, multi != 0, nbuf, words);
+}
+
+int64_t lp_small_lds(int64_t general, int64_t quot) { return (int64_t)pe::small_lds_bytes(general, quot); }
+
+int lp_single(int64_t units, int64_t general, int64_t quot) { return pe::single_launch(units, general, quot); }
+
+}  // extern "C"
