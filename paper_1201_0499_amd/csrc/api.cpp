@@ -26,6 +26,7 @@
 #include "polyeval.h"
 #include "eval.hpp"
 #include "internal.hpp"
+#include "launch_limits.hpp"
 #include "newton.hpp"
 #include "quotient_args.hpp"
 #include "schedule.hpp"
@@ -548,8 +549,7 @@ hipError_t System::run_quot(const Quot &q, int prec, int cc, int maxt, EvalArgs 
         qa.by_point = 0;
     }
     const int64_t work = qa.by_point ? (tiles + 7) / 8 * 8 * qa.blocks : tiles * ((qa.blocks + 7) / 8 * 8);
-    hipError_t e = launch_quot(prec, T, qa, dim3((unsigned)std::min<int64_t>(work, 1 << 30)), (unsigned)nt,
-                               qlds, hs);
+    hipError_t e = launch_quot(prec, T, qa, dim3((unsigned)strided_grid(work, nt)), (unsigned)nt, qlds, hs);
     if (e != hipSuccess) return e;
     return launch_eval(prec, cc, maxt, a, rgrid, dim3(threads), lds, hs);
 }

@@ -1,5 +1,6 @@
 // Test-only shim: the host functions that size the launches of the quotient
-// kernels (quotient_tables.cpp).  Built with g++ by the tests.
+// kernels (quotient_tables.cpp, launch_limits.hpp).  Built with g++ by the tests.
+#include "launch_limits.hpp"
 #include "quotient.hpp"
 
 extern "C" {
@@ -17,5 +18,9 @@ int64_t lp_lds(int n_vars, int max_exp, int pad, int CH, int multi, int nbuf, in
 int64_t lp_small_lds(int64_t general, int64_t quot) { return (int64_t)pe::small_lds_bytes(general, quot); }
 
 int lp_single(int64_t units, int64_t general, int64_t quot) { return pe::single_launch(units, general, quot); }
+
+int64_t lp_max_workgroups(int threads) { return pe::max_workgroups(threads); }
+
+int64_t lp_strided_grid(int64_t work, int threads) { return pe::strided_grid(work, threads); }
 
 }  // extern "C"

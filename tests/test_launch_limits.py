@@ -1,5 +1,5 @@
 """Host functions that size the launches of the quotient kernels
-(quotient_tables.cpp), checked on the CPU against the hardware's limits.
+(quotient_tables.cpp, launch_limits.hpp), checked on the CPU against the hardware's limits.
 """
 import ctypes as C
 import os
@@ -26,6 +26,8 @@ def probe():
     for name in ("lp_small_lds", "lp_single"):
         getattr(L, name).argtypes = [C.c_int64] * (2 if name == "lp_small_lds" else 3)
     L.lp_small_lds.restype = C.c_int64
+    L.lp_max_workgroups.restype = L.lp_strided_grid.restype = C.c_int64
+    L.lp_strided_grid.argtypes = [C.c_int64, C.c_int]
     return L
 
 
@@ -65,3 +67,12 @@ def test_single_launch_fits_the_lds(probe, words):
                             assert quot > LDS - 16
                     assert not probe.lp_single(1281, 0, quot)
     assert taken and refused
+
+
+@pytest.mark.parametrize("threads", [64, 128, 192, 256, 512, 1024])
+def test_grids_stay_below_the_work_item_limit(probe, threads):
+    assert probe.lp_max_workgroups(threads) * threads < 2 ** 32 <= (probe.lp_max_workgroups(threads) + 1) * threads
+    for work in (8, 800, 2 ** 22, 2 ** 24, 2 ** 26, 2 ** 30, 2 ** 33):
+        g = probe.lp_strided_grid(work, threads)
+        assert g % 8 == 0 and 0 < g <= work and g * threads < 2 ** 32
+        assert g == work or work * threads >= 2 ** 32
