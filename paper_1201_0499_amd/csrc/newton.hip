@@ -18,6 +18,7 @@
 //             the FP64 solve for n <= 128 by Gauss-Jordan elimination with
 //             partial pivoting, the matrix in registers of one workgroup.
 //  update     x <- x - d in dd (or quad-double).
+#include <algorithm>
 #include <type_traits>
 #include <vector>
 
@@ -25,6 +26,7 @@
 #include "device.hpp"
 #include "eval.hpp"
 #include "newton.hpp"
+#include "launch_limits.hpp"
 #include "lds_budget.hpp"
 #include "packing.hpp"
 
@@ -1118,8 +1120,7 @@ __global__ __launch_bounds__((NCOL / CPT) * 64) void gj_panel_kernel(int64_t n_s
 // MI355X: n = 103, 256 starts 1447 -> 627 us, 1024 starts 4342 -> 2497 us; n =
 // 63, 1024 starts 1583 -> 488 us.
 template <int RPT, int CPT>
-__global__ __launch_bounds__(512) void gj_dd_kernel(int64_t n_starts, int32_t n, LuPlanes planes,
-                                                    int32_t *status)
+__global__ __launch_bounds__(512) void gj_dd_kernel(int32_t n, LuPlanes planes, int32_t *status)
 {
     using A = ArithDD;
     using C = A::C;
@@ -1329,13 +1330,22 @@ hipError_t launch_lu_solve(int prec, int64_t n_starts, int32_t n, double *const 
     }
     if (prec == 1 && n <= 103) {
         // as many columns as the registers hold; the register kernel is the
-        // faster one at every number of starts (64 to 1024 measured)
-        if (n <= 63)
-            hipLaunchKernelGGL((gj_dd_kernel<1, 8>), dim3((unsigned)n_starts), dim3(512), 0, stream,
-                               n_starts, n, pl, status);
-        else
-            hipLaunchKernelGGL((gj_dd_kernel<2, 13>), dim3((unsigned)n_starts), dim3(512), 0,
-                               stream, n_starts, n, pl, status);
+        // faster one at every number of starts (64 to 1024 measured).  In
+        // pieces of as many starts as a grid holds of its large workgroups.
+        const int64_t most = max_workgroups(512);
+        for (int64_t first = 0; first < n_starts; first += most) {
+            const dim3 grid((unsigned)std::min(most, n_starts - first));
+            LuPlanes p = pl;
+            for (int q = 0; q < 4; ++q) {
+                p.J[q] += first * n * n;
+                p.r[q] += first * n;
+                p.d[q] += first * n;
+            }
+            if (n <= 63)
+                hipLaunchKernelGGL((gj_dd_kernel<1, 8>), grid, dim3(512), 0, stream, n, p, status + first);
+            else
+                hipLaunchKernelGGL((gj_dd_kernel<2, 13>), grid, dim3(512), 0, stream, n, p, status + first);
+        }
         return hipGetLastError();
     }
     const size_t lds = (prec == 0 ? sizeof(Arith64::C) : sizeof(ArithDD::C)) * (size_t)nb * n;

@@ -39,3 +39,24 @@ def test_points_past_the_grid():
         assert float((got - (c0 * z + c1 * z ** 3)).abs().max()) < 64 * u
         got = torch.complex(J[0][i:i + step], J[2][i:i + step])[:, 0]
         assert float((got - (c0 + 3 * c1 * z ** 2)).abs().max()) < 128 * u
+
+
+def test_starts_past_the_grid_of_the_elimination():
+    """c0 x + c1 = 0 by the all-dd corrector from 2^23 + 5 starts: the
+    elimination's workgroups of 512 lanes take more than 2^32 work-items."""
+    P = 2 ** 23 + 5
+    c0, c1 = 0.6 + 0.8j, 1.0 + 0.5j
+    S = pe.System.from_csr(synth.system_from_lists(1, [[[(0, 1)], []]], [[c0, c1]]))
+    g = torch.Generator(device="cuda").manual_seed(5)
+    x = tuple(torch.rand(P, 1, dtype=torch.float64, device="cuda", generator=g) if q % 2 == 0
+              else torch.zeros(P, 1, dtype=torch.float64, device="cuda") for q in range(4))
+    res = torch.zeros(P, dtype=torch.float64, device="cuda")
+    it = torch.zeros(P, dtype=torch.int32, device="cuda")
+    st = torch.full((P,), 7, dtype=torch.int32, device="cuda")
+    print(f"[case] grid limit of the elimination, {P} starts", flush=True)
+    code = S.newton(P, x, res, it, st, tol=1e-24, max_iter=3, mode=pe.PE_NEWTON_DD)
+    torch.cuda.synchronize()
+    S.close()
+    assert code == 0 and int(st.abs().max()) == 0 and int(it.max()) == 1
+    root = -c1 / c0
+    assert float((torch.complex(x[0], x[2]) - root).abs().max()) < 8 * 2.0 ** -53
