@@ -124,8 +124,13 @@ pe_status pe_system_info(pe_system sys, int32_t *n_vars, int32_t *n_polys, int64
  * that keeps this as accurate as the forward and backward products of
  * Section 3.2; the other (polynomial, point) pairs (a coordinate of zero, very
  * large or small magnitudes, non-finite points) and systems with exponents
- * above 31 take those products.  The results of the former do not depend on
- * the schedule; pe_set_schedule and the autotuner choose that of the latter.
+ * above 31 take those products.  So do whole calls where they are the faster
+ * way: outputs that are sums of many terms each (monomials times variables
+ * per monomial, over n_vars), and some calls of few (polynomial, point)
+ * pairs, by a rule on the system's sizes, the precision, n_points and the
+ * monomials that the schedule takes at once.  The quotients' results depend
+ * on the system and the point alone, those of the products on the schedule
+ * too, which pe_set_schedule and the autotuner choose.
  *
  * Every output entry is written, including the exact zeros of the Jacobian
  * where a polynomial does not depend on a variable.  Results are
@@ -151,7 +156,7 @@ pe_status pe_eval_jac(pe_system sys, int64_t n_points, pe_cvec points, pe_cvec o
  * device or the host:
  *   - it uses only schedule tables that already exist: call pe_eval_jac
  *     once with the same n_points (or pin the schedule and call it once)
- *     beforehand, else PE_EUNSUPPORTED;
+ *     beforehand, in either precision, else PE_EUNSUPPORTED;
  *   - when the schedule splits a polynomial over workgroups (groups > 1),
  *     the partial rows live in a static device array of 32 MiB per device
  *     (n_points * n_polys * groups * (n_vars + 1) complex values, 32 bytes

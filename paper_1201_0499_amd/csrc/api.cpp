@@ -268,6 +268,11 @@ pe_status System::schedule_with(int L, int cc, int nt, int G, Schedule **out)
     sc->G = G;
     pe_status st = build_schedule(*this, *sc);
     if (st != PE_OK) return st;
+    // With its tables those of the quotient kernels, in both precisions, if
+    // any call can go by them: a call that may neither allocate nor upload
+    // (pe_eval_jac_noalloc, a captured one) then takes the same kernels.
+    for (int words : {2, 4})
+        if (!general_faster(words, INT64_MAX, 0)) (void)pack_quot(words);
     *out = sc.get();
     schedules.push_back(std::move(sc));
     return PE_OK;
@@ -309,23 +314,32 @@ void System::fill_args(const Schedule &sc, EvalArgs &a) const
     a.group_info = (const int4 *)sc.group_info.ptr;
 }
 
-// Tables of the quotient kernels, packed and uploaded once per chunk size.
-// nullptr leaves the call to the general kernel: also while hs is being
-// captured, when nothing may be uploaded, and if memory for them runs out.
+// The quotient tables if they are packed.  nullptr leaves the call to the
+// general kernel: also while hs is being captured, when nothing may be
+// uploaded, and if memory for them runs out.
 Quot *System::quot_for(int words, bool find_only, hipStream_t hs)
+{
+    if (!quot_ok) return nullptr;
+    const int CH = quot_chunk(n_vars, max_exp, quot_pad, quot_max_m, words);
+    for (auto &q : quots)
+        if (q->CH == CH) return q.get();
+    if (find_only || CH == 0) return nullptr;
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(hs, &cs) != hipSuccess) {
+        (void)hipGetLastError();
+        return nullptr;
+    }
+    return cs == hipStreamCaptureStatusNone ? pack_quot(words) : nullptr;
+}
+
+// Packed and uploaded once per chunk size.
+Quot *System::pack_quot(int words)
 {
     if (!quot_ok) return nullptr;
     const int CH = quot_chunk(n_vars, max_exp, quot_pad, quot_max_m, words);
     if (CH == 0) return nullptr;
     for (auto &q : quots)
         if (q->CH == CH) return q.get();
-    if (find_only) return nullptr;
-    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(hs, &cs) != hipSuccess) {
-        (void)hipGetLastError();
-        return nullptr;
-    }
-    if (cs != hipStreamCaptureStatusNone) return nullptr;
     try {
         QuotTables t;
         t.CH = CH;
@@ -843,13 +857,11 @@ pe_status pe_get_schedule(pe_system sys, int64_t n_points, int32_t *lanes, int32
     if (groups) *groups = G;
     if (tile_points || stage_buffers) {
         // the tile shape depends on the schedule's tables (their LDS size)
-        Schedule *had = nullptr, *sc = nullptr;
-        (void)S->find_schedule(n_points, &had);
+        Schedule *sc = nullptr;
         pe_status st = S->schedule_for(n_points, &sc);
         if (st != PE_OK) return st;
         int T = 1, nbuf = 1;
         S->launch_shape(*sc, n_points, true, T, nbuf);
-        if (!had) (void)S->quot_for(4, false, nullptr);  // packed with them
         if (tile_points) *tile_points = T;
         if (stage_buffers) *stage_buffers = nbuf;
     }

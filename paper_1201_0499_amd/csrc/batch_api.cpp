@@ -197,6 +197,7 @@ static pe_status build_batch(Batch &B, const std::vector<int64_t> &pps, hipStrea
         System &S = *B.sys[i];
         const int L = lanes_for(S.max_k, B.cfg);
         Schedule *sc = nullptr;
+        std::lock_guard<std::mutex> lock(S.mu);
         pe_status st = S.schedule_with(L, B.cfg.cc, B.cfg.nt, 1, &sc);
         if (st != PE_OK) return st;
         S.fill_args(*sc, descs[(size_t)i].a);
