@@ -763,7 +763,7 @@ pe_status pe_create_system(int32_t n_vars, int32_t n_polys, int64_t n_monos,
     for (int64_t s = 0; s < n_monos && S->quot_ok; ++s) {
         const double big = std::max(std::fabs(c[4 * s + 0]), std::fabs(c[4 * s + 2]));
         S->quot_ok = big == 0.0 ? c[4 * s + 1] == 0.0 && c[4 * s + 3] == 0.0
-                                : std::abs(std::ilogb(big)) < kProductExp;
+                                : std::abs(std::ilogb(big)) < kCoefExp;
     }
     quot_shape(CsrView{n_vars, n_polys, n_monos, poly_start, mono_start, pos, exp}, S->quot_pad, S->quot_max_m);
     if (hipGetDevice(&S->device) != hipSuccess) return fail(PE_EDEVICE, "hipGetDevice failed");

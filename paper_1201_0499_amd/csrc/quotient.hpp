@@ -40,18 +40,21 @@ constexpr int kMaxQuotChunk = 1024;  // monomials per chunk, at most (<= 2^kEntr
 
 // Range rules.  Partial products of a monomial (quads of factors apart) must
 // have a binary exponent within +-kProductExp, which the kernel checks; a
-// quad of factors is bounded beforehand, by the points: every |x_i| (larger
-// part) within 2^+-b, b from quot_point_exp.  With coefficients within
-// 2^+-kProductExp (or zero) no product, nor an error term of quad-double
-// arithmetic, overflows or becomes subnormal.
-constexpr int kProductExp = 300;
-constexpr int kQuadExp = 400;
+// quad of factors is bounded by the same beforehand, by the points: every
+// |x_i| (larger part) within 2^+-b, b from quot_point_exp.  So a single quad
+// passes the check wherever it is made, and what is refused does not depend on
+// how many lanes share a monomial.  With coefficients within 2^+-kCoefExp (or
+// zero) no product, nor an error term of quad-double arithmetic, overflows or
+// becomes subnormal: the smallest entry of J is 2^-(400 + 300 + 60), its error
+// terms 2^-212 of it.
+constexpr int kProductExp = 400;
+constexpr int kCoefExp = 300;
 
 // Largest binary exponent of a coordinate (either sign) for maximal exponent
-// d: kQuad factors of at most 2^(d (b + 1/2)) each stay within 2^kQuadExp.
+// d: kQuad factors of at most 2^(d (b + 1/2)) each stay within 2^kProductExp.
 inline int quot_point_exp(int d)
 {
-    const int b = (2 * kQuadExp / kQuad - d) / (2 * d);
+    const int b = (2 * kProductExp / kQuad - d) / (2 * d);
     return b < 0 ? 0 : (b > 60 ? 60 : b);
 }
 

@@ -380,7 +380,8 @@ __device__ __forceinline__ void quot_table(const QuotArgs &a, const QuotLds<A> &
 
 // Factors of one lane's monomial: the quads of words wp[0], wp[cnt], ...
 // (Q of them) in the canonical order (quotient.hpp).  Checked after every
-// product of quads: a factor there is a quad (within kQuadExp) or was checked.
+// product of quads: a factor there is a quad (within the same range, by the
+// points') or was checked.
 template <class A>
 struct Factors {
     using C = typename A::C;
