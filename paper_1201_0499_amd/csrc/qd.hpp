@@ -3,21 +3,24 @@
 // beside double double as the way to more accurate path tracking).
 //
 // A quad-double number is an unevaluated sum x0 + x1 + x2 + x3 of doubles of
-// decreasing magnitude, each of order u = 2^-53 of the one before.  The
-// operations add their terms order by order: the terms of order 0, 1 and 2
+// decreasing magnitude, each of order u = 2^-53 of the one before.  A sum
+// "distils" all eight components: passes of error-free vector summation from
+// the smallest entry up (each pass replaces the entries by their rounded
+// running sum and the TwoSum errors, so the exact total never changes), after
+// which the first four entries are the result's components.  Nothing else is
+// dropped: a sum that cancels is as exact as its operands.  (Adding order by
+// order as in a product, the last in FP64, is faster, but errs by up to
+// 0.97 u^4 (|a| + |b|) instead of 0.38, whatever cancels.)
+//
+// A complex product's terms are added order by order: the terms of order 0, 1 and 2
 // (of the result's size times u^0, u^1, u^2) with TwoSum, whose errors join
 // the terms of the next order, and the terms of order 3 in FP64 (the last of
-// them with TwoSum again, where its rounding would show).  The sums of the
-// orders are then "distilled": passes of error-free vector summation from the
-// smallest entry up (each pass replaces the entries by their rounded running
-// sum and the TwoSum errors, so the exact total never changes), after which
-// the first four entries are the result's components.  Dropped or rounded are
-//   - in a sum: nothing but the FP64 sums of order 3;
-//   - in a product: the products x_i y_j with i + j >= 4 and the rounding of
-//     the terms of order 3 (x_i y_j with i + j = 3, the TwoProduct errors of
-//     order 2 and the TwoSum errors of order 3),
-// all below a small multiple of u^4 |x||y|; so each operation errs by a small
-// multiple of u^4 = 2^-212 relative to the magnitudes involved, plus what the
+// them with TwoSum again, where its rounding would show); then the sums of the
+// orders are distilled.  Dropped or rounded are the products x_i y_j with
+// i + j >= 4 and the rounding of the terms of order 3 (x_i y_j with i + j = 3,
+// the TwoProduct errors of order 2 and the TwoSum errors of order 3), all below
+// a small multiple of u^4 |x||y|.  So each operation errs by a small multiple
+// of u^4 = 2^-212 relative to the magnitudes involved, plus what the
 // distillation leaves, of the same order.  The tests check the operations and
 // the evaluation against exact rationals.
 //
@@ -80,11 +83,8 @@ PE_HD qd qd_neg(const qd &a) { return {-a.x0, -a.x1, -a.x2, -a.x3}; }
 
 PE_HD qd qd_add(const qd &a, const qd &b)
 {
-    const dd t0 = two_sum(a.x0, b.x0), t1 = two_sum(a.x1, b.x1), t2 = two_sum(a.x2, b.x2);
-    const dd u1 = two_sum(t1.hi, t0.lo);
-    const dd u2 = two_sum(t2.hi, t1.lo), v2 = two_sum(u2.hi, u1.lo);
-    double e[4] = {t0.hi, u1.hi, v2.hi, (a.x3 + b.x3) + (t2.lo + (u2.lo + v2.lo))};
-    return distill<4>(e);
+    double e[8] = {a.x0, b.x0, a.x1, b.x1, a.x2, b.x2, a.x3, b.x3};
+    return distill<8>(e);
 }
 
 // the significant terms of a * b: nine exact leading terms (products and
