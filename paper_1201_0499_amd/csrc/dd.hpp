@@ -221,6 +221,35 @@ struct ArithDD {
         dd r = dw_recip(den);
         return {dw_mul(b.re, r), dw_neg(dw_mul(b.im, r))};
     }
+    // 1 / b with an error below 2.5 u^2 |1/b| (0.18 u^2 root mean square, inv
+    // 0.88): y0 = 1 / b in FP64, then y0 + y0 (e + e^2) with e = 1 - b y0,
+    // whose terms of order u are added by TwoSum
+    PE_HD static C recip(C b)
+    {
+        const double den = fma(b.re.hi, b.re.hi, b.im.hi * b.im.hi), r = 1.0 / den;
+        const double p = b.re.hi * r, q = -b.im.hi * r;  // y0 = p + i q
+        dd er = one_minus(1.0, b.re, p, dw_neg(b.im), q), ei = one_minus(0.0, b.re, q, b.im, p);
+        er.lo += fma(er.hi, er.hi, -ei.hi * ei.hi);
+        ei.lo += 2.0 * er.hi * ei.hi;
+        return {plus_products(p, p, er, -q, ei), plus_products(q, p, ei, q, er)};
+    }
+    // one - u p - v q, where nothing of order 1 is left
+    PE_HD static dd one_minus(double one, dd u, double p, dd v, double q)
+    {
+        const dd a = two_prod(-u.hi, p), b = two_prod(-v.hi, q);
+        const dd s = two_sum(one, a.hi), t = two_sum(s.hi, b.hi);
+        const dd c = two_sum(s.lo, t.lo), d = two_sum(a.lo, b.lo), f = two_sum(-u.lo * p, -v.lo * q);
+        const dd g = two_sum(c.hi, d.hi), h = two_sum(g.hi, f.hi), k = two_sum(t.hi, h.hi);
+        return fast_two_sum(k.hi, k.lo + ((c.lo + d.lo) + (f.lo + (g.lo + h.lo))));
+    }
+    // y + p u + q v for u and v of order 2^-53
+    PE_HD static dd plus_products(double y, double p, dd u, double q, dd v)
+    {
+        const dd a = two_prod(p, u.hi), b = two_prod(q, v.hi), s = two_sum(a.hi, b.hi);
+        const double lo = s.lo + (a.lo + b.lo) + fma(p, u.lo, q * v.lo);
+        const dd t = two_sum(y, s.hi);
+        return fast_two_sum(t.hi, t.lo + lo);
+    }
     // cheap magnitude for pivot choice
     PE_HD static double mag(C a) { return fabs(a.re.hi) + fabs(a.im.hi); }
 };
@@ -263,6 +292,19 @@ struct Arith64 {
         double den = fma(b.re, b.re, b.im * b.im);
         double r = 1.0 / den;
         return {b.re * r, -b.im * r};
+    }
+    // 1 / b within u |1/b| of about the rounding of its parts (0.35 u root mean
+    // square, inv 0.83): y + y (1 - b y), the difference exactly to order u
+    PE_HD static C recip(C b)
+    {
+        const C y = inv(b);
+        const double er = one_minus(1.0, b.re, y.re, -b.im, y.im), ei = one_minus(0.0, b.re, y.im, b.im, y.re);
+        return {y.re + fma(y.re, er, -y.im * ei), y.im + fma(y.re, ei, y.im * er)};
+    }
+    PE_HD static double one_minus(double one, double u, double p, double v, double q)
+    {
+        const dd a = two_prod(-u, p), b = two_prod(-v, q), s = two_sum(one, a.hi), t = two_sum(s.hi, b.hi);
+        return t.hi + ((s.lo + t.lo) + (a.lo + b.lo));
     }
     PE_HD static double mag(C a) { return fabs(a.re) + fabs(a.im); }
 };

@@ -255,9 +255,9 @@ struct RunAcc<ArithQD> {
     __device__ __forceinline__ ArithQD::C get() const { return {sum(re), sum(im)}; }
 };
 
-// 1 / x
-__device__ __forceinline__ Arith64::C quot_inv(const Arith64::C &x) { return Arith64::inv(x); }
-__device__ __forceinline__ ArithDD::C quot_inv(const ArithDD::C &x) { return ArithDD::inv(x); }
+// 1 / x, an error of which every derivative by x would have whole
+__device__ __forceinline__ Arith64::C quot_inv(const Arith64::C &x) { return Arith64::recip(x); }
+__device__ __forceinline__ ArithDD::C quot_inv(const ArithDD::C &x) { return ArithDD::recip(x); }
 // from the double-double reciprocal y, with e = 1 - x y of order 2^-103:
 // y + y (e + e^2), the rest e^3
 __device__ __forceinline__ ArithQD::C quot_inv(const ArithQD::C &x)
