@@ -294,17 +294,15 @@ struct Arith64 {
         return {b.re * r, -b.im * r};
     }
     // 1 / b within u |1/b| of about the rounding of its parts (0.35 u root mean
-    // square, inv 0.83): y + y (1 - b y), the difference exactly to order u
+    // square, inv 0.83): conj(b) times r + s, r = 1 / |b|^2 in FP64 and s its
+    // correction from |b|^2 to order u
     PE_HD static C recip(C b)
     {
-        const C y = inv(b);
-        const double er = one_minus(1.0, b.re, y.re, -b.im, y.im), ei = one_minus(0.0, b.re, y.im, b.im, y.re);
-        return {y.re + fma(y.re, er, -y.im * ei), y.im + fma(y.re, ei, y.im * er)};
-    }
-    PE_HD static double one_minus(double one, double u, double p, double v, double q)
-    {
-        const dd a = two_prod(-u, p), b = two_prod(-v, q), s = two_sum(one, a.hi), t = two_sum(s.hi, b.hi);
-        return t.hi + ((s.lo + t.lo) + (a.lo + b.lo));
+        const dd p = two_prod(b.re, b.re), q = two_prod(b.im, b.im), den = two_sum(p.hi, q.hi);
+        const double r = 1.0 / den.hi;
+        const double s = r * fma(-(den.lo + (p.lo + q.lo)), r, fma(-den.hi, r, 1.0));
+        const dd re = two_prod(b.re, r), im = two_prod(-b.im, r);
+        return {re.hi + fma(b.re, s, re.lo), im.hi + fma(-b.im, s, im.lo)};
     }
     PE_HD static double mag(C a) { return fabs(a.re) + fabs(a.im); }
 };
