@@ -272,7 +272,7 @@ pe_status System::schedule_with(int L, int cc, int nt, int G, Schedule **out)
     // any call can go by them: a call that may neither allocate nor upload
     // (pe_eval_jac_noalloc, a captured one) then takes the same kernels.
     for (int words : {2, 4})
-        if (!general_faster(words, INT64_MAX, 0)) (void)pack_quot(words);
+        if (!general_faster(words, 1, 0) || !general_faster(words, INT64_MAX, 0)) (void)pack_quot(words);
     *out = sc.get();
     schedules.push_back(std::move(sc));
     return PE_OK;
@@ -520,7 +520,22 @@ hipError_t System::run_quot(const Quot &q, int prec, int cc, int maxt, EvalArgs 
     const auto lds_for = [&](int T, int nbuf) {
         return quot_lds_bytes(n_vars, max_exp, quot_pad, q.CH, q.multi, nbuf, T * words);
     };
-    if (single_launch(units, lds, lds_for(1, 1))) {
+    // workgroups of one polynomial each, many of whose outputs have no terms
+    const int64_t terms = quot_max_m * max_k;
+    const bool sparse = jac && prec != 2 && !q.multi && (n_vars < 200 ? 2 * terms <= n_vars : terms < 2 * n_vars);
+    const int64_t most = single_launch_units(n_vars, max_k, quot_max_m, words, jac);
+    if (single_launch(units, most, lds, lds_for(1, 1))) {
+        qa.sparse = sparse;
+        // At least a lane for each variable's powers and reciprocal, as far as
+        // the chip's registers hold the workgroups at once, whatever the
+        // general stages' schedule needs for its monomials (n = 300, m = 16, k
+        // = 8, one point in double-double: 16.2 us on that schedule's 64
+        // lanes, 9.9 us on 256; 3 points 20.1 us, on 128 lanes 16.6 us, on 256
+        // 19.3 us).
+        if (prec != 2) {
+            const unsigned want = std::min((n_vars + 63) / 64 * 64, units <= 512 ? 256 : 128);
+            threads = std::max(threads, want);
+        }
         few_lanes(qa, m, (int)threads);
         return launch_small(prec, cc, maxt, a, qa, dim3((unsigned)n_polys, (unsigned)P, 1), threads,
                             small_lds_bytes(lds, lds_for(1, 1)), hs);
@@ -558,6 +573,7 @@ hipError_t System::run_quot(const Quot &q, int prec, int cc, int maxt, EvalArgs 
     if (prec == 0 && m * (int64_t)max_k < n_vars) pp = 1;
     qa.blocks = (n_polys + pp - 1) / pp;
     qa.by_point = 1;
+    qa.sparse = sparse && pp == 1;
     if (n_polys >= 256 || tiles < 16) {
         qa.blocks = std::max(qa.blocks, std::min(n_polys, 64));
         qa.by_point = 0;

@@ -77,7 +77,7 @@ __global__ __launch_bounds__(kQuotMaxThreads<A>) void quot_kernel(const QuotArgs
         if (!live) continue;
         if (!first) __syncthreads();  // the previous points are done with LDS
         first = false;
-        quot_table<A>(a, lds, pt, npt, true);
+        quot_table<A>(a, lds, pt, npt, block, true);
         __syncthreads();
         int vo = 0;
         for (int p = block; p < a.n_polys; p += a.blocks) quot_poly<A, false>(a, lds, pt, live, p, vo, true, [] {});
@@ -107,7 +107,7 @@ __global__ __launch_bounds__(kQuotMaxThreads<A>) void quot_values_kernel(const Q
         if (!live) continue;
         if (!first) __syncthreads();  // the previous points are done with LDS
         first = false;
-        quot_table<A>(a, lds, pt, npt, false);
+        quot_table<A>(a, lds, pt, npt, 0, false);
         __syncthreads();
         for (int p = p0 + wave; p < p1; p += nw) quot_value<A>(a, lds.u, pt, live, p);
     }
@@ -140,7 +140,7 @@ __global__ __launch_bounds__(kQuotMaxThreads<A>) void quot_batch_kernel(const Qu
         double2 *end;
         const QuotLds<A> lds = quot_lds<A>(lds_raw, a, end);
         __syncthreads();  // the previous task is done with LDS
-        quot_table<A>(a, lds, task.pt, 1, JAC);
+        quot_table<A>(a, lds, task.pt, 1, 0, JAC);
         __syncthreads();
         if constexpr (JAC) {
             int vo = 0;

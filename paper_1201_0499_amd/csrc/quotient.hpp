@@ -98,16 +98,27 @@ size_t quot_lds_bytes(int n_vars, int max_exp, bool pad, int CH, bool multi, int
 // Calls of at most this many (polynomial, point) pairs run in one launch
 // (small.hip): five workgroups per CU.  One MI355X, two launches against one:
 // n = 350, m = 69, k = 8, 3 points in FP64 17.5 and 14.7 us, n = 16, m = 64, k
-// = 16, 128 points (2048 pairs) 17 and 18.3 us.
+// = 16, 128 points (2048 pairs) 17 and 18.3 us.  With the Jacobian, where most
+// outputs of many have no or one term, so that the table and the stores are
+// the work, up to kSparseUnits pairs (two launches against one): double-double,
+// n = 400, m = 8, k = 2, 5 points 36.5 and 28.3 us, 35 points 161 and 151 us, n
+// = 300, m = 200, k = 2, 23 points 94 and 82 us, n = 128, m = 8, k = 2, 20
+// points 27 and 23 us, n = 300, m = 60, k = 4, 8 points 41 and 36 us; FP64, n =
+// 400, m = 8, k = 2, 35 points 89 and 71 us, m = 60, k = 6, 5 points 26 and 19
+// us, n = 500, m = 60, k = 12, 3 points 24 and 20 us; but n = 300, m = 60, k = 6,
+// 13 points in double-double 56 and 69 us, and n = 128, m = 8, k = 2, 54 points
+// 41 and 53 us.
 constexpr int64_t kSmallUnits = 1280;
+constexpr int64_t kSparseUnits = 16384;
+int64_t single_launch_units(int n_vars, int max_k, int64_t max_m, int words, bool jac);
 // ... whose workgroups hold the general stages' LDS (general_lds bytes), or
 // the quotients' (quot_lds, for one point and one buffer) and then a flag.
 constexpr size_t kSmallFlagBytes = 16;
 size_t small_lds_bytes(size_t general_lds, size_t quot_lds);
-// Whether a call of `units` pairs runs in one launch.  Tables of the quotients
-// may fill the LDS without the flag (n = 512, m = 512, d = 8 in
-// double-double): two launches then, whatever the number of pairs.
-bool single_launch(int64_t units, size_t general_lds, size_t quot_lds);
+// Whether a call of `units` pairs, of at most `most`, runs in one launch.
+// Tables of the quotients may fill the LDS without the flag (n = 512, m = 512,
+// d = 8 in double-double): two launches then, whatever the number of pairs.
+bool single_launch(int64_t units, int64_t most, size_t general_lds, size_t quot_lds);
 
 // Whether the power table needs the entry 1 (see QuotTables::pad), and the
 // most monomials of a polynomial without its folded constant.

@@ -16,6 +16,8 @@ struct QuotArgs {
     int32_t pad;         // 1: the power table ends with the entry 1
     int32_t CH;          // monomials per chunk
     int32_t n_blk;       // rank blocks per chunk
+    int32_t sparse;      // workgroups of one polynomial each, with few terms for its
+                         //   variables: see quot_table
     int32_t multi;       // some polynomial has more than one chunk
     int32_t log2L;       // lanes per monomial: 1, 2 or 4
     int32_t log2S;       // lanes per run of terms: 1, 2 or 4

@@ -346,16 +346,35 @@ __device__ __forceinline__ QuotLds<A> quot_lds(double2 *raw, const QuotArgs &a, 
 
 // The power table and the reciprocals of points pt .. pt+npt-1 (callers add
 // the barrier).  A coordinate out of range becomes NaN in the table: the
-// values of the polynomials that contain it then are NaN too.
+// values of the polynomials that contain it then are NaN too.  With a.sparse
+// only the variables that share a block of ranks with one of polynomial p, its
+// only one: what no term reads stays unset, and what multiplies no terms is 1.
 template <class A>
-__device__ __forceinline__ void quot_table(const QuotArgs &a, const QuotLds<A> &lds, int64_t pt, int npt,
+__device__ __forceinline__ void quot_table(const QuotArgs &a, const QuotLds<A> &lds, int64_t pt, int npt, int p,
                                            bool jac)
 {
     using C = typename A::C;
     using P = Pts<A>;
     using One = typename P::One;
     const int n = a.n_vars, NT = (int)blockDim.x;
-    for (int i = (int)threadIdx.x; i < n; i += NT) {
+    int4 pl = make_int4(0, 0, 0, 0), ck = pl;
+    int count = n;
+    if (a.sparse) {
+        pl = uniform_int4(a.poly + p);
+        if (pl.x == pl.y) return;
+        ck = uniform_int4(a.chunk + pl.x);
+        count = a.n_blk * kRankBlock;
+    }
+    for (int j = (int)threadIdx.x; j < count; j += NT) {
+        int i = j;
+        if (a.sparse) {
+            i = (int)a.out[(int64_t)pl.x * count + j];
+            if (i >= n) continue;
+            if (a.block[ck.w + j / kRankBlock].y == 0) {
+                if (jac) lds.y.put(i, A::one());
+                continue;
+            }
+        }
         C x, y;
 #pragma unroll
         for (int t = 0; t < P::T; ++t) {

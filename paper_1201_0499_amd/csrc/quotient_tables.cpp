@@ -21,9 +21,23 @@ size_t small_lds_bytes(size_t general_lds, size_t quot_lds)
     return std::max(general_lds, quot_lds + kSmallFlagBytes);
 }
 
-bool single_launch(int64_t units, size_t general_lds, size_t quot_lds)
+int64_t single_launch_units(int n_vars, int max_k, int64_t max_m, int words, bool jac)
 {
-    return units <= kSmallUnits && small_lds_bytes(general_lds, quot_lds) <= kLdsBytes;
+    const int64_t terms = max_m * max_k;
+    if (!jac || words == 8 || n_vars < 100) return kSmallUnits;
+    if (max_k <= 2) {
+        const bool less = n_vars < 200 || (words == 4 && n_vars >= 450 && 2 * terms >= n_vars);
+        return less ? kSparseUnits / 4 : kSparseUnits;
+    }
+    if (n_vars < 200) return kSmallUnits;
+    if (4 * terms <= n_vars) return kSparseUnits;
+    const bool few = 2 * terms <= n_vars || (n_vars >= 300 && terms <= n_vars) || (n_vars >= 400 && terms < 2 * n_vars);
+    return few ? kSparseUnits / 4 : kSmallUnits;
+}
+
+bool single_launch(int64_t units, int64_t most, size_t general_lds, size_t quot_lds)
+{
+    return units <= most && small_lds_bytes(general_lds, quot_lds) <= kLdsBytes;
 }
 
 int quot_chunk(int n_vars, int max_exp, bool pad, int64_t max_m, int words)

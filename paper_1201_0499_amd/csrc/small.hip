@@ -28,7 +28,7 @@ small_kernel(const EvalArgs a, const QuotArgs qa)
         int *const flag = reinterpret_cast<int *>(end);
         if (threadIdx.x == 0) *flag = 0;
         const bool jac = qa.J[0] != nullptr;
-        quot_table<A>(qa, lds, pt, 1, jac);
+        quot_table<A>(qa, lds, pt, 1, p, jac);
         __syncthreads();
         int vo = 0;
         quot_poly<A, true>(qa, lds, pt, 1u, p, vo, jac, [&] { *flag = 1; });

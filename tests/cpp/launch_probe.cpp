@@ -17,7 +17,15 @@ int64_t lp_lds(int n_vars, int max_exp, int pad, int CH, int multi, int nbuf, in
 
 int64_t lp_small_lds(int64_t general, int64_t quot) { return (int64_t)pe::small_lds_bytes(general, quot); }
 
-int lp_single(int64_t units, int64_t general, int64_t quot) { return pe::single_launch(units, general, quot); }
+int lp_single(int64_t units, int64_t general, int64_t quot)
+{
+    return pe::single_launch(units, pe::kSmallUnits, general, quot);
+}
+
+int64_t lp_single_units(int n_vars, int max_k, int64_t max_m, int words, int jac)
+{
+    return pe::single_launch_units(n_vars, max_k, max_m, words, jac != 0);
+}
 
 int64_t lp_max_workgroups(int threads) { return pe::max_workgroups(threads); }
 

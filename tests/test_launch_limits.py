@@ -25,6 +25,8 @@ def probe():
     L.lp_lds.restype = C.c_int64
     for name in ("lp_small_lds", "lp_single"):
         getattr(L, name).argtypes = [C.c_int64] * (2 if name == "lp_small_lds" else 3)
+    L.lp_single_units.restype = C.c_int64
+    L.lp_single_units.argtypes = [C.c_int, C.c_int, C.c_int64, C.c_int, C.c_int]
     L.lp_small_lds.restype = C.c_int64
     L.lp_max_workgroups.restype = L.lp_strided_grid.restype = C.c_int64
     L.lp_strided_grid.argtypes = [C.c_int64, C.c_int]
@@ -76,3 +78,17 @@ def test_grids_stay_below_the_work_item_limit(probe, threads):
         g = probe.lp_strided_grid(work, threads)
         assert g % 8 == 0 and 0 < g <= work and g * threads < 2 ** 32
         assert g == work or work * threads >= 2 ** 32
+
+
+def test_single_launch_units(probe):
+    """Only with the Jacobian, and for systems of many variables of which most
+    outputs have no or one term."""
+    for n, k, m, units in ((99, 2, 8, 1280), (100, 2, 8, 4096), (199, 2, 900, 4096), (200, 2, 900, 16384),
+                           (199, 4, 2, 1280), (200, 4, 12, 16384), (200, 4, 13, 4096), (200, 4, 25, 4096),
+                           (200, 4, 26, 1280), (300, 4, 75, 4096), (300, 4, 76, 1280), (299, 4, 74, 1280),
+                           (400, 4, 199, 4096), (400, 4, 200, 1280), (449, 2, 900, 16384), (450, 2, 113, 4096),
+                           (450, 2, 112, 16384)):
+        assert probe.lp_single_units(n, k, m, 4, 1) == units
+        assert probe.lp_single_units(n, k, m, 2, 1) == (16384 if (n, k, m) == (450, 2, 113) else units)
+        for words, jac in ((2, 0), (4, 0), (8, 1)):
+            assert probe.lp_single_units(n, k, m, words, jac) == 1280
