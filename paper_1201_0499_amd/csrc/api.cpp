@@ -387,6 +387,7 @@ void System::fill_quot(const Quot &q, QuotArgs &a) const
     a.pad = quot_pad;
     a.CH = q.CH;
     a.n_blk = q.n_blk;
+    a.pairs = max_k <= 2;
     a.multi = q.multi;
     a.PP = 1;
     a.nbuf = 1;
@@ -405,11 +406,12 @@ void System::fill_quot(const Quot &q, QuotArgs &a) const
 }
 
 // Lanes per monomial (of at most m in a chunk) and per run on nt threads in
-// calls of few workgroups: as many as fit one round.
+// calls of few workgroups: as many as fit one round.  (Two factors leave a
+// second lane nothing to do.)
 static void few_lanes(QuotArgs &a, int m, int nt)
 {
     const int ranks = a.n_blk * kRankBlock;
-    a.log2L = m * 4 <= nt ? 2 : (m * 2 <= nt ? 1 : 0);
+    a.log2L = a.pairs ? 0 : (m * 4 <= nt ? 2 : (m * 2 <= nt ? 1 : 0));
     a.log2S = ranks * 4 <= nt ? 2 : (ranks * 2 <= nt ? 1 : 0);
 }
 
@@ -417,12 +419,17 @@ static void few_lanes(QuotArgs &a, int m, int nt)
 // per run, whose reads of the values the packer spread over the LDS banks.
 // Runs of fewer than four terms on average are mostly latency, which more
 // workgroups hide better than more lanes: then 256 are enough (n = 292, m =
-// 37, k = 15, 2 points in double-double: 20 us at 512 lanes, 15.7 us).
-int System::quot_lanes(const Quot &q) const
+// 37, k = 15, 2 points in double-double: 20 us at 512 lanes, 15.7 us).  But
+// where the LDS holds three workgroups at most (per_cu) the table, with its
+// reciprocals, is most of the work of short monomials, and wants the lanes
+// (double-double, n = 512, m = 200, k = 2, 78 points 726 us at 256, 560 us; n =
+// 512, m = 20, k = 16, 27 points 247 us, at 512 265 us).
+int System::quot_lanes(const Quot &q, int words, int per_cu) const
 {
     const int m = (int)std::max<int64_t>(1, std::min<int64_t>(quot_max_m, q.CH));
     const int sums = q.n_blk * kRankBlock * 2;
-    return std::max(m, quot_max_m * max_k >= 4 * (int64_t)n_vars ? sums : std::min(sums, 256));
+    const bool many = quot_max_m * max_k >= 4 * (int64_t)n_vars || (words == 4 && max_k <= 2 && per_cu <= 3);
+    return std::max(m, many ? sums : std::min(sums, 256));
 }
 
 // Workgroup size: the smallest that fills the CU's registers (cap threads)
@@ -450,12 +457,13 @@ int quot_threads(int lanes, size_t lds, int64_t workgroups, int cap)
 //   as short a chain: n = 16, m = 256, k = 16, one point in double-double 15.3
 //   and 17.1 us, in quad-double 63 and 71 us; n = 32, m = 256, k = 8, 32
 //   points in FP64 12.6 and 13.7 us.
-// * Monomials of two variables, which save the least, in calls whose
-//   workgroups build a power table, with its reciprocals, for one or two
-//   polynomials each: double-double, n = 186, m = 274, 29 points 88 and 97 us;
-//   but n = 11, m = 147, 719 points (7909 pairs) 69 and 48 us; quad-double, n
-//   = 11, m = 8, 4 points 27.7 and 29.7 us; but n = 52, m = 185, 7 points 44
-//   and 36 us.
+// * Monomials of two variables, which save the least, in quad-double calls
+//   whose workgroups build a power table, with its reciprocals, for one or two
+//   polynomials each: n = 11, m = 8, 4 points 27.7 and 29.7 us; but n = 52, m =
+//   185, 7 points 44 and 36 us.
+// * The same in double-double for very many variables and a few points: n =
+//   500, m = 8, 3 points 29 and 31 us, 8 points 61 and 71 us; but one point 16
+//   and 12 us, and n = 400, 5 points 31 and 28 us.
 // The same with and without the Jacobian, so that both give the same values
 // bit for bit.
 bool System::general_faster(int words, int64_t units, int64_t chunk) const
@@ -464,7 +472,8 @@ bool System::general_faster(int words, int64_t units, int64_t chunk) const
     const bool small = units <= kSmallUnits;
     if (small && quot_max_m <= chunk && (words == 2 ? run >= 64 && n_vars <= 32 : run > 192 && n_vars < 18))
         return true;
-    if (max_k <= 2 && (words == 4 ? units <= 6144 : words == 8 && small && run < 3)) return true;
+    if (max_k <= 2 && words == 8 && small && run < 3) return true;
+    if (max_k <= 2 && words == 4 && !small && units <= 6144 && n_vars >= 450) return true;
     if (words == 2) return run > 64 && n_vars < 24;
     return words == 4 && run > 64 && n_vars < 12 && quot_max_m > 512;
 }
@@ -557,7 +566,7 @@ hipError_t System::run_quot(const Quot &q, int prec, int cc, int maxt, EvalArgs 
     if (lds_for(T, 2) <= (size_t)kMaxLds) qa.nbuf = 2;
     const size_t qlds = lds_for(T, qa.nbuf);
     const int per_cu = (int)std::max<size_t>(1, kMaxLds / qlds);
-    const int nt = quot_threads(quot_lanes(q), qlds, tiles * n_polys, cap);
+    const int nt = quot_threads(quot_lanes(q, words, per_cu), qlds, tiles * n_polys, cap);
     // several polynomials per workgroup share one power table, while the
     // workgroups still make eight rounds of the chip.  With at least 256
     // polynomials, or few points, each XCD takes neighbouring ones of several

@@ -145,7 +145,7 @@ static void build_quot(Batch &B, const std::vector<BatchDesc> &descs, const std:
         };
         lds1 = std::max(lds1, lds(1));
         lds2 = std::max(lds2, lds(2));
-        lanes = std::max(lanes, S.quot_lanes(*q));
+        lanes = std::max(lanes, S.quot_lanes(*q, words, (int)((size_t)kMaxLds / lds(1))));
         items += pps[(size_t)i] * S.n_polys;
         terms += (double)pps[(size_t)i] * (double)system_terms(S);
     }

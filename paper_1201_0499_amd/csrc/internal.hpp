@@ -111,7 +111,7 @@ struct System {
     // packed yet) and cannot be made
     Quot *quot_for(int words, bool find_only, hipStream_t hs);
     Quot *pack_quot(int words);
-    int quot_lanes(const Quot &q) const;
+    int quot_lanes(const Quot &q, int words, int per_cu) const;
     bool general_faster(int words, int64_t units, int64_t chunk) const;
     // launch arguments of the quotient kernels (points, outputs, mask and
     // launch shape unset)

@@ -118,7 +118,7 @@ __global__ __launch_bounds__(kQuotMaxThreads<A>) void quot_values_kernel(const Q
 // kernels are refused whole.  24 systems of up to 160 variables and 512
 // monomials, 24 points each in double-double: 2108 us by the general kernel,
 // 1510 us with that kernel's coarse tasks and the descriptors in vector
-// registers, 887 us.
+// registers, 876 us.
 template <class A, bool JAC>
 __global__ __launch_bounds__(kQuotMaxThreads<A>) void quot_batch_kernel(const QuotBatchArgs b)
 {

@@ -433,8 +433,14 @@ struct Factors {
         return p;
     }
     // product of all ranges by one lane
-    __device__ __forceinline__ C all() const
+    __device__ __forceinline__ C all(bool pairs) const
     {
+        // a quad of at most two factors, without its products by 1
+        if (pairs) {
+            if (Q == 0) return A::one();
+            const uint2 w = *wp;
+            return A::mul(u.get((int)(w.x & 0xFFFFu)), u.get((int)(w.x >> 16)));
+        }
         C prod = A::one();
         for (int h = 0; h < 2 && has(2 * h); ++h) {
             C t = range(2 * h);
@@ -475,7 +481,7 @@ __device__ __forceinline__ void chunk_values(const QuotArgs &a, const int4 &ck, 
         const typename One::C coef = Io<One>::coef(a.coef, (int64_t)ck.x + (on ? s : 0));
         C prod = A::one();
         if (log2L == 0) {
-            prod = fac.all();
+            prod = fac.all(a.pairs);
         } else {
             // ranges 2 sub, 2 sub + 1 of two lanes, or range sub of four; a
             // lower lane's product is the left factor, and only what reaches
@@ -564,7 +570,7 @@ __device__ __forceinline__ void quot_value(const QuotArgs &a, const LdsVec<A> &u
             Worst<A> worst;
             const Factors<A> fac(u, a.words + (int64_t)sh.x + lane, cnt, sh.y, worst);
             const typename One::C coef = Io<One>::coef(a.coef, (int64_t)ck.x + 64 * sl + lane);
-            C v = A::mul(fac.all(), P::all(coef));
+            C v = A::mul(fac.all(a.pairs), P::all(coef));
             worst.mark(v);
             acc.add(v, 1.0);
         }
