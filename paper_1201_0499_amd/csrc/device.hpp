@@ -266,6 +266,20 @@ __device__ __forceinline__ bool is_refused(double v)
     return __double_as_longlong(v) == 0x7FF8A55E55EDD1F7ll;
 }
 
+// Whether any lane of the workgroup says so, through one word of its LDS that
+// is free (__syncthreads_or would take 256 bytes of static LDS, and a kernel
+// whose dynamic LDS may be all 160 KiB has none to spare).
+__device__ __forceinline__ bool any_of_workgroup(bool v, int *word)
+{
+    if (threadIdx.x == 0) *word = 0;
+    __syncthreads();
+    if (__ballot(v) != 0 && (threadIdx.x & 63) == 0) *word = 1;
+    __syncthreads();
+    const bool any = *word != 0;
+    __syncthreads();  // the word is free again
+    return any;
+}
+
 template <class A>
 struct Io;
 

@@ -51,12 +51,12 @@ namespace pe {
 
 // Whether a quotient kernel left polynomial p to this one at some of the
 // points pt0, pt0 + gridDim.y, ... (the same answer on every thread).
-__device__ __forceinline__ bool any_refused(const EvalArgs &a, int p, int64_t pt0)
+__device__ __forceinline__ bool any_refused(const EvalArgs &a, int p, int64_t pt0, int *word)
 {
     bool any = false;
     for (int64_t pt = pt0 + (int64_t)threadIdx.x * gridDim.y; pt < a.n_points; pt += (int64_t)blockDim.x * gridDim.y)
         any = any || is_refused(a.f[0][pt * a.n_polys + p]);
-    return __syncthreads_or(any);
+    return any_of_workgroup(any, word);
 }
 
 // One system: workgroup (group, tile block); tiles of T consecutive points,
@@ -80,7 +80,7 @@ eval_kernel(const EvalArgs a)
         const int group = xcd_order(blockIdx.x, gridDim.x);
         const int64_t pt0 = blockIdx.y;
         if constexpr (REPAIR) {
-            if (!any_refused(a, group, pt0)) return;
+            if (!any_refused(a, group, pt0, reinterpret_cast<int *>(lds_raw))) return;
         }
         const bool has_x = (int)threadIdx.x < a.n_vars;
         // the first point's entry is requested before the tables
@@ -176,7 +176,7 @@ __global__ __launch_bounds__(MAXT) void batch_kernel(const BatchArgs b)
             const double *f = b.f[0] + d.f_off + task.pt * d.a.n_polys;
             for (int p = task.p0; p < task.p1; p += task.step) any = any || is_refused(f[p]);
         }
-        if (!__syncthreads_or(any)) return;
+        if (!any_of_workgroup(any, reinterpret_cast<int *>(lds_raw))) return;
     }
     for (int64_t t = blockIdx.x; t < b.n_tasks; t += gridDim.x) {
         const BatchTask task = b.tasks[t];

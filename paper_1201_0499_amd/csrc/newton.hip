@@ -52,7 +52,7 @@ __global__ __launch_bounds__(NT) void resid_kernel(const ResidArgs a)
     if (a.repair) {
         bool any = false;
         for (int p = tid; p < a.n_polys; p += NT) any = any || is_refused(a.f[0][pt * a.n_polys + p]);
-        if (!__syncthreads_or(any)) return;
+        if (!any_of_workgroup(any, reinterpret_cast<int *>(lds_raw))) return;
     }
     double2 *next = lds_raw;
     const LdsVec<A> pw = LdsVec<A>::at(lds_raw, a.R * np1, next);  // [R][np1]: x^1 .. x^R
