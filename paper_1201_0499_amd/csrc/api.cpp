@@ -785,11 +785,8 @@ pe_status pe_create_system(int32_t n_vars, int32_t n_polys, int64_t n_monos,
     }
     // the quotient kernels need coefficients in their products' range (or zero)
     S->quot_ok = true;
-    for (int64_t s = 0; s < n_monos && S->quot_ok; ++s) {
-        const double big = std::max(std::fabs(c[4 * s + 0]), std::fabs(c[4 * s + 2]));
-        S->quot_ok = big == 0.0 ? c[4 * s + 1] == 0.0 && c[4 * s + 3] == 0.0
-                                : std::abs(std::ilogb(big)) < kCoefExp;
-    }
+    for (int64_t s = 0; s < n_monos && S->quot_ok; ++s)
+        S->quot_ok = quot_coef_ok(c[4 * s + 0], c[4 * s + 1], c[4 * s + 2], c[4 * s + 3]);
     quot_shape(CsrView{n_vars, n_polys, n_monos, poly_start, mono_start, pos, exp}, S->quot_pad, S->quot_max_m);
     if (hipGetDevice(&S->device) != hipSuccess) return fail(PE_EDEVICE, "hipGetDevice failed");
     // the device address of the static scratch, looked up once per device

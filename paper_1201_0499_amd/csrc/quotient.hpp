@@ -15,6 +15,9 @@
 
 #include <stdint.h>
 
+#include <algorithm>
+#include <cmath>
+#include <cstdlib>
 #include <string>
 #include <vector>
 
@@ -49,6 +52,16 @@ constexpr int kMaxQuotChunk = 1024;  // monomials per chunk, at most (<= 2^kEntr
 // terms 2^-212 of it.
 constexpr int kProductExp = 400;
 constexpr int kCoefExp = 300;
+
+// Whether the quotient kernels take a coefficient (its parts as double-words):
+// its larger part within 2^+-kCoefExp, or zero; finite, as a NaN would be refused
+// at every point, after the work.
+inline bool quot_coef_ok(double re_hi, double re_lo, double im_hi, double im_lo)
+{
+    if (!std::isfinite(re_hi) || !std::isfinite(re_lo) || !std::isfinite(im_hi) || !std::isfinite(im_lo)) return false;
+    const double big = std::max(std::fabs(re_hi), std::fabs(im_hi));
+    return big == 0.0 ? re_lo == 0.0 && im_lo == 0.0 : std::abs(std::ilogb(big)) < kCoefExp;
+}
 
 // Largest binary exponent of a coordinate (either sign) for maximal exponent
 // d: kQuad factors of at most 2^(d (b + 1/2)) each stay within 2^kProductExp.

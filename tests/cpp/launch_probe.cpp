@@ -1,5 +1,5 @@
-// Test-only shim: the host functions that size the launches of the quotient
-// kernels (quotient_tables.cpp, launch_limits.hpp).  Built with g++ by the tests.
+// Test-only shim: the host functions that choose and size the launches of the
+// quotient kernels (quotient_tables.cpp, launch_limits.hpp).  Built with g++ by the tests.
 #include "launch_limits.hpp"
 #include "quotient.hpp"
 
@@ -26,6 +26,8 @@ int64_t lp_single_units(int n_vars, int max_k, int64_t max_m, int words, int jac
 {
     return pe::single_launch_units(n_vars, max_k, max_m, words, jac != 0);
 }
+
+int lp_coef_ok(const double *c) { return pe::quot_coef_ok(c[0], c[1], c[2], c[3]); }
 
 int64_t lp_max_workgroups(int threads) { return pe::max_workgroups(threads); }
 

@@ -92,3 +92,13 @@ def test_single_launch_units(probe):
         assert probe.lp_single_units(n, k, m, 2, 1) == (16384 if (n, k, m) == (450, 2, 113) else units)
         for words, jac in ((2, 0), (4, 0), (8, 1)):
             assert probe.lp_single_units(n, k, m, words, jac) == 1280
+
+
+def test_coefficients_that_the_quotients_take(probe):
+    """Within 2^+-300 or exactly zero, and finite in every word."""
+    inf, nan = float("inf"), float("nan")
+    for c, ok in (((1, 0, 0, 0), 1), ((0, 0, 0, 0), 1), ((0, 0, -1, 1e-20), 1), ((0, 1e-20, 0, 0), 0),
+                  ((2.0 ** 299, 0, 0, 0), 1), ((2.0 ** 300, 0, 0, 0), 0), ((0, 0, 2.0 ** -299, 0), 1),
+                  ((0, 0, 2.0 ** -300, 0), 0), ((nan, 0, 1, 0), 0), ((1, 0, nan, 0), 0), ((1, nan, 1, 0), 0),
+                  ((inf, 0, 1, 0), 0), ((1, 0, -inf, 0), 0), ((1, 0, 1, inf), 0), ((nan, 0, nan, 0), 0)):
+        assert probe.lp_coef_ok((C.c_double * 4)(*c)) == ok, c
