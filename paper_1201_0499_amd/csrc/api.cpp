@@ -391,7 +391,9 @@ void System::fill_quot(const Quot &q, QuotArgs &a) const
     a.multi = q.multi;
     a.PP = 1;
     a.nbuf = 1;
-    const int b = quot_point_exp(max_exp) - 1;
+    bool check;
+    const int b = quot_window(max_exp, check);
+    a.check = check;
     a.x_lo = (uint32_t)(1023 - b) << 20;
     a.x_span = (uint32_t)(2 * b + 1) << 20;
     a.words = (const uint2 *)q.words.ptr;

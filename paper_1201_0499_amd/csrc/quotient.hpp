@@ -42,14 +42,19 @@ constexpr int kMaxQuotExp = (1 << (16 - kEntryBits)) - 1;
 constexpr int kMaxQuotChunk = 1024;  // monomials per chunk, at most (<= 2^kEntryBits)
 
 // Range rules.  Partial products of a monomial (quads of factors apart) must
-// have a binary exponent within +-kProductExp, which the kernel checks; a
-// quad of factors is bounded by the same beforehand, by the points: every
-// |x_i| (larger part) within 2^+-b, b from quot_point_exp.  So a single quad
-// passes the check wherever it is made, and what is refused does not depend on
-// how many lanes share a monomial.  With coefficients within 2^+-kCoefExp (or
-// zero) no product, nor an error term of quad-double arithmetic, overflows or
-// becomes subnormal: the smallest entry of J is 2^-(400 + 300 + 60), its error
-// terms 2^-212 of it.
+// have a binary exponent within +-kProductExp, which the kernel checks.  A quad
+// of factors is bounded by the same: by the points, where that leaves them a
+// window of at least 2^+-kWideExp, so that a single quad passes the check
+// wherever it is made; else by checking quads too, and then the points only
+// keep the power table's entries within 2^+-kPowerExp (quot_window).  Either
+// way what is refused does not depend on how many lanes share a monomial.
+// (Products of two factors are within 2^+-600 there; those of quads may
+// overflow or vanish, and are then out of range.)  With coefficients within
+// 2^+-kCoefExp (or zero) no product that counts, nor an error term of
+// quad-double arithmetic, overflows or becomes subnormal: the smallest entry of
+// J is 2^-(400 + 300 + 60), its error terms 2^-212 of it.
+constexpr int kWideExp = 16;
+constexpr int kPowerExp = 300;
 constexpr int kProductExp = 400;
 constexpr int kCoefExp = 300;
 
@@ -69,6 +74,22 @@ inline int quot_point_exp(int d)
 {
     const int b = (2 * kProductExp / kQuad - d) / (2 * d);
     return b < 0 ? 0 : (b > 60 ? 60 : b);
+}
+
+// The window of the points for maximal exponent d: the larger part of every
+// coordinate has a binary exponent of at most b, either sign.  Up to d = 5 a
+// window of 2^+-18 or more comes without checked quads, above 2^+-48 (d = 6) to
+// 2^+-8 (d = 31) with them; without them it would be 2^+-8 at d = 10 and 2^+-1
+// at d = 31, where complex Gaussian coordinates leave 9 polynomials in 10 to the
+// general kernel (n = 64, m = 128, k = 16, 200 points in double-double, which
+// that kernel alone takes 669 us for: 874 us without, 312 us with).
+inline int quot_window(int d, bool &check_quads)
+{
+    const int b = quot_point_exp(d) - 1;
+    check_quads = b < kWideExp;
+    if (!check_quads) return b;
+    const int c = (2 * kPowerExp - d) / (2 * d);
+    return std::min(c, 60) - 1;
 }
 
 // Packed tables of one system for chunks of CH monomials.  Monomials of a

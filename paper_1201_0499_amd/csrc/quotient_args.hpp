@@ -16,6 +16,7 @@ struct QuotArgs {
     int32_t pad;         // 1: the power table ends with the entry 1
     int32_t CH;          // monomials per chunk
     int32_t n_blk;       // rank blocks per chunk
+    int32_t check;       // quads of factors are checked too (see quot_window)
     int32_t pairs;       // no monomial has more than two variables
     int32_t sparse;      // workgroups of one polynomial each, with few terms for its
                          //   variables: see quot_table

@@ -399,9 +399,9 @@ __device__ __forceinline__ void quot_table(const QuotArgs &a, const QuotLds<A> &
 
 // Factors of one lane's monomial: the quads of words wp[0], wp[cnt], ...
 // (Q of them) in the canonical order (quotient.hpp).  Checked after every
-// product of quads: a factor there is a quad (within the same range, by the
-// points') or was checked.
-template <class A>
+// product of quads: a factor there was checked, or is a quad, within the same
+// range by the points' or (CHECK) checked itself.
+template <class A, bool CHECK>
 struct Factors {
     using C = typename A::C;
     const LdsVec<A> &u;
@@ -418,7 +418,9 @@ struct Factors {
     {
         const C u0 = u.get((int)(w.x & 0xFFFFu)), u1 = u.get((int)(w.x >> 16));
         const C u2 = u.get((int)(w.y & 0xFFFFu)), u3 = u.get((int)(w.y >> 16));
-        return A::mul(A::mul(u0, u1), A::mul(u2, u3));
+        const C v = A::mul(A::mul(u0, u1), A::mul(u2, u3));
+        if (CHECK) worst.see(v);
+        return v;
     }
     __device__ __forceinline__ bool has(int r) const { return r * qs < Q; }
     // product of range r (quads r qs .. ), which has at least one quad
@@ -439,7 +441,9 @@ struct Factors {
         if (pairs) {
             if (Q == 0) return A::one();
             const uint2 w = *wp;
-            return A::mul(u.get((int)(w.x & 0xFFFFu)), u.get((int)(w.x >> 16)));
+            const C v = A::mul(u.get((int)(w.x & 0xFFFFu)), u.get((int)(w.x >> 16)));
+            if (CHECK) worst.see(v);
+            return v;
         }
         C prod = A::one();
         for (int h = 0; h < 2 && has(2 * h); ++h) {
@@ -461,8 +465,8 @@ struct Factors {
 
 // Values of the monomials of chunk ck into V at entry vo, one lane per
 // monomial (ONE) or as many as the launch says.
-template <class A, bool ONE>
-__device__ __forceinline__ void chunk_values(const QuotArgs &a, const int4 &ck, const QuotLds<A> &lds, int vo)
+template <class A, bool ONE, bool CHECK>
+__device__ __forceinline__ void chunk_products(const QuotArgs &a, const int4 &ck, const QuotLds<A> &lds, int vo)
 {
     using C = typename A::C;
     using P = Pts<A>;
@@ -476,8 +480,8 @@ __device__ __forceinline__ void chunk_values(const QuotArgs &a, const int4 &ck, 
         const int sl = __builtin_amdgcn_readfirstlane(s >> 6);
         const int2 sh = uniform_int2(a.slice + ck.z + sl);
         Worst<A> worst;
-        const Factors<A> fac(lds.u, a.words + (int64_t)sh.x + (on ? s - 64 * sl : 0), min(64, ck.y - 64 * sl),
-                             sh.y, worst);
+        const Factors<A, CHECK> fac(lds.u, a.words + (int64_t)sh.x + (on ? s - 64 * sl : 0), min(64, ck.y - 64 * sl),
+                                    sh.y, worst);
         const typename One::C coef = Io<One>::coef(a.coef, (int64_t)ck.x + (on ? s : 0));
         C prod = A::one();
         if (log2L == 0) {
@@ -504,6 +508,16 @@ __device__ __forceinline__ void chunk_values(const QuotArgs &a, const int4 &ck, 
         worst.mark(prod);
         if (on && sub == 0) lds.V.put(vo + s, prod);
     }
+}
+
+// (a branch for each quad in the place of two loops costs 4% in FP64)
+template <class A, bool ONE>
+__device__ __forceinline__ void chunk_values(const QuotArgs &a, const int4 &ck, const QuotLds<A> &lds, int vo)
+{
+    if (a.check)
+        chunk_products<A, ONE, true>(a, ck, lds, vo);
+    else
+        chunk_products<A, ONE, false>(a, ck, lds, vo);
 }
 
 // Sum over the wave, by a butterfly.
@@ -550,8 +564,8 @@ __device__ __forceinline__ void quot_store(const QuotArgs &a, int64_t pt, uint32
 // multiplies monomials l, l + 64, ... of a chunk and adds their values, then
 // the wave adds the lanes; the same operations in the same order as
 // chunk_values and chunk_sums.
-template <class A>
-__device__ __forceinline__ void quot_value(const QuotArgs &a, const LdsVec<A> &u, int64_t pt, uint32_t live, int p)
+template <class A, bool CHECK>
+__device__ __forceinline__ void quot_value_of(const QuotArgs &a, const LdsVec<A> &u, int64_t pt, uint32_t live, int p)
 {
     using C = typename A::C;
     using P = Pts<A>;
@@ -568,7 +582,7 @@ __device__ __forceinline__ void quot_value(const QuotArgs &a, const LdsVec<A> &u
             const int cnt = min(64, ck.y - 64 * sl);
             if (lane >= cnt) break;  // the chunk's last slice
             Worst<A> worst;
-            const Factors<A> fac(u, a.words + (int64_t)sh.x + lane, cnt, sh.y, worst);
+            const Factors<A, CHECK> fac(u, a.words + (int64_t)sh.x + lane, cnt, sh.y, worst);
             const typename One::C coef = Io<One>::coef(a.coef, (int64_t)ck.x + 64 * sl + lane);
             C v = A::mul(fac.all(a.pairs), P::all(coef));
             worst.mark(v);
@@ -578,6 +592,15 @@ __device__ __forceinline__ void quot_value(const QuotArgs &a, const LdsVec<A> &u
         f = c == pl.x && pl.z == 0 ? v : A::sum(f, v);
     }
     if (lane == 0) quot_store<A>(a, pt, live, p, a.n_vars, f, [] {});
+}
+
+template <class A>
+__device__ __forceinline__ void quot_value(const QuotArgs &a, const LdsVec<A> &u, int64_t pt, uint32_t live, int p)
+{
+    if (a.check)
+        quot_value_of<A, true>(a, u, pt, live, p);
+    else
+        quot_value_of<A, false>(a, u, pt, live, p);
 }
 
 // Sum of a run by one lane's NP of its kParts partial sums, combined with

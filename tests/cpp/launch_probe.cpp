@@ -27,6 +27,14 @@ int64_t lp_single_units(int n_vars, int max_k, int64_t max_m, int words, int jac
     return pe::single_launch_units(n_vars, max_k, max_m, words, jac != 0);
 }
 
+int lp_window(int d, int *check)
+{
+    bool c;
+    const int b = pe::quot_window(d, c);
+    *check = c;
+    return b;
+}
+
 int lp_coef_ok(const double *c) { return pe::quot_coef_ok(c[0], c[1], c[2], c[3]); }
 
 int64_t lp_max_workgroups(int threads) { return pe::max_workgroups(threads); }

@@ -102,3 +102,20 @@ def test_coefficients_that_the_quotients_take(probe):
                   ((0, 0, 2.0 ** -300, 0), 0), ((nan, 0, 1, 0), 0), ((1, 0, nan, 0), 0), ((1, nan, 1, 0), 0),
                   ((inf, 0, 1, 0), 0), ((1, 0, -inf, 0), 0), ((1, 0, 1, inf), 0), ((nan, 0, nan, 0), 0)):
         assert probe.lp_coef_ok((C.c_double * 4)(*c)) == ok, c
+
+
+def test_window_of_the_points(probe):
+    """Every |x_i| < 2^(b + 1/2 + 1/2): quads of factors within 2^400, or, where
+    they are checked, powers within 2^300; never narrower than 2^+-8."""
+    check = C.c_int()
+    last = 61
+    for d in range(1, 32):
+        b = probe.lp_window(d, C.byref(check))
+        top = b + 1.5  # log2 of the modulus, at most
+        assert 8 <= b <= 59
+        if check.value:
+            assert d * top <= 300 and d >= 6
+        else:
+            assert 4 * d * top <= 400 and b >= 16 and d <= 5
+            assert b <= last
+            last = b
