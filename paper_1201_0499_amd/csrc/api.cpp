@@ -356,6 +356,7 @@ Quot *System::pack_quot(int words)
         q->CH = CH;
         q->n_blk = t.n_blk;
         q->multi = t.multi;
+        q->complete = t.complete;
         hipError_t e = q->coef.upload(c.data(), c.size() * sizeof(double));
 #define PE_UP(buf)                                                          \
     if (e == hipSuccess) e = q->buf.upload(t.buf.data(), t.buf.size() * sizeof(t.buf[0]));
@@ -490,7 +491,8 @@ hipError_t System::run_values(const Quot &q, int prec, QuotArgs qa, hipStream_t 
         return ((size_t)max_exp * n_vars + (quot_pad ? 1 : 0)) * T * words * sizeof(double);
     };
     const int T = prec == 0 && P >= kPointsF64 && lds_for(kPointsF64) <= (size_t)kMaxLds ? kPointsF64 : 1;
-    const size_t lds = lds_for(T);
+    size_t lds = lds_for(T);
+    qa.skip = T == 1 && q.complete && add_skip_words(lds);
     const int per_cu = (int)std::max<size_t>(1, kMaxLds / lds);
     // the smallest workgroups that fill the CU's registers, at most a wave
     // for each polynomial
@@ -547,6 +549,7 @@ hipError_t System::run_quot(const Quot &q, int prec, int cc, int maxt, EvalArgs 
             const unsigned want = std::min((n_vars + 63) / 64 * 64, units <= 512 ? 256 : 128);
             threads = std::max(threads, want);
         }
+        qa.skip = q.complete;
         few_lanes(qa, m, (int)threads);
         return launch_small(prec, cc, maxt, a, qa, dim3((unsigned)n_polys, (unsigned)P, 1), threads,
                             small_lds_bytes(lds, lds_for(1, 1)), hs);
@@ -566,7 +569,8 @@ hipError_t System::run_quot(const Quot &q, int prec, int cc, int maxt, EvalArgs 
     const int T = prec == 0 && P >= kPointsF64 && lds_for(kPointsF64, 1) * 4 <= (size_t)kMaxLds ? kPointsF64 : 1;
     const int64_t tiles = (P + T - 1) / T;
     if (lds_for(T, 2) <= (size_t)kMaxLds) qa.nbuf = 2;
-    const size_t qlds = lds_for(T, qa.nbuf);
+    size_t qlds = lds_for(T, qa.nbuf);
+    qa.skip = T == 1 && q.complete && (qa.nbuf > 1 || add_skip_words(qlds));
     const int per_cu = (int)std::max<size_t>(1, kMaxLds / qlds);
     const int nt = quot_threads(quot_lanes(q, words, per_cu), qlds, tiles * n_polys, cap);
     // several polynomials per workgroup share one power table, while the

@@ -196,6 +196,8 @@ struct LdsVec<ArithDD> {
         re[i] = make_double2(v.re.hi, v.re.lo);
         im[i] = make_double2(v.im.hi, v.im.lo);
     }
+    // the first 16 bytes of entry i
+    __device__ __forceinline__ double2 *piece(int i) const { return re + i; }
     // the array of `count` entries at raw, and the LDS that follows it
     __device__ __forceinline__ static LdsVec at(double2 *raw, int count, double2 *&next)
     {
@@ -220,6 +222,7 @@ struct LdsVec<ArithQD> {
         p[2 * count + i] = make_double2(v.im.x0, v.im.x1);
         p[3 * count + i] = make_double2(v.im.x2, v.im.x3);
     }
+    __device__ __forceinline__ double2 *piece(int i) const { return p + i; }
     __device__ __forceinline__ static LdsVec at(double2 *raw, int count, double2 *&next)
     {
         next = raw + 4 * (size_t)count;
@@ -236,6 +239,7 @@ struct LdsVec<Arith64> {
         return {r.x, r.y};
     }
     __device__ __forceinline__ void put(int i, const Arith64::C &c) const { v[i] = make_double2(c.re, c.im); }
+    __device__ __forceinline__ double2 *piece(int i) const { return v + i; }
     __device__ __forceinline__ static LdsVec at(double2 *raw, int count, double2 *&next)
     {
         next = raw + count;

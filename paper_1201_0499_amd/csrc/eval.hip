@@ -49,14 +49,16 @@
 
 namespace pe {
 
-// Whether a quotient kernel left polynomial p to this one at some of the
-// points pt0, pt0 + gridDim.y, ... (the same answer on every thread).
-__device__ __forceinline__ bool any_refused(const EvalArgs &a, int p, int64_t pt0, int *word)
+// Which of the points pt0 + i gridDim.y, i = 0 .. 63, a quotient kernel left
+// polynomial p at, among those that are evaluated (bit i; the same answer on
+// every thread).  Each wave reads the marks of 64 points at once: one at a time,
+// the load was a fifth of the work on a point in FP64.  The caller writes these
+// values only after a barrier.
+__device__ __forceinline__ uint64_t refused_points(const EvalArgs &a, int p, int64_t pt0)
 {
-    bool any = false;
-    for (int64_t pt = pt0 + (int64_t)threadIdx.x * gridDim.y; pt < a.n_points; pt += (int64_t)blockDim.x * gridDim.y)
-        any = any || is_refused(a.f[0][pt * a.n_polys + p]);
-    return any_of_workgroup(any, word);
+    const int64_t pt = pt0 + (int64_t)(threadIdx.x & 63) * gridDim.y;
+    return __ballot(pt < a.n_points && !(a.mask && a.mask[pt] != kMaskLive) &&
+                    is_refused(a.f[0][pt * a.n_polys + p]));
 }
 
 // One system: workgroup (group, tile block); tiles of T consecutive points,
@@ -78,14 +80,17 @@ eval_kernel(const EvalArgs a)
         HIP_DYNAMIC_SHARED(double2, lds_raw)
         const LdsLayout<A> lds = lds_layout<A, false>(lds_raw, a);
         const int group = xcd_order(blockIdx.x, gridDim.x);
-        const int64_t pt0 = blockIdx.y;
+        int64_t pt0 = blockIdx.y;
+        const int64_t batch = 64 * (int64_t)gridDim.y;  // points asked for at once
+        uint64_t todo = 0;
         if constexpr (REPAIR) {
-            if (!any_refused(a, group, pt0, reinterpret_cast<int *>(lds_raw))) return;
+            while (pt0 < a.n_points && !(todo = refused_points(a, group, pt0))) pt0 += batch;
+            if (!todo) return;
         }
         const bool has_x = (int)threadIdx.x < a.n_vars;
         // the first point's entry is requested before the tables
         C x0 = A::zero();
-        if (pt0 < a.n_points && has_x) x0 = Io<A>::load(a.x, pt0 * a.n_vars + threadIdx.x);
+        if (!REPAIR && pt0 < a.n_points && has_x) x0 = Io<A>::load(a.x, pt0 * a.n_vars + threadIdx.x);
         const int4 *gi = a.group_info + 2 * (int64_t)group * (REPAIR ? a.merge : 1);
         const int4 g0 = gi[0], g1 = gi[1];
         const int c_begin = g0.x, c_end = REPAIR ? gi[2 * (a.merge - 1)].y : g0.y;
@@ -93,14 +98,10 @@ eval_kernel(const EvalArgs a)
         ChunkIn<A, CC> in;
         RunIn rin = 0u;
         bool loaded = false, first = true;
-        for (int64_t pt = pt0; pt < a.n_points; pt += gridDim.y) {
-            if (a.mask && a.mask[pt] != kMaskLive) continue;
-            if constexpr (REPAIR) {
-                if (!is_refused(a.f[0][pt * a.n_polys + group])) continue;
-            }
+        auto point = [&](int64_t pt) {
             if (!first) __syncthreads();  // the previous point is done with LDS
             first = false;
-            if (pt != pt0 && has_x) x0 = Io<A>::load(a.x, pt * a.n_vars + threadIdx.x);
+            if ((REPAIR || pt != pt0) && has_x) x0 = Io<A>::load(a.x, pt * a.n_vars + threadIdx.x);
             if (!loaded && c_begin < c_end) {
                 // (merged shares: the first one may be empty, without a header)
                 in.ci = REPAIR ? a.chunk_info[c_begin] : make_int4(g0.z, g0.w, g1.x, g1.y);
@@ -111,6 +112,16 @@ eval_kernel(const EvalArgs a)
             begin_point<A>(a, pt, lds, x0, gi + 1);
             __syncthreads();
             eval_group<A, CC, (CC <= 4)>(a, group, c_begin, c_end, pt, lds, in, rin);
+        };
+        if constexpr (REPAIR) {
+            for (;;) {
+                for (; todo; todo &= todo - 1) point(pt0 + (int64_t)(__ffsll((unsigned long long)todo) - 1) * gridDim.y);
+                if ((pt0 += batch) >= a.n_points) break;
+                todo = refused_points(a, group, pt0);
+            }
+        } else {
+            for (int64_t pt = pt0; pt < a.n_points; pt += gridDim.y)
+                if (!(a.mask && a.mask[pt] != kMaskLive)) point(pt);
         }
     } else {
         using C = typename A::C;
@@ -190,9 +201,15 @@ __global__ __launch_bounds__(MAXT) void batch_kernel(const BatchArgs b)
         const LdsLayout<A> lds = lds_layout<A, false>(lds_raw, a);
         __syncthreads();  // the previous task is done with LDS
         bool begun = false;
-        for (int p = task.p0; p < task.p1; p += task.step) {
-            // (f of polynomial p is written only by this task, below)
-            if (b.repair && !is_refused(a.f[0][task.pt * a.n_polys + p])) continue;
+        uint64_t todo = 0;
+        for (int i = 0, p = task.p0; p < task.p1; ++i, p += task.step) {
+            // the marks of 64 polynomials at once (f of polynomial p is written
+            // only by this task, below, after a barrier)
+            if ((i & 63) == 0) {
+                const int q = p + (int)(threadIdx.x & 63) * task.step;
+                todo = __ballot(q < task.p1 && (!b.repair || is_refused(a.f[0][task.pt * a.n_polys + q])));
+            }
+            if (!((todo >> (i & 63)) & 1)) continue;
             const int4 g0 = a.group_info[2 * p];
             const int4 g1 = a.group_info[2 * p + 1];
             if (g0.x < g0.y) {

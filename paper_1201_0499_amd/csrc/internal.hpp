@@ -48,7 +48,7 @@ struct Schedule {
 // Packed tables of one system for the quotient kernels (quotient.hpp).
 struct Quot {
     int CH = 0, n_blk = 0;
-    bool multi = false;
+    bool multi = false, complete = false;
     DevBuf words, coef, slice, chunk, poly, block, runs, out;
 };
 

@@ -57,6 +57,7 @@ __global__ __launch_bounds__(kQuotMaxThreads<A>) void quot_kernel(const QuotArgs
     HIP_DYNAMIC_SHARED(double2, lds_raw)
     double2 *end;
     const QuotLds<A> lds = quot_lds<A>(lds_raw, a, end);
+    uint32_t *const words = wave_words<A>(a, lds, end);
     const int64_t tiles = (a.n_points + T - 1) / T;
     const int per_xcd = a.by_point ? a.blocks : (a.blocks + 7) / 8;
     const int64_t rounds = a.by_point ? (tiles + 7) / 8 : tiles;
@@ -77,10 +78,12 @@ __global__ __launch_bounds__(kQuotMaxThreads<A>) void quot_kernel(const QuotArgs
         if (!live) continue;
         if (!first) __syncthreads();  // the previous points are done with LDS
         first = false;
-        quot_table<A>(a, lds, pt, npt, block, true);
+        quot_table<A, true>(a, lds, pt, npt, block, a.n_polys, a.blocks, true, words);
         __syncthreads();
+        const bool bad = bad_point<A>(a, words);
         int vo = 0;
-        for (int p = block; p < a.n_polys; p += a.blocks) quot_poly<A, false>(a, lds, pt, live, p, vo, true, [] {});
+        for (int p = block; p < a.n_polys; p += a.blocks)
+            quot_poly<A, false>(a, lds, pt, live, bad, p, vo, true, [] {});
     }
 }
 
@@ -97,6 +100,7 @@ __global__ __launch_bounds__(kQuotMaxThreads<A>) void quot_values_kernel(const Q
     double2 *end;
     QuotLds<A> lds{};
     lds.u = LdsVec<A>::at(lds_raw, a.D * a.n_vars + a.pad, end);
+    uint32_t *const words = reinterpret_cast<uint32_t *>(end);
     bool first = true;
     for (int64_t pt = (int64_t)blockIdx.y * T; pt < a.n_points; pt += (int64_t)gridDim.y * T) {
         const int npt = (int)min<int64_t>(T, a.n_points - pt);
@@ -107,9 +111,10 @@ __global__ __launch_bounds__(kQuotMaxThreads<A>) void quot_values_kernel(const Q
         if (!live) continue;
         if (!first) __syncthreads();  // the previous points are done with LDS
         first = false;
-        quot_table<A>(a, lds, pt, npt, 0, false);
+        quot_table<A, true>(a, lds, pt, npt, p0, p1, 1, false, words);
         __syncthreads();
-        for (int p = p0 + wave; p < p1; p += nw) quot_value<A>(a, lds.u, pt, live, p);
+        const bool bad = bad_point<A>(a, words);
+        for (int p = p0 + wave; p < p1; p += nw) quot_value<A>(a, lds.u, pt, live, bad, p);
     }
 }
 
@@ -140,14 +145,16 @@ __global__ __launch_bounds__(kQuotMaxThreads<A>) void quot_batch_kernel(const Qu
         double2 *end;
         const QuotLds<A> lds = quot_lds<A>(lds_raw, a, end);
         __syncthreads();  // the previous task is done with LDS
-        quot_table<A>(a, lds, task.pt, 1, 0, JAC);
+        quot_table<A, false>(a, lds, task.pt, 1, task.p0, task.p1, task.step, JAC, nullptr);
         __syncthreads();
         if constexpr (JAC) {
             int vo = 0;
-            for (int p = task.p0; p < task.p1; p += task.step) quot_poly<A, false>(a, lds, task.pt, 1u, p, vo, true, [] {});
+            for (int p = task.p0; p < task.p1; p += task.step)
+                quot_poly<A, false>(a, lds, task.pt, 1u, false, p, vo, true, [] {});
         } else {
             const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), nw = (int)blockDim.x >> 6;
-            for (int p = task.p0 + wave * task.step; p < task.p1; p += nw * task.step) quot_value<A>(a, lds.u, task.pt, 1u, p);
+            for (int p = task.p0 + wave * task.step; p < task.p1; p += nw * task.step)
+                quot_value<A>(a, lds.u, task.pt, 1u, false, p);
         }
     }
 }

@@ -106,6 +106,7 @@ struct QuotTables {
                            //   folded ones has the same number of variables, a
                            //   multiple of kQuad)
     bool multi = false;    // some polynomial has more than one chunk
+    bool complete = false; // every variable occurs in some polynomial (see poly)
     int n_chunks = 0;
     std::vector<uint16_t> words;     // per slice [quads][monomials][kQuad]: power-table
                                      //   entry (a-1) n + variable, or d n: the entry 1
@@ -114,7 +115,8 @@ struct QuotTables {
     std::vector<int32_t> chunk;      // [chunks][4]: first monomial (table order),
                                      //   monomials, first slice, first rank block
     std::vector<int32_t> poly;       // [n_polys][4]: first chunk, end chunk, 1 + index
-                                     //   of the folded constant (0: none), 0
+                                     //   of the folded constant (0: none), 1 if every
+                                     //   variable occurs in it
     std::vector<int32_t> block;      // [chunks][n_blk][2]: first row, rows
     std::vector<uint16_t> runs;      // [rows][kRankBlock][kParts] entries
     std::vector<uint16_t> out;       // [chunks][n_blk * kRankBlock]: output of a rank
@@ -129,6 +131,12 @@ int quot_chunk(int n_vars, int max_exp, bool pad, int64_t max_m, int words);
 // LDS bytes of a workgroup with nbuf buffers of chunk values.
 size_t quot_lds_bytes(int n_vars, int max_exp, bool pad, int CH, bool multi, int nbuf, int words);
 
+// Words for a workgroup's waves: whether the wave saw a coordinate out of range
+// (see quot_table); after the tables, where there is one buffer of values.
+constexpr size_t kQuotWordBytes = 64;
+// Where they fit a workgroup's `lds` bytes and leave as many workgroups on a
+// CU, add_skip_words adds them.
+bool add_skip_words(size_t &lds);
 // Calls of at most this many (polynomial, point) pairs run in one launch
 // (small.hip): five workgroups per CU.  One MI355X, two launches against one:
 // n = 350, m = 69, k = 8, 3 points in FP64 17.5 and 14.7 us, n = 16, m = 64, k
@@ -147,7 +155,7 @@ constexpr int64_t kSparseUnits = 16384;
 int64_t single_launch_units(int n_vars, int max_k, int64_t max_m, int words, bool jac);
 // ... whose workgroups hold the general stages' LDS (general_lds bytes), or
 // the quotients' (quot_lds, for one point and one buffer) and then a flag.
-constexpr size_t kSmallFlagBytes = 16;
+constexpr size_t kSmallFlagBytes = 16 + kQuotWordBytes;
 size_t small_lds_bytes(size_t general_lds, size_t quot_lds);
 // Whether a call of `units` pairs, of at most `most`, runs in one launch.
 // Tables of the quotients may fill the LDS without the flag (n = 512, m = 512,

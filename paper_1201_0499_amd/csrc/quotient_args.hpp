@@ -20,6 +20,9 @@ struct QuotArgs {
     int32_t pairs;       // no monomial has more than two variables
     int32_t sparse;      // workgroups of one polynomial each, with few terms for its
                          //   variables: see quot_table
+    int32_t skip;        // polynomials in which every variable occurs are left to the
+                         //   general kernel at points with a coordinate out of range
+                         //   without further work: see bad_point
     int32_t multi;       // some polynomial has more than one chunk
     int32_t log2L;       // lanes per monomial: 1, 2 or 4
     int32_t log2S;       // lanes per run of terms: 1, 2 or 4

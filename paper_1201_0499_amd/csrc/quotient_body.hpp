@@ -101,6 +101,7 @@ struct LdsVec<PointsF64<T>> {
 #pragma unroll
         for (int t = 0; t < T; ++t) p[t * count + i] = make_double2(c.v[t].re, c.v[t].im);
     }
+    __device__ __forceinline__ double2 *piece(int i) const { return p + i; }
     __device__ __forceinline__ static LdsVec at(double2 *raw, int count, double2 *&next)
     {
         next = raw + T * (size_t)count;
@@ -345,13 +346,15 @@ __device__ __forceinline__ QuotLds<A> quot_lds(double2 *raw, const QuotArgs &a, 
 }
 
 // The power table and the reciprocals of points pt .. pt+npt-1 (callers add
-// the barrier).  A coordinate out of range becomes NaN in the table: the
+// the barrier), and with a.skip (SKIP: it may be set) the wave's word of `words`, and the marks of
+// those of the polynomials p, p + step, ... below p1 at such a point in which
+// every variable occurs.  A coordinate out of range becomes NaN in the table: the
 // values of the polynomials that contain it then are NaN too.  With a.sparse
 // only the variables that share a block of ranks with one of polynomial p, its
 // only one: what no term reads stays unset, and what multiplies no terms is 1.
-template <class A>
-__device__ __forceinline__ void quot_table(const QuotArgs &a, const QuotLds<A> &lds, int64_t pt, int npt, int p,
-                                           bool jac)
+template <class A, bool SKIP>
+__device__ __forceinline__ void quot_table(const QuotArgs &a, const QuotLds<A> &lds, int64_t pt, int npt, int p, int p1,
+                                           int step, bool jac, uint32_t *words)
 {
     using C = typename A::C;
     using P = Pts<A>;
@@ -359,6 +362,7 @@ __device__ __forceinline__ void quot_table(const QuotArgs &a, const QuotLds<A> &
     const int n = a.n_vars, NT = (int)blockDim.x;
     int4 pl = make_int4(0, 0, 0, 0), ck = pl;
     int count = n;
+    bool bad = false;
     if (a.sparse) {
         pl = uniform_int4(a.poly + p);
         if (pl.x == pl.y) return;
@@ -383,6 +387,7 @@ __device__ __forceinline__ void quot_table(const QuotArgs &a, const QuotLds<A> &
             if (range_pos(v, a.x_lo) >= a.x_span) {
                 make_nan(v);
                 P::at(y, t) = One::one();
+                bad = true;
             }
             P::at(x, t) = v;
         }
@@ -395,6 +400,38 @@ __device__ __forceinline__ void quot_table(const QuotArgs &a, const QuotLds<A> &
         if (jac) lds.y.put(i, y);
     }
     if (a.pad && threadIdx.x == 0) lds.u.put(a.D * n, A::one());
+    if constexpr (SKIP && P::T == 1) {
+        if (a.skip) {
+            const bool any = __ballot(bad) != 0;
+            if ((threadIdx.x & 63) == 0) words[threadIdx.x >> 6] = any;
+            if (bad)
+                for (int q = p; q < p1; q += step)
+                    if (a.poly[q].w) a.f[0][pt * a.n_polys + q] = refused();
+        }
+    }
+}
+
+// Whether a coordinate of the point is out of range, after the table's barrier;
+// with a.skip, else never.  Polynomials in which every variable occurs are then
+// refused before the work on them (n = 128, m = 256, k = 16, d = 3, one
+// coordinate zero at every point, double-double, the general kernel alone, the
+// quotients and it, it after a look at the point: one point 16.8, 24.1 and 17.4
+// us; 1000 points 5.8, 7.7 and 6.0 ms); the others after it, if they contain it.
+// Not for two points in FP64, nor in batches, where the look costs every call 3%.
+template <class A>
+__device__ __forceinline__ bool bad_point(const QuotArgs &a, const uint32_t *words)
+{
+    if (Pts<A>::T > 1 || !a.skip) return false;
+    const int lane = (int)threadIdx.x & 63;
+    return __ballot(lane < (int)(blockDim.x >> 6) && words[lane] != 0) != 0;
+}
+
+// Where the words are: in the second buffer of values, if there is one, which
+// nothing writes before the barrier after the first polynomial's values.
+template <class A>
+__device__ __forceinline__ uint32_t *wave_words(const QuotArgs &a, const QuotLds<A> &lds, double2 *end)
+{
+    return reinterpret_cast<uint32_t *>(a.nbuf > 1 ? lds.V.piece(a.CH) : end);
 }
 
 // Factors of one lane's monomial: the quads of words wp[0], wp[cnt], ...
@@ -595,8 +632,10 @@ __device__ __forceinline__ void quot_value_of(const QuotArgs &a, const LdsVec<A>
 }
 
 template <class A>
-__device__ __forceinline__ void quot_value(const QuotArgs &a, const LdsVec<A> &u, int64_t pt, uint32_t live, int p)
+__device__ __forceinline__ void quot_value(const QuotArgs &a, const LdsVec<A> &u, int64_t pt, uint32_t live,
+                                           bool bad, int p)
 {
+    if (bad && uniform_int4(a.poly + p).w) return;  // marked with the table
     if (a.check)
         quot_value_of<A, true>(a, u, pt, live, p);
     else
@@ -677,18 +716,19 @@ __device__ __forceinline__ void chunk_sums(const QuotArgs &a, int ci, const int4
 }
 
 // Polynomial p at the points from pt on, of which those with their bit set in
-// live are written; vo is the buffer in use (it alternates).  FEW: lanes per
+// live are written (bad: see bad_point); vo is the buffer in use (it alternates).  FEW: lanes per
 // monomial and per run as the launch says (calls of few workgroups); else one
 // lane per monomial and two per run.  on_refused: see quot_store.
 template <class A, bool FEW, class Refused>
 __device__ __forceinline__ void quot_poly(const QuotArgs &a, const QuotLds<A> &lds, int64_t pt, uint32_t live,
-                                          int p, int &vo, bool jac, const Refused &on_refused)
+                                          bool bad, int p, int &vo, bool jac, const Refused &on_refused)
 {
     using C = typename A::C;
     using P = Pts<A>;
     using One = typename P::One;
     const int n = a.n_vars;
     const int4 pl = uniform_int4(a.poly + p);
+    if (bad && pl.w) return;  // marked with the table
     for (int c = pl.x; c < pl.y; ++c) {
         const int4 ck = uniform_int4(a.chunk + c);
         chunk_values<A, !FEW>(a, ck, lds, vo);

@@ -16,6 +16,14 @@ size_t quot_lds_bytes(int n_vars, int max_exp, bool pad, int CH, bool multi, int
     return values * (size_t)words * sizeof(double);
 }
 
+bool add_skip_words(size_t &lds)
+{
+    const size_t with = lds + kQuotWordBytes;
+    if (with > kLdsBytes || kLdsBytes / with < kLdsBytes / lds) return false;
+    lds = with;
+    return true;
+}
+
 size_t small_lds_bytes(size_t general_lds, size_t quot_lds)
 {
     return std::max(general_lds, quot_lds + kSmallFlagBytes);
@@ -173,7 +181,7 @@ std::string build_quot_tables(const CsrView &S, QuotTables &t)
     int max_exp = 1;
     for (int64_t e = 0; e < (S.n_monos ? S.mono_start[S.n_monos] : 0); ++e) max_exp = std::max(max_exp, S.exp[e]);
     if (max_exp > kMaxQuotExp) return "exponents too large";
-    t.multi = false;
+    t.multi = t.complete = false;
     t.words.clear();
     t.mono.clear();
     t.slice.clear();
@@ -184,6 +192,7 @@ std::string build_quot_tables(const CsrView &S, QuotTables &t)
     t.out.clear();
     t.mono.reserve((size_t)S.n_monos);
     std::vector<int32_t> len((size_t)n), rank((size_t)n), at((size_t)n + 1), order((size_t)n), bin;
+    std::vector<char> has((size_t)n);
     std::vector<int32_t> by_k[257];
     Pool pool[kRankBlock];
     std::vector<uint16_t> list, terms;
@@ -211,6 +220,8 @@ std::string build_quot_tables(const CsrView &S, QuotTables &t)
         const int nch = (int)((m + CH - 1) / CH);
         if (nch > 1) t.multi = true;
         const int32_t chunk0 = (int32_t)(t.chunk.size() / 4);
+        int missing = n;
+        std::fill(has.begin(), has.end(), 0);
         for (int c = 0; c < nch; ++c) {
             const int64_t a = first + (int64_t)c * CH;
             const int cnt = (int)std::min<int64_t>(CH, first + m - a);
@@ -261,6 +272,11 @@ std::string build_quot_tables(const CsrView &S, QuotTables &t)
                     }
                 }
             }
+            for (int o = 0; o < n; ++o)
+                if (len[(size_t)o] && !has[(size_t)o]) {
+                    has[(size_t)o] = 1;
+                    --missing;
+                }
             // outputs by run length, longest first (stable counting sort)
             const int lmax = cnt;
             bin.assign((size_t)lmax + 2, 0);
@@ -322,7 +338,8 @@ std::string build_quot_tables(const CsrView &S, QuotTables &t)
         t.poly.push_back(chunk0);
         t.poly.push_back(chunk0 + nch);
         t.poly.push_back(fold);
-        t.poly.push_back(0);
+        t.poly.push_back(missing == 0);
+        t.complete = t.complete || missing == 0;
     }
     t.n_chunks = (int)(t.chunk.size() / 4);
     return std::string();

@@ -28,13 +28,16 @@ small_kernel(const EvalArgs a, const QuotArgs qa)
         int *const flag = reinterpret_cast<int *>(end);
         if (threadIdx.x == 0) *flag = 0;
         const bool jac = qa.J[0] != nullptr;
-        quot_table<A>(qa, lds, pt, 1, p, jac);
+        uint32_t *const words = reinterpret_cast<uint32_t *>(end + 1);
+        quot_table<A, true>(qa, lds, pt, 1, p, 0, 1, jac, words);
         __syncthreads();
-        int vo = 0;
-        quot_poly<A, true>(qa, lds, pt, 1u, p, vo, jac, [&] { *flag = 1; });
-        __syncthreads();
-        if (*flag == 0) return;
-        __syncthreads();  // the flag has been read
+        if (!(bad_point<A>(qa, words) && uniform_int4(qa.poly + p).w)) {
+            int vo = 0;
+            quot_poly<A, true>(qa, lds, pt, 1u, false, p, vo, jac, [&] { *flag = 1; });
+            __syncthreads();
+            if (*flag == 0) return;
+        }
+        __syncthreads();  // the flag and the words have been read
     }
     const LdsLayout<A> lds = lds_layout<A, false>(lds_raw, a);
     const int4 *gi = a.group_info + 2 * (int64_t)p * a.merge;

@@ -27,6 +27,12 @@ int64_t lp_single_units(int n_vars, int max_k, int64_t max_m, int words, int jac
     return pe::single_launch_units(n_vars, max_k, max_m, words, jac != 0);
 }
 
+int64_t lp_add_skip_words(int64_t lds)
+{
+    size_t v = (size_t)lds;
+    return pe::add_skip_words(v) ? (int64_t)v : -1;
+}
+
 int lp_window(int d, int *check)
 {
     bool c;

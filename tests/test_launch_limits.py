@@ -66,7 +66,7 @@ def test_single_launch_fits_the_lds(probe, words):
                             assert probe.lp_small_lds(general, quot) >= max(general, quot + 4)
                         else:
                             refused += 1
-                            assert quot > LDS - 16
+                            assert quot > LDS - 80
                     assert not probe.lp_single(1281, 0, quot)
     assert taken and refused
 
@@ -119,3 +119,16 @@ def test_window_of_the_points(probe):
             assert 4 * d * top <= 400 and b >= 16 and d <= 5
             assert b <= last
             last = b
+
+
+def test_words_of_the_waves_fit(probe):
+    """16 words after a workgroup's tables, only where they cost no workgroup."""
+    probe.lp_add_skip_words.restype = C.c_int64
+    probe.lp_add_skip_words.argtypes = [C.c_int64]
+    for per_cu in range(1, 40):
+        most = LDS // per_cu
+        for lds in (most, most - 63, most - 64, most - 65):
+            if LDS // lds != per_cu:
+                continue
+            got = probe.lp_add_skip_words(lds)
+            assert got == (lds + 64 if lds + 64 <= most else -1)
