@@ -20,8 +20,8 @@
 // Bound: instruction issue (in double-double 38 FP64 instructions per factor
 // and 23 per scaled addition).  Against the general kernel's forward and
 // backward products, one MI355X: n = 512, m = 1024, k = 32, d = 5, 256 points
-// in double-double 58.2 -> 12.8 ms; n = 100, m = 200, k up to 16, 1000 points
-// in FP64 1130 -> 305 us; values only, n = 150, m = 299, k up to 12, 333
+// in double-double 58.2 -> 12.7 ms; n = 100, m = 200, k up to 16, 1000 points
+// in FP64 1130 -> 307 us; values only, n = 150, m = 299, k up to 12, 333
 // points in double-double 2912 -> 232 us.
 //
 // Rounding: a term takes k products where the other way takes about 2k, but

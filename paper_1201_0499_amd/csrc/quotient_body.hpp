@@ -346,12 +346,13 @@ __device__ __forceinline__ QuotLds<A> quot_lds(double2 *raw, const QuotArgs &a, 
 }
 
 // The power table and the reciprocals of points pt .. pt+npt-1 (callers add
-// the barrier), and with a.skip (SKIP: it may be set) the wave's word of `words`, and the marks of
-// those of the polynomials p, p + step, ... below p1 at such a point in which
-// every variable occurs.  A coordinate out of range becomes NaN in the table: the
-// values of the polynomials that contain it then are NaN too.  With a.sparse
-// only the variables that share a block of ranks with one of polynomial p, its
-// only one: what no term reads stays unset, and what multiplies no terms is 1.
+// the barrier).  A coordinate out of range becomes NaN in the table: the values
+// of the polynomials that contain it then are NaN too.  With a.skip (SKIP: it
+// may be set) also the wave's word of `words`, and the marks of those of the
+// polynomials p, p + step, ... below p1 at such a point in which every variable
+// occurs.  With a.sparse only the variables that share a block of ranks with
+// one of polynomial p, the workgroup's only one: what no term reads stays
+// unset, and what multiplies no terms is 1.
 template <class A, bool SKIP>
 __device__ __forceinline__ void quot_table(const QuotArgs &a, const QuotLds<A> &lds, int64_t pt, int npt, int p, int p1,
                                            int step, bool jac, uint32_t *words)
@@ -716,9 +717,10 @@ __device__ __forceinline__ void chunk_sums(const QuotArgs &a, int ci, const int4
 }
 
 // Polynomial p at the points from pt on, of which those with their bit set in
-// live are written (bad: see bad_point); vo is the buffer in use (it alternates).  FEW: lanes per
-// monomial and per run as the launch says (calls of few workgroups); else one
-// lane per monomial and two per run.  on_refused: see quot_store.
+// live are written (bad: see bad_point); vo is the buffer in use (it
+// alternates).  FEW: lanes per monomial and per run as the launch says (calls
+// of few workgroups); else one lane per monomial and two per run.  on_refused:
+// see quot_store.
 template <class A, bool FEW, class Refused>
 __device__ __forceinline__ void quot_poly(const QuotArgs &a, const QuotLds<A> &lds, int64_t pt, uint32_t live,
                                           bool bad, int p, int &vo, bool jac, const Refused &on_refused)

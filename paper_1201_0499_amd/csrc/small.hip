@@ -4,7 +4,7 @@
 // the general stages (eval.hip) itself, where larger calls leave the refused
 // ones to a second launch.  Bound: launch, point load and the chain of the
 // three stages; general kernel -> here, n = 128, m = 256, k = 16 at one point
-// in double-double 16.5 -> 10.4 us per call, in quad-double 117 -> 55 us.  Two
+// in double-double 16.5 -> 9.9 us per call, in quad-double 117 -> 57 us.  Two
 // launches cost about 4 us more.
 #include "eval_body.hpp"
 #include "quotient_body.hpp"

@@ -223,8 +223,8 @@ struct SlotExps {
 // the endgame's tolerance) any other rounding ends some path otherwise.
 // Latency is the bound, all of it being one dependent chain; hence one wave,
 // with no barriers, and one workgroup per path.  Quadrics, n = 10, all 1024
-// paths with the endgame: 71.2 ms in lockstep, 11.1 ms here (some 1170 rounds
-// of the slowest path at 9 us).
+// paths with the endgame: 71.2 ms in lockstep, 11.1 ms here (11 to 16 by card;
+// some 1170 rounds of the slowest path at 9 us).
 template <int NB, int CC>
 __global__ __launch_bounds__(64) void track_small_kernel(TrackArgs a, TrackTerms tt, int rounds)
 {
